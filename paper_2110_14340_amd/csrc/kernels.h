@@ -190,26 +190,32 @@ hipError_t launch_poison(void *base, size_t pitch_bytes, size_t width_bytes, int
 constexpr int kMlpHidden = 64;
 constexpr int kMlpMaxFeatures = 16;
 
+// Gradient partials of a training step: one set per workgroup, which walks
+// every kMlpGroups-th tile of 16 samples (64 sets of 37 KB: minibatches up
+// to 1024 samples spread one tile to a workgroup, and their sum stays a
+// short loop over independent loads).
+constexpr int kMlpGroups = 64;
+
 // Device buffers of one model: parameters, Adam moments, gradient, feature
-// scaler, and per-sample scratch for `cap` samples.
+// scaler, the workgroups' gradient partials and squared-error sums, and the
+// predictions of `cap` samples.
 struct MlpBufs {
     int F = 0, cap = 0;
     float *params = nullptr, *m = nullptr, *v = nullptr, *grad = nullptr, *mu = nullptr, *sd = nullptr;
-    float *xs = nullptr, *h1 = nullptr, *h2 = nullptr, *h3 = nullptr, *yhat = nullptr, *g = nullptr;
-    float *d1 = nullptr, *d2 = nullptr, *d3 = nullptr, *sqerr = nullptr;
-    float *loss = nullptr;  // loss of each training step
-    int64_t loss_at = 0;    // index written by the next backward pass
+    float *yhat = nullptr;
+    float *part = nullptr;    // kMlpGroups x parameters
+    double *sqerr = nullptr;  // kMlpGroups
+    float *loss = nullptr;    // loss of each training step
 };
 int mlp_nparams(int F);
-size_t mlp_lds_bytes(int F);
-// Forward pass of n samples (rows idx[b] of X, or row b when idx is null);
-// keep = store the activations for a backward pass.
-hipError_t mlp_forward(const MlpBufs &B, const float *X, const int *idx, int n, float *yhat, bool keep,
-                       hipStream_t s);
-// Deltas, parameter gradient (B.grad) and mean squared error (B.loss[loss_at])
-// of the last kept forward pass.
-hipError_t mlp_backward(const MlpBufs &B, const float *y, const int *idx, int n, hipStream_t s);
-// One Adam step (t is 1-based).
+// Forward pass of n samples.
+hipError_t mlp_forward(const MlpBufs &B, const float *X, int n, float *yhat, hipStream_t s);
+// Forward and backward pass of n samples (rows idx[b] of X and y, or row b
+// when idx is null): the parameter gradient (B.grad) and the mean squared
+// error (*loss), and for t > 0 the Adam step t (1-based) on it.
+hipError_t mlp_train(const MlpBufs &B, const float *X, const float *y, const int *idx, int n, int t, float lr,
+                     float *loss, hipStream_t s);
+// One Adam step (t is 1-based) on the last gradient.
 hipError_t mlp_adam(const MlpBufs &B, int t, float lr, hipStream_t s);
 
 }  // namespace jk

@@ -39,19 +39,8 @@ int alloc_f(jacc_model *m, size_t count, float **out) {
 
 int ensure_capacity(jacc_model *m, int n) {
     if (n <= m->B.cap) return JACC_OK;
-    const int F = m->B.F, H = jk::kMlpHidden;
-    jk::MlpBufs &B = m->B;
-    int rc = alloc_f(m, (size_t)n * F, &B.xs);
-    if (!rc) rc = alloc_f(m, (size_t)n * H, &B.h1);
-    if (!rc) rc = alloc_f(m, (size_t)n * H, &B.h2);
-    if (!rc) rc = alloc_f(m, (size_t)n * H, &B.h3);
-    if (!rc) rc = alloc_f(m, (size_t)n, &B.yhat);
-    if (!rc) rc = alloc_f(m, (size_t)n, &B.g);
-    if (!rc) rc = alloc_f(m, (size_t)n * H, &B.d1);
-    if (!rc) rc = alloc_f(m, (size_t)n * H, &B.d2);
-    if (!rc) rc = alloc_f(m, (size_t)n * H, &B.d3);
-    if (!rc) rc = alloc_f(m, (size_t)n, &B.sqerr);
-    if (!rc) B.cap = n;
+    int rc = alloc_f(m, (size_t)n, &m->B.yhat);
+    if (!rc) m->B.cap = n;
     return rc;
 }
 
@@ -99,6 +88,10 @@ int jacc_model_create(jacc_ctx *ctx, int nfeat, jacc_model **out) {
     if (!rc) rc = alloc_f(m, P, &B.grad);
     if (!rc) rc = alloc_f(m, nfeat, &B.mu);
     if (!rc) rc = alloc_f(m, nfeat, &B.sd);
+    if (!rc) rc = alloc_f(m, (size_t)jk::kMlpGroups * P, &B.part);
+    float *sq = nullptr;
+    if (!rc) rc = alloc_f(m, (size_t)jk::kMlpGroups * 2, &sq);
+    B.sqerr = (double *)sq;
     if (!rc) rc = ensure_loss(m, 1);
     if (!rc) {
         std::vector<float> zero(P, 0.f), one(nfeat, 1.f);
@@ -165,7 +158,7 @@ int jacc_model_predict(jacc_model *m, const float *X, int n, float *yhat) {
     if (rc) return rc;
     hipStream_t s = jr::stream0(m->ctx);
     MCHK(m, hipMemcpyAsync(dX, X, (size_t)n * m->B.F * sizeof(float), hipMemcpyHostToDevice, s), "hipMemcpyAsync");
-    MCHK(m, jk::mlp_forward(m->B, dX, nullptr, n, m->B.yhat, false, s), "mlp forward");
+    MCHK(m, jk::mlp_forward(m->B, dX, n, m->B.yhat, s), "mlp forward");
     MCHK(m, hipMemcpyAsync(yhat, m->B.yhat, (size_t)n * sizeof(float), hipMemcpyDeviceToHost, s), "hipMemcpyAsync");
     MCHK(m, hipStreamSynchronize(s), "hipStreamSynchronize");
     jr::release(m->ctx, dX);
@@ -175,18 +168,14 @@ int jacc_model_predict(jacc_model *m, const float *X, int n, float *yhat) {
 
 int jacc_model_gradients(jacc_model *m, const float *X, const float *y, int n, float *grad, float *loss) {
     if (bad(m) || !X || !y || n < 1) return JACC_ERR_INVALID;
-    int rc = ensure_capacity(m, n);
-    if (rc) return rc;
     float *dX = nullptr, *dy = nullptr;
-    rc = alloc_f(m, (size_t)n * m->B.F, &dX);
+    int rc = alloc_f(m, (size_t)n * m->B.F, &dX);
     if (!rc) rc = alloc_f(m, (size_t)n, &dy);
     if (rc) return rc;
     hipStream_t s = jr::stream0(m->ctx);
     MCHK(m, hipMemcpyAsync(dX, X, (size_t)n * m->B.F * sizeof(float), hipMemcpyHostToDevice, s), "hipMemcpyAsync");
     MCHK(m, hipMemcpyAsync(dy, y, (size_t)n * sizeof(float), hipMemcpyHostToDevice, s), "hipMemcpyAsync");
-    m->B.loss_at = 0;
-    MCHK(m, jk::mlp_forward(m->B, dX, nullptr, n, m->B.yhat, true, s), "mlp forward");
-    MCHK(m, jk::mlp_backward(m->B, dy, nullptr, n, s), "mlp backward");
+    MCHK(m, jk::mlp_train(m->B, dX, dy, nullptr, n, 0, 0.f, m->B.loss, s), "mlp gradients");
     const int P = jk::mlp_nparams(m->B.F);
     if (grad) MCHK(m, hipMemcpyAsync(grad, m->B.grad, P * sizeof(float), hipMemcpyDeviceToHost, s), "hipMemcpyAsync");
     if (loss) MCHK(m, hipMemcpyAsync(loss, m->B.loss, sizeof(float), hipMemcpyDeviceToHost, s), "hipMemcpyAsync");
@@ -210,8 +199,7 @@ int jacc_model_fit(jacc_model *m, const float *X, const float *y, int n, int epo
     if (bad(m) || !X || !y || n < 1 || epochs < 0 || batch < 1) return JACC_ERR_INVALID;
     const int bsz = batch < n ? batch : n;
     const int nb = (n + bsz - 1) / bsz;
-    int rc = ensure_capacity(m, bsz);
-    if (!rc) rc = ensure_loss(m, (int64_t)epochs * nb + 1);
+    int rc = ensure_loss(m, (int64_t)epochs * nb + 1);
     if (rc) return rc;
     float *dX = nullptr, *dy = nullptr, *didx = nullptr;
     rc = alloc_f(m, (size_t)n * m->B.F, &dX);
@@ -238,11 +226,9 @@ int jacc_model_fit(jacc_model *m, const float *X, const float *y, int n, int epo
         for (int k = 0; k < nb; ++k) {
             const int off = k * bsz;
             const int cnt = (off + bsz <= n) ? bsz : n - off;
-            m->B.loss_at = (int64_t)e * nb + k;
-            MCHK(m, jk::mlp_forward(m->B, dX, dperm + off, cnt, m->B.yhat, true, s), "mlp forward");
-            MCHK(m, jk::mlp_backward(m->B, dy, dperm + off, cnt, s), "mlp backward");
             m->step++;
-            MCHK(m, jk::mlp_adam(m->B, m->step, lr, s), "mlp adam");
+            MCHK(m, jk::mlp_train(m->B, dX, dy, dperm + off, cnt, m->step, lr, m->B.loss + (int64_t)e * nb + k, s),
+                 "mlp training step");
         }
     }
     if (epoch_loss && epochs > 0) {

@@ -121,3 +121,48 @@ def test_training_lowers_loss_and_generalises():
         m.close()
     assert losses[-1] < 0.2 * losses[0]
     assert np.mean((pred - y[2500:]) ** 2) < 0.2 * np.var(y[2500:])
+
+
+@pytest.mark.parametrize("F,n", [(13, 1), (1, 15), (4, 16), (13, 17), (16, 1024), (13, 1025), (3, 2500)])
+def test_tiles_of_samples_at_their_edges(F, n):
+    """Sample counts around the 16-sample tiles and beyond one tile per
+    workgroup (64 x 16), features from 1 to 16: forward, loss and every
+    gradient against the FP64 oracle within the bound of the test above."""
+    say(f"mlp tiles F={F} n={n}")
+    X, y, P = _problem(F, n, seed=F + 10 * n)
+    ref_P = {k: v.astype(np.float64) for k, v in P.items()}
+    with context(1) as c:
+        m = jacc.Model(c, F)
+        m.set_params(P)
+        yhat = m.predict(X)
+        loss, g = m.gradients(X, y)
+        again = m.gradients(X, y)
+        m.close()
+    assert again[0] == loss and all(np.array_equal(again[1][k], g[k]) for k in g)  # every sum in a fixed order
+    ref_yhat, _ = omlp.forward(ref_P, X.astype(np.float64))
+    assert _rel(yhat, ref_yhat) <= 1e-4
+    ref_loss, ref_g = omlp.gradients(ref_P, X.astype(np.float64), y.astype(np.float64))
+    assert abs(loss - ref_loss) <= 1e-4 * ref_loss
+    for k in omlp.PARAM_NAMES:
+        assert _rel(g[k], ref_g[k]) <= 1e-4, k
+
+
+def test_training_steps_equal_gradients_and_adam_steps():
+    """A fit of one sample, where the sample order leaves nothing open, takes
+    the same steps as separate gradient and Adam calls, bit for bit."""
+    say("mlp fit = gradients + adam")
+    X, y, P = _problem(13, 1, seed=8)
+    with context(1) as c:
+        m = jacc.Model(c, 13)
+        m.set_params(P)
+        losses = m.train(X, y, epochs=3, batch=5)
+        fitted = m.get_params()
+        m.set_params(P)
+        for t in range(3):
+            loss, _ = m.gradients(X, y)
+            assert losses[t] == np.float32(loss)
+            m.adam_step(1e-3)
+        stepped = m.get_params()
+        m.close()
+    for k in P:
+        assert np.array_equal(fitted[k], stepped[k]), k
