@@ -168,8 +168,8 @@ typedef struct {
  * which a reduction adds its terms does depend on it.
  *   bx, by     workgroup shape in threads (bx a multiple of 64; bx*by <= 1024)
  *   tile       rows (2-D) or planes (3-D) each thread marches through;
- *              GEMM: k-slab depth staged through LDS, 16 or 32 (with bx =
- *              256 or 512 threads per 128x128 tile); SPMV_CSR: lanes per
+ *              GEMM: 16 or 32 (and bx 256 or 512), without effect: the tile
+ *              follows from the shape, the bits do not; SPMV_CSR: lanes per
  *              row, 4, 8 or 16 (order 2 = non-temporal col/val loads), or
  *              with order 4 (column bands) lanes per row and band, 1 to 16,
  *              by = bands per XCD (1, 2, 4, 8), rows = rows per lane (2 or 4

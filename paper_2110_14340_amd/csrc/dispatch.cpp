@@ -40,10 +40,10 @@ Cfg default_config(int kind, const Launch &L, Cfg c) {
             if (!c.march) c.march = 2;
             break;
         default:
-            if (!c.bx) c.bx = kind == JACC_LOOP_GEMM ? 512 : 256;  // GEMM: 8 waves of 64x32 measured faster
+            if (!c.bx) c.bx = 256;
             if (!c.by) c.by = 1;
-            // measured: GEMM 16-deep slabs; SpMV 16 lanes per row (one gather
-            // per lane for ~16 non-zeros) with non-temporal col/val loads
+            // measured: SpMV 16 lanes per row (one gather per lane for ~16
+            // non-zeros) with non-temporal col/val loads
             if (!c.tile) c.tile = kind == JACC_LOOP_GEMM ? 16 : kind == JACC_LOOP_SPMV_CSR ? 16 : 1;
             if (!c.vec) c.vec = 1;
             if (!c.order) c.order = kind == JACC_LOOP_SPMV_CSR ? 2 : 1;
@@ -72,7 +72,7 @@ int check_config(const Launch &L) {
             if (c.rows != 1 && c.bx * c.by > 256) return 1;  // multi-row waves: workgroups of at most 256
             return 0;
         case JACC_LOOP_GEMM:
-            // k-slab depth and workgroup size; other fields are ignored
+            // the values earlier kernels took; the kernel chooses its tile by shape
             return ((c.tile == 16 || c.tile == 32) && (c.bx == 256 || c.bx == 512)) ? 0 : 1;
         case JACC_LOOP_SPMV_CSR:
             // order 4: column-banded, by = bands per XCD, tile = lanes per

@@ -245,3 +245,36 @@ def test_gemm_shared_b_equals_replicated(M, N, L, K):
     say(f"gemm shared B {M}x{N}x{L} K={K}")
     A, B = inputs.gemm_inputs(M, N, L, seed=M + K)
     assert np.array_equal(_gemm_dev(A, B, K, whole=jacc.SHARED), _gemm_dev(A, B, K))
+
+
+@pytest.mark.parametrize("M,N,L", [(1, 1, 1), (17, 1, 9), (1, 2, 8), (33, 31, 7), (64, 63, 16), (65, 129, 71),
+                                   (97, 40, 515), (513, 517, 24), (700, 1100, 40)])
+def test_gemm_tiles_edges_boxes_and_nonfinite_rows(M, N, L):
+    """Shapes around the wave tiles (16x32 to 64x64), the 8-deep stages and
+    the 16-byte pairs (odd rows, one column): the product against the oracle
+    (exact for integer inputs), a box whose edges cut pairs and tiles leaves
+    the rest of C alone and has the same bits as the whole product, and an
+    infinity in A's last row and a NaN in B's last column reach only that row
+    and column."""
+    say(f"gemm tiles {M}x{N}x{L}")
+    Ai, Bi = inputs.gemm_inputs(M, N, L, seed=M + L, integer=True)
+    assert np.array_equal(_gemm_dev(Ai, Bi, 1), oracle.gemm(Ai, Bi))
+    A, B = inputs.gemm_inputs(M, N, L, seed=M + N)
+    full = _gemm_dev(A, B, 1)
+    assert np.linalg.norm(full - oracle.gemm(A, B)) <= 1e-12 * np.linalg.norm(A) * np.linalg.norm(B)
+    for r0, r1, c0, c1 in ((0, M, N - 1, N), (M // 3, M, N // 2, N), (0, (M + 1) // 2, N // 3, max(N // 3, N - 1))):
+        C = np.full((M, N), 7.0)
+        want = C.copy()
+        want[r0:r1, c0:c1] = full[r0:r1, c0:c1]
+        with context(1) as c:
+            c.enter(A)
+            c.enter(B, whole=True)
+            c.enter(C)
+            c.loop(jacc.GEMM, jacc.bounds((r0, r1), (c0, c1)),
+                   [(A, jacc.READ, 0, 0, 0), (B, jacc.READ, 0, 0, 1), (C, jacc.WRITE, 0, 0, 0)])
+            c.exit(C)
+        assert np.array_equal(C, want), (r0, r1, c0, c1)
+    A[-1, -1], B[0, -1] = np.inf, np.nan
+    got = _gemm_dev(A, B, 1)
+    assert np.array_equal(got[:-1, :-1], full[:-1, :-1])
+    assert not np.isfinite(got[-1]).any() and np.isnan(got[:, -1]).all()
