@@ -32,7 +32,7 @@
  *     row), so no copy is needed at all.  Both replace the paper's
  *     send-everything-after-each-kernel scheme with range-driven transfers.
  *   - Asynchrony: partition p's work runs on stream p (outside batches the
- *     partitions of a JACOBI2D, HEAT3D, SUM or column-banded SPMV_CSR loop
+ *     partitions of a JACOBI2D, HEAT3D, SUM or binned SPMV_CSR loop
  *     instead run as one packed launch on one stream; see
  *     JACC_INIT_NO_PACK).  Cross-stream waits are inserted only for the
  *     rows actually shared (read-after-write and write-after-read),
@@ -170,18 +170,19 @@ typedef struct {
  *   tile       rows (2-D) or planes (3-D) each thread marches through;
  *              GEMM: 16 or 32 (and bx 256 or 512), without effect: the tile
  *              follows from the shape, the bits do not; SPMV_CSR: lanes per
- *              row, 4, 8 or 16 (order 2 = non-temporal col/val loads), or
- *              with order 4 (column bands) lanes per row and band, 1 to 16,
- *              by = bands per XCD (1, 2, 4, 8), rows = rows per lane (2 or 4
- *              with one lane).  The banded form copies each partition's
- *              entries once into band-major order on the device (kept until
- *              row_ptr, col or val change), runs the bands of XCD j on XCD j
- *              so that its slice of x stays in that XCD's L2, and adds each
- *              row's band sums in band order: within the SpMV bound of the
- *              plain order, and the same bits for every partition count.  It
+ *              row, 4, 8 or 16 (default by the matrix's mean row length; order
+ *              2 = non-temporal col/val loads), or with order 4 (binned) 1 to
+ *              16, by 1, 2, 4 or 8, and rows 2 or 4 with tile 1, without
+ *              effect.  The binned form copies the matrix's entries once on
+ *              the device, ordered by column block (kept until row_ptr, col or
+ *              val change), multiplies them against the block's x in LDS and
+ *              adds each row's products in the plain form's order: within the
+ *              SpMV bound, and the same bits for every partition count.  It
  *              is the default when x has at least 2^20 elements, except
  *              inside batches, which capture the plain form (an explicit
- *              order 4 there returns JACC_ERR_UNSUPPORTED).
+ *              order 4 there returns JACC_ERR_UNSUPPORTED); where the device
+ *              memory of the copy (20 bytes an entry) is not to be had, the
+ *              plain form runs.
  *   vec        1 or 2 consecutive FP64 elements per lane (2 needs an even row
  *              length)
  *   persistent 1 = run the loop inside the batched persistent kernel
@@ -293,14 +294,14 @@ enum {
                                       --marker-trace */
     JACC_INIT_NO_PACK = 1u << 10   /* a launch per partition on its own stream for every loop.
                                       Default: outside batches, a JACOBI2D, HEAT3D, SUM or
-                                      column-banded SPMV_CSR loop of 2 to 16 row-split partitions
+                                      binned SPMV_CSR loop of 2 to 16 row-split partitions
                                       (JACOBI2D also over arrays split along dim 1)
                                       without a FILTERED output runs all its partitions in one
                                       launch on one stream, each partition's tiles a run of the
                                       workgroups, in the loop's configuration (halo pulls before
                                       it, mirror stores inside it; reductions finalised per
                                       partition by one launch and combined in partition order,
-                                      banded products combined by one launch: the same bits as a
+                                      binned products by two launches: the same bits as a
                                       launch per partition); JACC_INIT_SPLIT, SERIALIZE,
                                       per-partition timing, and reductions whose workgroup
                                       partials of all partitions exceed the stream's buffer keep

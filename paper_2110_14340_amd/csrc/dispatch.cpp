@@ -42,8 +42,8 @@ Cfg default_config(int kind, const Launch &L, Cfg c) {
         default:
             if (!c.bx) c.bx = 256;
             if (!c.by) c.by = 1;
-            // measured: SpMV 16 lanes per row (one gather per lane for ~16
-            // non-zeros) with non-temporal col/val loads
+            // SpMV: non-temporal col/val loads; the runtime sets the lanes per
+            // row by the matrix's mean row length
             if (!c.tile) c.tile = kind == JACC_LOOP_GEMM ? 16 : kind == JACC_LOOP_SPMV_CSR ? 16 : 1;
             if (!c.vec) c.vec = 1;
             if (!c.order) c.order = kind == JACC_LOOP_SPMV_CSR ? 2 : 1;
@@ -75,8 +75,8 @@ int check_config(const Launch &L) {
             // the values earlier kernels took; the kernel chooses its tile by shape
             return ((c.tile == 16 || c.tile == 32) && (c.bx == 256 || c.bx == 512)) ? 0 : 1;
         case JACC_LOOP_SPMV_CSR:
-            // order 4: column-banded, by = bands per XCD, tile = lanes per
-            // row and band (1 to 16)
+            // order 4: the binned form; tile, by and rows take the values that
+            // an earlier form split its work by, without effect
             if (c.order == 4)
                 return ((c.tile == 1 || c.tile == 2 || c.tile == 4 || c.tile == 8 || c.tile == 16) &&
                         (c.by == 1 || c.by == 2 || c.by == 4 || c.by == 8) &&

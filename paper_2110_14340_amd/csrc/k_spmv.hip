@@ -1,8 +1,8 @@
 // CSR sparse matrix-vector product for gfx950: the plain row-parallel form
-// and a column-banded form for x vectors larger than an XCD's L2.
+// and a binned form for x vectors larger than an XCD's L2.
 //
-// G lanes cooperate on one row (G = 4, 8 or 16; 16 by default for ~16
-// non-zeros per row: one gather per lane): lane g of the group adds val[k]*x[col[k]] for k = row_ptr[i] + g,
+// Plain form: G lanes cooperate on one row (G = 4, 8 or 16, by the mean row
+// length): lane g of the group adds val[k]*x[col[k]] for k = row_ptr[i] + g,
 // + g + G, ... in increasing k, then the group adds its lanes by a fixed
 // butterfly.  col/val reads of a group are contiguous; x is gathered.
 #include "k_common.h"
@@ -13,6 +13,26 @@ namespace jk {
 namespace {
 
 constexpr int kSpmvThreads = 256;
+
+// v of another lane of its row of 16 lanes, by a DPP pattern.
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, true);
+    return __hiloint2double(hi, lo);
+}
+
+// Sum over each aligned group of G lanes by the butterfly xor 1, 2, 4, 8.  Once
+// the lanes of a quad hold the same value, mirroring 8 lanes reaches the
+// same value as xor 4 does, and mirroring 16 as xor 8.
+template <int G>
+__device__ __forceinline__ double group_sum(double s) {
+    s += dpp<0xB1>(s);                          // quad_perm 1 0 3 2
+    s += dpp<0x4E>(s);                          // quad_perm 2 3 0 1
+    if constexpr (G >= 8) s += dpp<0x141>(s);   // row_half_mirror
+    if constexpr (G >= 16) s += dpp<0x140>(s);  // row_mirror
+    return s;
+}
 
 template <int G, bool NT>
 __global__ void __launch_bounds__(kSpmvThreads)
@@ -33,378 +53,529 @@ spmv_kernel(const int32_t *__restrict__ rp, const int32_t *__restrict__ col, con
             s += v * x[c];
         }
     }
-#pragma unroll
-    for (int m = 1; m < G; m <<= 1) s += __shfl_xor(s, m, kWave);
+    s = group_sum<G>(s);
     if (live && g == 0) y[i] = s;
 }
 
 // ---------------------------------------------------------------------------
-// Column-banded form.  The columns are cut into B = 8*S bands of width W; a
-// partition's entries are copied once into band-major order (all of band 0's
-// entries row by row, then band 1's, ...), keeping their order inside each
-// row and band.  Workgroup b of the banded launch runs on XCD b mod 8 and
-// handles only the S bands of that XCD, one after the other, so the x values
-// an XCD gathers at any time (one band, ncols/B doubles) stay in its L2
-// instead of crossing the fabric once per gathered double.  Each row's band
-// sums go to a partial array; a second kernel adds them in band order.
+// Binned form.  What bounds the plain form is its gathers of x: each reads a
+// 128-byte line through L1 (and, for an x beyond an XCD's 4 MB L2, mostly
+// through the fabric) for 8 bytes of it.  Here every gather is an LDS access.
+//
+// The columns are cut into column blocks of kBinCols (an x segment of 128 KB
+// in LDS), the rows into row blocks whose entries fit LDS, and the matrix's
+// entries are copied once into column-block-major order, each column block's
+// entries by row block (the bucket of row block r and column block c is a
+// contiguous run).  A product is two launches:
+//   multiply: each workgroup takes an equal share of that order, keeps the
+//     current column block's x segment in LDS and streams
+//     prod[i] = bval[i] * x[bcol[i]], all accesses contiguous;
+//   sum: each workgroup takes a row block, copies its buckets' products to LDS
+//     at the entries' places in the row order (dst) and adds each row's
+//     products as the plain form does: lane g of G adds entries g, g + G, ...
+//     in increasing k, then a fixed butterfly.
+// The order inside a bucket is whatever the build left; the sums do not
+// depend on it, nor on the row blocks, so y has the same bits for every
+// partition count.  A row block with more entries than LDS holds keeps no
+// buckets and is summed straight from the CSR arrays in the same order.
+//
+// An entry costs 8 + 2 bytes read and 8 written, then 8 + 2 read: 1.9 GB for
+// 2^22 rows of 16.  Measured there: multiply 246 us (5.3 TB/s), sum 226 us
+// (3.1 TB/s: see its comment), one-time copy 540 us; a form that walked one
+// eighth of the columns per XCD took 841 us (its gathers 786, each a line from
+// L2) and 5.3 ms for its copy, the plain form 1122 us.  2^20 rows of 16: 118
+// us, plain 181; 2^19 rows: 72 us, plain 65, so the plain form stays the
+// default below 2^20 columns.
 // ---------------------------------------------------------------------------
-constexpr int kBandThreads = 256;
-constexpr int kScanThreads = 1024;
-constexpr int kScanPer = 8;  // elements per thread in a scan block
+constexpr int kBinShift = 14;
+constexpr int kBinCols = 1 << kBinShift;  // x elements per column block (128 KB of LDS)
+constexpr int kBinMaxRows = 1024;         // rows per row block
+constexpr int kBinCap = 9600;             // products a row block may have in LDS (with its row pointers 80 KB: two per CU)
+constexpr int kBinTarget = 7424;          // entries a row block is sized for at the matrix's mean row length
+constexpr int kMulThreads = 1024;
+constexpr int kMulGroups = 512;
+constexpr int kSumRowThreads = 512;
+constexpr int kSegments = 64;             // of row blocks, in the scan of the bucket sizes
+constexpr int kPad = 64;                  // entries to which a column block's start is aligned
 
-// cnt[b*n + r] = entries of row r0 + r whose column lies in band b
-__global__ void band_count_kernel(const int32_t *__restrict__ rp, const int32_t *__restrict__ col, int64_t r0,
-                                  int64_t n, int64_t W, int B, int32_t *__restrict__ cnt) {
-    const int64_t r = (int64_t)blockIdx.x * kBandThreads + threadIdx.x;
-    if (r >= n) return;
-    const int32_t kb = rp[r0 + r], ke = rp[r0 + r + 1];
-    for (int b = 0; b < B; ++b) {
-        int32_t c = 0;
-        for (int32_t k = kb; k < ke; ++k) c += (col[k] / W == b) ? 1 : 0;
-        cnt[(int64_t)b * n + r] = c;
-    }
+struct BinPart {
+    const int32_t *rp;  // biased: rp[row]
+    double *y;          // biased: y[row]
+    int64_t r0, r1;
+    int64_t blk;        // its first row block
+};
+struct BinParts {
+    BinPart p[kMaxPack];
+    int32_t n;
+};
+typedef const __attribute__((address_space(4))) BinPart ConstBinPart;
+
+// Rows [lo, hi) of row block `blk`, and its partition's pointers.
+struct BinBlock {
+    const int32_t *rp;
+    double *y;
+    int64_t lo;
+    int rows;
+    int32_t e0, m;  // its first entry and entry count
+};
+__device__ __forceinline__ BinBlock bin_block(const BinParts &bp, int64_t blk, int rb) {
+    ConstBinPart *cp = (ConstBinPart *)&bp.p[0];
+    int q = 0;
+    for (int k = 1; k < bp.n; ++k)
+        if (cp[k].blk <= blk) q = k;
+    BinBlock B;
+    B.rp = cp[q].rp;
+    B.y = cp[q].y;
+    B.lo = cp[q].r0 + (blk - cp[q].blk) * rb;
+    const int64_t left = cp[q].r1 - B.lo;
+    B.rows = (int)(left < rb ? left : rb);
+    B.e0 = B.rp[B.lo];
+    B.m = B.rp[B.lo + B.rows] - B.e0;
+    return B;
 }
 
-// exclusive scan of v[0, len) in blocks of kScanThreads*kScanPer: out gets
-// each element's offset inside its block, sums[blk] the block total
-__global__ void __launch_bounds__(kScanThreads)
-scan_blocks_kernel(const int32_t *__restrict__ v, int64_t len, int32_t *__restrict__ out, int32_t *__restrict__ sums) {
-    __shared__ int32_t sh[kScanThreads];
-    const int64_t base = (int64_t)blockIdx.x * kScanThreads * kScanPer + (int64_t)threadIdx.x * kScanPer;
-    int32_t loc[kScanPer];
+// Row block of a workgroup: the grid is a multiple of 8, and XCD x (workgroups
+// b with b mod 8 = x) takes the x-th contiguous eighth of the blocks, so the
+// lines that neighbouring blocks' buckets share are used in one L2.
+__device__ __forceinline__ int64_t bin_order() {
+    const int64_t b = blockIdx.x;
+    return (b & 7) * (gridDim.x >> 3) + (b >> 3);
+}
+
+// ---- build ------------------------------------------------------------------
+// cnt[blk][c] = entries of row block blk in column block c (none for a block
+// beyond LDS)
+__global__ void __launch_bounds__(512)
+bin_count_kernel(BinParts bp, const int32_t *__restrict__ col, int rb, int nblk, int nc, uint16_t *__restrict__ cnt) {
+    extern __shared__ int32_t hist[];
+    const int64_t blk = bin_order();
+    if (blk >= nblk) return;
+    const BinBlock B = bin_block(bp, blk, rb);
+    for (int c = threadIdx.x; c < nc; c += blockDim.x) hist[c] = 0;
+    __syncthreads();
+    if (B.m <= kBinCap)
+        for (int32_t i = threadIdx.x; i < B.m; i += blockDim.x) atomicAdd(&hist[col[(int64_t)B.e0 + i] >> kBinShift], 1);
+    __syncthreads();
+    for (int c = threadIdx.x; c < nc; c += blockDim.x) cnt[blk * nc + c] = (uint16_t)hist[c];
+}
+
+// Totals of each column block over each of the kSegments segments of row
+// blocks: segs[seg * nc + c].  Workgroups of 64 columns x 16 lanes.
+__global__ void __launch_bounds__(1024)
+bin_segments_kernel(const uint16_t *__restrict__ cnt, int nblk, int nc, int per, int32_t *__restrict__ segs) {
+    __shared__ int32_t sh[16][64];
+    const int c = blockIdx.x * 64 + (threadIdx.x & 63), j = threadIdx.x >> 6;
+    const int lo = blockIdx.y * per, hi = lo + per < nblk ? lo + per : nblk;
     int32_t t = 0;
-#pragma unroll
-    for (int u = 0; u < kScanPer; ++u) {
-        loc[u] = t;
-        t += base + u < len ? v[base + u] : 0;
-    }
-    sh[threadIdx.x] = t;
+    if (c < nc)
+        for (int b = lo + j; b < hi; b += 16) t += cnt[(int64_t)b * nc + c];
+    sh[j][threadIdx.x & 63] = t;
     __syncthreads();
-    for (int off = 1; off < kScanThreads; off <<= 1) {  // inclusive scan of the thread totals
-        const int32_t add = threadIdx.x >= (unsigned)off ? sh[threadIdx.x - off] : 0;
-        __syncthreads();
-        sh[threadIdx.x] += add;
-        __syncthreads();
+    if (j == 0 && c < nc) {
+        for (int k = 1; k < 16; ++k) t += sh[k][threadIdx.x];
+        segs[(int64_t)blockIdx.y * nc + c] = t;
     }
-    const int32_t before = threadIdx.x > 0 ? sh[threadIdx.x - 1] : 0;
-#pragma unroll
-    for (int u = 0; u < kScanPer; ++u)
-        if (base + u < len) out[base + u] = before + loc[u];
-    if (threadIdx.x == kScanThreads - 1) sums[blockIdx.x] = sh[kScanThreads - 1];
 }
 
-// exclusive scan of the nb block totals in place (one workgroup; nb is at
-// most kScanThreads*kScanPer), and the grand total at sums[nb]
-__global__ void __launch_bounds__(kScanThreads) scan_sums_kernel(int32_t *__restrict__ sums, int64_t nb) {
-    __shared__ int32_t sh[kScanThreads];
-    const int64_t base = (int64_t)threadIdx.x * kScanPer;
-    int32_t loc[kScanPer];
+// One workgroup: the start of every column block, aligned to kPad entries
+// (cbase[c]; cbase[nc] the end), and segs turned into the start of each
+// segment within it.
+__global__ void __launch_bounds__(1024) bin_bases_kernel(int nc, int32_t *__restrict__ segs, int32_t *__restrict__ cbase) {
+    __shared__ int32_t sh[1024];
+    int32_t before = 0;
+    for (int c0 = 0; c0 < nc; c0 += 1024) {
+        const int c = c0 + threadIdx.x;
+        int32_t total = 0;
+        if (c < nc)
+#pragma unroll 16
+            for (int g = 0; g < kSegments; ++g) total += segs[(int64_t)g * nc + c];
+        const int32_t padded = (total + kPad - 1) / kPad * kPad;
+        sh[threadIdx.x] = padded;
+        __syncthreads();
+        for (int off = 1; off < 1024; off <<= 1) {
+            const int32_t add = (int)threadIdx.x >= off ? sh[threadIdx.x - off] : 0;
+            __syncthreads();
+            sh[threadIdx.x] += add;
+            __syncthreads();
+        }
+        int32_t at = before + sh[threadIdx.x] - padded;
+        before += sh[1023];
+        if (c < nc) {
+            cbase[c] = at;
+            for (int g0 = 0; g0 < kSegments; g0 += 16) {
+                int32_t v[16];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) v[u] = segs[(int64_t)(g0 + u) * nc + c];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) {
+                    segs[(int64_t)(g0 + u) * nc + c] = at;
+                    at += v[u];
+                }
+            }
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) cbase[nc] = before;
+}
+
+// start[blk][c]: lane j of a column takes the j-th sixteenth of the segment.
+__global__ void __launch_bounds__(1024)
+bin_starts_kernel(const uint16_t *__restrict__ cnt, int nblk, int nc, int per, const int32_t *__restrict__ segs,
+                  int32_t *__restrict__ start) {
+    __shared__ int32_t sh[16][64];
+    const int cl = threadIdx.x & 63, c = blockIdx.x * 64 + cl, j = threadIdx.x >> 6;
+    const int lo = blockIdx.y * per, hi = lo + per < nblk ? lo + per : nblk;
+    const int sub = (per + 15) / 16, b0 = lo + j * sub, b1 = b0 + sub < hi ? b0 + sub : hi;
     int32_t t = 0;
-#pragma unroll
-    for (int u = 0; u < kScanPer; ++u) {
-        loc[u] = t;
-        t += base + u < nb ? sums[base + u] : 0;
-    }
-    sh[threadIdx.x] = t;
+    if (c < nc)
+        for (int b = b0; b < b1; ++b) t += cnt[(int64_t)b * nc + c];
+    sh[j][cl] = t;
     __syncthreads();
-    for (int off = 1; off < kScanThreads; off <<= 1) {
-        const int32_t add = threadIdx.x >= (unsigned)off ? sh[threadIdx.x - off] : 0;
-        __syncthreads();
-        sh[threadIdx.x] += add;
-        __syncthreads();
+    if (c >= nc) return;
+    int32_t at = segs[(int64_t)blockIdx.y * nc + c];
+    for (int k = 0; k < j; ++k) at += sh[k][cl];
+    for (int b = b0; b < b1; ++b) {
+        start[(int64_t)b * nc + c] = at;
+        at += cnt[(int64_t)b * nc + c];
     }
-    const int32_t before = threadIdx.x > 0 ? sh[threadIdx.x - 1] : 0;
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < kScanPer; ++u)
-        if (base + u < nb) sums[base + u] = before + loc[u];
-    if (threadIdx.x == kScanThreads - 1) sums[nb] = sh[kScanThreads - 1];
 }
 
-__global__ void scan_add_kernel(int32_t *__restrict__ out, int64_t len, const int32_t *__restrict__ sums) {
-    const int64_t i = (int64_t)blockIdx.x * kBandThreads + threadIdx.x;
-    if (i < len) out[i] += sums[i / ((int64_t)kScanThreads * kScanPer)];
-    if (i == len) out[len] = sums[(len + (int64_t)kScanThreads * kScanPer - 1) / ((int64_t)kScanThreads * kScanPer)];
+// Copies a row block's entries into their buckets: value, column within the
+// column block, place within the row block.  SORT: the entries are ordered by
+// bucket in LDS first, so that a bucket is written by neighbouring lanes
+// (2^22 rows of 16: 2.6 ms with each lane writing its own entry's bucket);
+// the column blocks' counters then have to fit beside them.
+constexpr int kSortCols = 2048;
+template <bool SORT>
+__global__ void __launch_bounds__(1024)
+bin_fill_kernel(BinParts bp, const int32_t *__restrict__ col, const double *__restrict__ val, int rb, int nblk, int nc,
+                const int32_t *__restrict__ start, const uint16_t *__restrict__ cnt, double *__restrict__ bval,
+                uint16_t *__restrict__ bcol, uint16_t *__restrict__ dst) {
+    extern __shared__ int32_t at[];  // next free entry of each bucket
+    __shared__ double sval[SORT ? kBinCap : 1];
+    __shared__ int32_t scol[SORT ? kBinCap : 1];
+    __shared__ uint16_t sdst[SORT ? kBinCap : 1];
+    __shared__ int32_t shift[SORT ? kSortCols : 1];  // a bucket's start in memory minus that in LDS
+    __shared__ int32_t sums[1024 / kWave];
+    const int64_t blk = bin_order();
+    if (blk >= nblk) return;
+    const BinBlock B = bin_block(bp, blk, rb);
+    if (B.m > kBinCap) return;
+    const int tid = threadIdx.x;
+    if constexpr (!SORT) {
+        for (int c = tid; c < nc; c += 1024) at[c] = start[blk * nc + c];
+        __syncthreads();
+        for (int32_t i = tid; i < B.m; i += 1024) {
+            const int32_t c = col[(int64_t)B.e0 + i];
+            const int32_t k = atomicAdd(&at[c >> kBinShift], 1);
+            bval[k] = val[(int64_t)B.e0 + i];
+            bcol[k] = (uint16_t)(c & (kBinCols - 1));
+            dst[k] = (uint16_t)i;
+        }
+    } else {
+        // exclusive scan of the bucket sizes, two columns per thread
+        const int c = 2 * tid;
+        const int32_t n0 = c < nc ? cnt[blk * nc + c] : 0, n1 = c + 1 < nc ? cnt[blk * nc + c + 1] : 0;
+        int32_t t = n0 + n1;
+#pragma unroll
+        for (int m = 1; m < kWave; m <<= 1) {
+            const int32_t o = __shfl_up(t, m, kWave);
+            if ((tid & (kWave - 1)) >= m) t += o;
+        }
+        if ((tid & (kWave - 1)) == kWave - 1) sums[tid / kWave] = t;
+        __syncthreads();
+        for (int w = 0; w < tid / kWave; ++w) t += sums[w];
+        const int32_t before = t - n0 - n1;
+        if (c < nc) {
+            at[c] = before;
+            shift[c] = start[blk * nc + c] - before;
+        }
+        if (c + 1 < nc) {
+            at[c + 1] = before + n0;
+            shift[c + 1] = start[blk * nc + c + 1] - before - n0;
+        }
+        __syncthreads();
+#pragma unroll 4
+        for (int32_t i = tid; i < B.m; i += 1024) {
+            const int32_t cc = col[(int64_t)B.e0 + i];
+            const double x = val[(int64_t)B.e0 + i];
+            const int32_t k = atomicAdd(&at[cc >> kBinShift], 1);
+            sval[k] = x;
+            scol[k] = cc;
+            sdst[k] = (uint16_t)i;
+        }
+        __syncthreads();
+        for (int32_t k = tid; k < B.m; k += 1024) {
+            const int32_t cc = scol[k], to = k + shift[cc >> kBinShift];
+            bval[to] = sval[k];
+            bcol[to] = (uint16_t)(cc & (kBinCols - 1));
+            dst[to] = sdst[k];
+        }
+    }
 }
 
-// copies row r's entries into band-major order at the offsets bptr gives
-__global__ void band_fill_kernel(const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
-                                 const double *__restrict__ val, int64_t r0, int64_t n, int64_t W, int B,
-                                 const int32_t *__restrict__ bptr, int32_t *__restrict__ bcol,
-                                 double *__restrict__ bval) {
-    const int64_t r = (int64_t)blockIdx.x * kBandThreads + threadIdx.x;
-    if (r >= n) return;
-    const int32_t kb = rp[r0 + r], ke = rp[r0 + r + 1];
-    for (int b = 0; b < B; ++b) {
-        int32_t pos = bptr[(int64_t)b * n + r];
-        for (int32_t k = kb; k < ke; ++k) {
-            const int32_t c = col[k];
-            if (c / W == b) {
-                bcol[pos] = c;
-                bval[pos] = val[k];
-                ++pos;
+// ---- product ----------------------------------------------------------------
+typedef uint16_t us4 __attribute__((ext_vector_type(4)));
+typedef uint16_t us2u __attribute__((ext_vector_type(2), aligned(2)));
+typedef double pair_u __attribute__((ext_vector_type(2), aligned(8)));
+
+// prod = bval * x[bcol] over this workgroup's share of the column-block-major
+// order.  The entries that align a column block's start hold anything: their
+// column is masked to the segment, their product is never read.
+__global__ void __launch_bounds__(kMulThreads)
+bin_multiply_kernel(const int32_t *__restrict__ cbase, int nc, int64_t ncols, const double *__restrict__ x,
+                    const double *__restrict__ bval, const uint16_t *__restrict__ bcol, double *__restrict__ prod) {
+    __shared__ double xs[kBinCols];
+    const int64_t total = cbase[nc];
+    const int64_t per = ((total + gridDim.x - 1) / gridDim.x + kPad - 1) / kPad * kPad;
+    int64_t i0 = blockIdx.x * per;
+    const int64_t i1 = i0 + per < total ? i0 + per : total;
+    if (i0 >= i1) return;
+    int c = 0;
+    for (int lo = 0, hi = nc - 1; lo <= hi;) {  // the last column block starting at or before i0
+        const int mid = (lo + hi) >> 1;
+        if (cbase[mid] <= i0) {
+            c = mid;
+            lo = mid + 1;
+        } else {
+            hi = mid - 1;
+        }
+    }
+    for (; i0 < i1; ++c) {
+        const int64_t end = cbase[c + 1] < i1 ? cbase[c + 1] : i1;
+        if (end <= i0) continue;
+        const double *seg = x + ((int64_t)c << kBinShift);
+        const int64_t len = ncols - ((int64_t)c << kBinShift);
+        __syncthreads();  // every wave is done with the previous segment
+#pragma unroll 8
+        for (int k = threadIdx.x; k < kBinCols; k += kMulThreads) xs[k] = k < len ? seg[k] : 0.0;
+        __syncthreads();
+        auto four = [&](int64_t i) {
+            const us4 k = __builtin_nontemporal_load(reinterpret_cast<const us4 *>(bcol + i));
+            const dvec2 a = __builtin_nontemporal_load(reinterpret_cast<const dvec2 *>(bval + i));
+            const dvec2 b = __builtin_nontemporal_load(reinterpret_cast<const dvec2 *>(bval + i + 2));
+            dvec2 p, q;
+            p.x = a.x * xs[k.x & (kBinCols - 1)];
+            p.y = a.y * xs[k.y & (kBinCols - 1)];
+            q.x = b.x * xs[k.z & (kBinCols - 1)];
+            q.y = b.y * xs[k.w & (kBinCols - 1)];
+            *reinterpret_cast<dvec2 *>(prod + i) = p;
+            *reinterpret_cast<dvec2 *>(prod + i + 2) = q;
+        };
+#pragma unroll 2
+        for (int64_t i = i0 + threadIdx.x * 4; i < end; i += kMulThreads * 4) four(i);
+        i0 = end;
+    }
+}
+
+// One row block per workgroup: LB lanes copy a bucket's products to LDS, two
+// neighbours each, then G lanes add up a row.  The latency of its chain of
+// loads (bucket table, then products, then the sums) bounds it, so all
+// products of a block are in flight at once, and the row pointers with them.
+// (Tried at 2^22 rows of 16, against 226 us: four workgroups of half the size
+// per compute unit 230, smaller buckets 266, places read in row order during
+// the sums 330, one bucket batch after the other 257, and a persistent walk
+// that fetches the next block's table early, whose registers spilled, 395.)
+template <int G, int LB>
+__global__ void __launch_bounds__(kSumRowThreads)
+bin_sum_kernel(BinParts bp, int rb, int nblk, int nc, const int32_t *__restrict__ start, const uint16_t *__restrict__ cnt,
+               const double *__restrict__ prod, const uint16_t *__restrict__ dst, const int32_t *__restrict__ col,
+               const double *__restrict__ val, const double *__restrict__ x) {
+    __shared__ double v[kBinCap];
+    __shared__ int32_t rps[kBinMaxRows + 1];
+    constexpr int kQ = kSumRowThreads / LB;  // buckets side by side
+    constexpr int kU = 8;                    // and in each group's hands
+    constexpr int kP = 2 * LB;               // entries a group takes at a time
+    constexpr int kRp = (kBinMaxRows + kSumRowThreads) / kSumRowThreads;  // row pointers per thread
+    const int64_t blk = bin_order();
+    if (blk >= nblk) return;
+    const int tid = threadIdx.x, sub = 2 * (tid & (LB - 1)), q = tid / LB;
+    const int32_t *st = start + blk * nc;
+    const uint16_t *ct = cnt + blk * nc;
+    const BinBlock B = bin_block(bp, blk, rb);
+    const bool inlds = B.m <= kBinCap;
+    int32_t rp[kRp];
+#pragma unroll
+    for (int u = 0; u < kRp; ++u) {
+        const int i = tid + u * kSumRowThreads;
+        rp[u] = B.rp[B.lo + (i <= B.rows ? i : B.rows)];
+    }
+    for (int c0 = q; inlds && c0 < nc; c0 += kQ * kU) {
+        int32_t at[kU], n[kU];
+        pair_u p[kU], p2[kU];
+        us2u d[kU], d2[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            n[u] = at[u] = 0;
+            if (c0 + u * kQ < nc) {
+                n[u] = ct[c0 + u * kQ];
+                at[u] = st[c0 + u * kQ];
+            }
+        }
+        // the first 2 kP products of every bucket in flight at once (a pair
+        // may reach one entry past its bucket: in the buffers, and not used)
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            if (sub < n[u]) {
+                p[u] = *reinterpret_cast<const pair_u *>(prod + at[u] + sub);
+                d[u] = *reinterpret_cast<const us2u *>(dst + at[u] + sub);
+            }
+            if (sub + kP < n[u]) {
+                p2[u] = *reinterpret_cast<const pair_u *>(prod + at[u] + sub + kP);
+                d2[u] = *reinterpret_cast<const us2u *>(dst + at[u] + sub + kP);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            if (sub < n[u]) v[d[u].x] = p[u].x;
+            if (sub + 1 < n[u]) v[d[u].y] = p[u].y;
+            if (sub + kP < n[u]) v[d2[u].x] = p2[u].x;
+            if (sub + kP + 1 < n[u]) v[d2[u].y] = p2[u].y;
+            for (int i = sub + 2 * kP; i < n[u]; i += kP) {
+                v[dst[at[u] + i]] = prod[at[u] + i];
+                if (i + 1 < n[u]) v[dst[at[u] + i + 1]] = prod[at[u] + i + 1];
             }
         }
     }
-}
-
-// partial[b*n + r] = sum over row r's entries of band b (G lanes per row,
-// entries k, k+G, ... per lane, then a fixed butterfly); `wg` is the
-// workgroup's index within the partition's launch (a multiple of 8 from
-// the grid's start, so wg & 7 is still the XCD it runs on)
-template <int G>
-__device__ __forceinline__ void band_block(const int32_t *__restrict__ bptr, const int32_t *__restrict__ bcol,
-                                           const double *__restrict__ bval, const double *__restrict__ x,
-                                           double *__restrict__ part, int64_t n, int S, int64_t chunks, int64_t wg) {
-    const int xcd = (int)(wg & 7);
-    const int64_t t = wg >> 3;
-    const int pass = (int)(t / chunks);
-    const int64_t chunk = t % chunks;
-    const int band = xcd * S + pass;
-    const int64_t r = chunk * (kBandThreads / G) + threadIdx.x / G;
-    const int g = threadIdx.x & (G - 1);
-    double s = 0.0;
-    if (r < n) {
-        const int32_t kb = bptr[(int64_t)band * n + r], ke = bptr[(int64_t)band * n + r + 1];
-        for (int32_t k = kb + g; k < ke; k += G)
-            s += __builtin_nontemporal_load(&bval[k]) * x[__builtin_nontemporal_load(&bcol[k])];
-    }
 #pragma unroll
-    for (int m = 1; m < G; m <<= 1) s += __shfl_xor(s, m, kWave);
-    if (r < n && g == 0) part[(int64_t)band * n + r] = s;
-}
-
-template <int G>
-__global__ void __launch_bounds__(kBandThreads)
-spmv_band_kernel(const int32_t *__restrict__ bptr, const int32_t *__restrict__ bcol, const double *__restrict__ bval,
-                 const double *__restrict__ x, double *__restrict__ part, int64_t n, int S, int64_t chunks) {
-    band_block<G>(bptr, bcol, bval, x, part, n, S, chunks, blockIdx.x);
-}
-
-// The partitions of one banded product in one launch: partition q's
-// workgroups [wg_begin, wg_begin + 8*S*chunks) and, for the combine,
-// [comb_begin, comb_begin + ceil(n / kBandThreads)).  Descriptors are read
-// through the constant address space (their pointers are then known to be
-// global).
-struct SpmvPart {
-    const int32_t *bptr, *bcol;
-    const double *bval, *x;
-    double *part, *y;
-    int64_t n, r0, chunks, wg_begin, comb_begin;
-};
-struct SpmvParts {
-    SpmvPart p[kMaxPack];
-    int32_t n;
-};
-typedef const __attribute__((address_space(4))) SpmvPart ConstSpmvPart;
-
-template <int G>
-__global__ void __launch_bounds__(kBandThreads) spmv_band_parts_kernel(SpmvParts sp, int S) {
-    ConstSpmvPart *cp = (ConstSpmvPart *)&sp.p[0];
-    const int64_t b = blockIdx.x;
-    int q = 0;
-    for (int k = 1; k < sp.n; ++k)
-        if (cp[k].wg_begin <= b) q = k;
-    band_block<G>(cp[q].bptr, cp[q].bcol, cp[q].bval, cp[q].x, cp[q].part, cp[q].n, S, cp[q].chunks,
-                  b - cp[q].wg_begin);
-}
-
-__global__ void band_combine_parts_kernel(SpmvParts sp, int B) {
-    ConstSpmvPart *cp = (ConstSpmvPart *)&sp.p[0];
-    const int64_t b = blockIdx.x;
-    int q = 0;
-    for (int k = 1; k < sp.n; ++k)
-        if (cp[k].comb_begin <= b) q = k;
-    const double *part = cp[q].part;
-    double *y = cp[q].y;
-    const int64_t n = cp[q].n, r = (b - cp[q].comb_begin) * kBandThreads + threadIdx.x;
-    if (r >= n) return;
-    double s = 0.0;
-    for (int k = 0; k < B; ++k) s += part[(int64_t)k * n + r];
-    y[cp[q].r0 + r] = s;
-}
-
-// One lane per row and band, R rows per lane (rows r, r + blockDim, ...):
-// the band offsets, the first two entries and their x values of all R rows
-// are loaded before any is used, so each lane keeps 2R gathers in flight;
-// entries beyond the second follow in increasing k (the same additions, in
-// the same order, as one lane walking the row).
-template <int R>
-__global__ void __launch_bounds__(kBandThreads)
-spmv_band_rows_kernel(const int32_t *__restrict__ bptr, const int32_t *__restrict__ bcol,
-                      const double *__restrict__ bval, const double *__restrict__ x, double *__restrict__ part,
-                      int64_t n, int S, int64_t chunks) {
-    const int64_t wg = blockIdx.x;
-    const int xcd = (int)(wg & 7);
-    const int64_t t = wg >> 3;
-    const int pass = (int)(t / chunks);
-    const int64_t chunk = t % chunks;
-    const int64_t band_base = (int64_t)(xcd * S + pass) * n;
-    int64_t r[R];
-    int32_t kb[R], ke[R];
+    for (int u = 0; u < kRp; ++u)
+        if (tid + u * kSumRowThreads <= B.rows) rps[tid + u * kSumRowThreads] = rp[u] - B.e0;
+    __syncthreads();
+    const int g = tid & (G - 1);
+    constexpr int kStep = kSumRowThreads / G, kR = 4;  // rows side by side, and in each group's hands
+    if (inlds) {
+        for (int r0 = tid / G; r0 < B.rows; r0 += kStep * kR) {
+            int32_t k[kR], ke[kR];
+            double t[kR];
 #pragma unroll
-    for (int u = 0; u < R; ++u) {
-        r[u] = chunk * (kBandThreads * R) + u * kBandThreads + threadIdx.x;
-        kb[u] = ke[u] = 0;
-        if (r[u] < n) {
-            kb[u] = bptr[band_base + r[u]];
-            ke[u] = bptr[band_base + r[u] + 1];
+            for (int u = 0; u < kR; ++u) {
+                const int r = r0 + u * kStep < B.rows ? r0 + u * kStep : r0;
+                k[u] = rps[r] + g;
+                ke[u] = rps[r + 1];
+            }
+#pragma unroll
+            for (int u = 0; u < kR; ++u) t[u] = k[u] < ke[u] ? 0.0 + v[k[u]] : 0.0;
+#pragma unroll
+            for (int u = 0; u < kR; ++u) {
+                for (int32_t i = k[u] + G; i < ke[u]; i += G) t[u] += v[i];
+                t[u] = group_sum<G>(t[u]);
+                if (g == 0 && r0 + u * kStep < B.rows) B.y[B.lo + r0 + u * kStep] = t[u];
+            }
+        }
+    } else {
+        for (int r = tid / G; r < B.rows; r += kStep) {
+            double t = 0.0;
+            for (int32_t k = rps[r] + g; k < rps[r + 1]; k += G) t += val[(int64_t)B.e0 + k] * x[col[(int64_t)B.e0 + k]];
+            t = group_sum<G>(t);
+            if (g == 0) B.y[B.lo + r] = t;
         }
     }
-    int32_t c0[R], c1[R];
-    double v0[R], v1[R];
-#pragma unroll
-    for (int u = 0; u < R; ++u) {
-        c0[u] = c1[u] = -1;
-        v0[u] = v1[u] = 0.0;
-        if (kb[u] < ke[u]) {
-            c0[u] = __builtin_nontemporal_load(&bcol[kb[u]]);
-            v0[u] = __builtin_nontemporal_load(&bval[kb[u]]);
-        }
-        if (kb[u] + 1 < ke[u]) {
-            c1[u] = __builtin_nontemporal_load(&bcol[kb[u] + 1]);
-            v1[u] = __builtin_nontemporal_load(&bval[kb[u] + 1]);
-        }
-    }
-    double x0[R], x1[R];
-#pragma unroll
-    for (int u = 0; u < R; ++u) {
-        x0[u] = c0[u] >= 0 ? x[c0[u]] : 0.0;
-        x1[u] = c1[u] >= 0 ? x[c1[u]] : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < R; ++u) {
-        double s = 0.0;
-        if (c0[u] >= 0) s += v0[u] * x0[u];
-        if (c1[u] >= 0) s += v1[u] * x1[u];
-        for (int32_t k = kb[u] + 2; k < ke[u]; ++k)
-            s += __builtin_nontemporal_load(&bval[k]) * x[__builtin_nontemporal_load(&bcol[k])];
-        if (r[u] < n) part[band_base + r[u]] = s;
-    }
 }
 
-// y[r0 + r] = partial[0][r] + partial[1][r] + ... in band order
-__global__ void band_combine_kernel(const double *__restrict__ part, int64_t n, int B, double *__restrict__ y,
-                                    int64_t r0) {
-    const int64_t r = (int64_t)blockIdx.x * kBandThreads + threadIdx.x;
-    if (r >= n) return;
-    double s = 0.0;
-    for (int b = 0; b < B; ++b) s += part[(int64_t)b * n + r];
-    y[r0 + r] = s;
-}
-
-}  // namespace
-
-int64_t band_width(int64_t ncols, int bands) { return (ncols + bands - 1) / bands; }
-
-int64_t band_scan_blocks(int64_t len) { return (len + (int64_t)kScanThreads * kScanPer - 1) / ((int64_t)kScanThreads * kScanPer); }
-
-hipError_t build_bands(const Launch &L, const BandBufs &bb, hipStream_t s) {
-    const int64_t r0 = L.lo[0], n = L.hi[0] - L.lo[0];
-    if (n <= 0) return hipSuccess;
-    const int B = bb.bands;
-    const int64_t W = band_width(bb.ncols, B);
-    const int64_t len = (int64_t)B * n;
-    const int64_t nb = band_scan_blocks(len);
-    if (nb > (int64_t)kScanThreads * kScanPer) return hipErrorInvalidValue;
-    const unsigned rows_grid = (unsigned)((n + kBandThreads - 1) / kBandThreads);
-    const int32_t *rp = (const int32_t *)L.a[0].ptr, *col = (const int32_t *)L.a[1].ptr;
-    const double *val = (const double *)L.a[2].ptr;
-    int32_t *cnt = (int32_t *)bb.part;  // the partials are free until the product runs
-    hipLaunchKernelGGL(band_count_kernel, dim3(rows_grid), dim3(kBandThreads), 0, s, rp, col, r0, n, W, B, cnt);
-    hipLaunchKernelGGL(scan_blocks_kernel, dim3((unsigned)nb), dim3(kScanThreads), 0, s, cnt, len, bb.bptr, bb.sums);
-    hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(kScanThreads), 0, s, bb.sums, nb);
-    hipLaunchKernelGGL(scan_add_kernel, dim3((unsigned)((len + kBandThreads) / kBandThreads)), dim3(kBandThreads), 0, s,
-                       bb.bptr, len, bb.sums);
-    hipLaunchKernelGGL(band_fill_kernel, dim3(rows_grid), dim3(kBandThreads), 0, s, rp, col, val, r0, n, W, B, bb.bptr,
-                       bb.bcol, bb.bval);
-    return hipGetLastError();
-}
-
-hipError_t launch_spmv_banded(const Launch &L, const BandBufs &bb, hipStream_t s) {
-    const int64_t r0 = L.lo[0], n = L.hi[0] - L.lo[0];
-    if (n <= 0) return hipSuccess;
-    const int G = L.cfg.tile;
-    const int S = bb.bands / 8;
-    const double *x = (const double *)L.a[3].ptr;
-    if (G == 1 && (L.cfg.rows == 2 || L.cfg.rows == 4)) {  // several rows per lane
-        const int R = L.cfg.rows;
-        const int64_t chunks = (n + (int64_t)kBandThreads * R - 1) / ((int64_t)kBandThreads * R);
-        const unsigned grid = (unsigned)(8 * (int64_t)S * chunks);
-        if (R == 2)
-            hipLaunchKernelGGL((spmv_band_rows_kernel<2>), dim3(grid), dim3(kBandThreads), 0, s, bb.bptr, bb.bcol,
-                               bb.bval, x, bb.part, n, S, chunks);
-        else
-            hipLaunchKernelGGL((spmv_band_rows_kernel<4>), dim3(grid), dim3(kBandThreads), 0, s, bb.bptr, bb.bcol,
-                               bb.bval, x, bb.part, n, S, chunks);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(band_combine_kernel, dim3((unsigned)((n + kBandThreads - 1) / kBandThreads)),
-                           dim3(kBandThreads), 0, s, bb.part, n, bb.bands, (double *)L.a[4].ptr, r0);
-        return hipGetLastError();
-    }
-    const int64_t chunks = (n + kBandThreads / G - 1) / (kBandThreads / G);
-    const unsigned grid = (unsigned)(8 * (int64_t)S * chunks);
-#define SPMV_BAND(GG)                                                                                           \
-    hipLaunchKernelGGL((spmv_band_kernel<GG>), dim3(grid), dim3(kBandThreads), 0, s, bb.bptr, bb.bcol, bb.bval, x, \
-                       bb.part, n, S, chunks)
-    switch (G) {  // a row's band holds about nnz/bands entries: few lanes per row
-        case 1: SPMV_BAND(1); break;
-        case 2: SPMV_BAND(2); break;
-        case 4: SPMV_BAND(4); break;
-        case 16: SPMV_BAND(16); break;
-        default: SPMV_BAND(8); break;
-    }
-#undef SPMV_BAND
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(band_combine_kernel, dim3((unsigned)((n + kBandThreads - 1) / kBandThreads)), dim3(kBandThreads),
-                       0, s, bb.part, n, bb.bands, (double *)L.a[4].ptr, r0);
-    return hipGetLastError();
-}
-
-hipError_t launch_spmv_banded_parts(const Launch *L, const BandBufs *bb, int n, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    if (n > kMaxPack) return hipErrorInvalidValue;
-    const int G = L[0].cfg.tile;
-    const int S = bb[0].bands / 8;
-    if (G != 1 && G != 2 && G != 4 && G != 8 && G != 16) return hipErrorInvalidValue;
-    SpmvParts sp{};
-    int64_t wg = 0, comb = 0;
+BinParts bin_parts(const Launch *L, int n, int rb) {
+    BinParts bp{};
+    int64_t blk = 0;
     for (int k = 0; k < n; ++k) {
         const int64_t rows = L[k].hi[0] - L[k].lo[0];
         if (rows <= 0) continue;
-        if (bb[k].bands != bb[0].bands) return hipErrorInvalidValue;
-        SpmvPart &d = sp.p[sp.n++];
-        d.bptr = bb[k].bptr;
-        d.bcol = bb[k].bcol;
-        d.bval = bb[k].bval;
-        d.x = (const double *)L[k].a[3].ptr;
-        d.part = bb[k].part;
+        BinPart &d = bp.p[bp.n++];
+        d.rp = (const int32_t *)L[k].a[0].ptr;
         d.y = (double *)L[k].a[4].ptr;
-        d.n = rows;
         d.r0 = L[k].lo[0];
-        d.chunks = (rows + kBandThreads / G - 1) / (kBandThreads / G);
-        d.wg_begin = wg;
-        d.comb_begin = comb;
-        wg += 8 * (int64_t)S * d.chunks;
-        comb += (rows + kBandThreads - 1) / kBandThreads;
+        d.r1 = L[k].hi[0];
+        d.blk = blk;
+        blk += (rows + rb - 1) / rb;
     }
-    if (sp.n == 0) return hipSuccess;
-    if (wg > (int64_t)INT32_MAX) return hipErrorInvalidValue;
-#define SPMV_BAND_PARTS(GG) \
-    hipLaunchKernelGGL((spmv_band_parts_kernel<GG>), dim3((unsigned)wg), dim3(kBandThreads), 0, s, sp, S)
-    switch (G) {
-        case 1: SPMV_BAND_PARTS(1); break;
-        case 2: SPMV_BAND_PARTS(2); break;
-        case 4: SPMV_BAND_PARTS(4); break;
-        case 16: SPMV_BAND_PARTS(16); break;
-        default: SPMV_BAND_PARTS(8); break;
+    return bp;
+}
+
+unsigned bin_grid(int nblk) { return (unsigned)((nblk + 7) / 8 * 8); }
+
+}  // namespace
+
+// Lanes per row: about one entry each (2^19 rows: 4 entries a row 19 / 22 / 33
+// us with 4 / 8 / 16 lanes, 8 entries 40 / 34 / 41, 16 entries 100 / 74 / 64).
+int spmv_lanes(int64_t nnz, int64_t rows) {
+    const int64_t mean = rows > 0 ? (nnz + rows - 1) / rows : 0;
+    return mean > 8 ? 16 : mean > 4 ? 8 : 4;
+}
+
+bool bin_geometry(int64_t ncols, int64_t nnz, int64_t rows, const Launch *L, int n, BinBufs *bb) {
+    *bb = BinBufs{};
+    // the histogram of column blocks takes 4 bytes of LDS each (128 KB); row
+    // blocks are sized by the mean row length of the whole matrix, and so are
+    // the lanes of a row: neither depends on the partitions
+    if (ncols < 1 || ncols > ((int64_t)kBinCols << 15) || n > kMaxPack) return false;
+    const int64_t mean = (nnz + rows - 1) / (rows > 0 ? rows : 1);
+    if (mean > kBinCap) return false;  // most row blocks would hold no buckets
+    int64_t rb = mean > 0 ? kBinTarget / mean : kBinMaxRows;
+    rb = rb < 16 ? 16 : rb > kBinMaxRows ? kBinMaxRows : rb;
+    bb->ncols = ncols;
+    bb->nc = (int)((ncols + kBinCols - 1) >> kBinShift);
+    bb->rb = (int)rb;
+    bb->lanes = spmv_lanes(nnz, rows);
+    int64_t nblk = 0;
+    for (int k = 0; k < n; ++k) {
+        const int64_t r = L[k].hi[0] - L[k].lo[0];
+        if (r > 0) nblk += (r + rb - 1) / rb;
     }
-#undef SPMV_BAND_PARTS
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(band_combine_parts_kernel, dim3((unsigned)comb), dim3(kBandThreads), 0, s, sp, bb[0].bands);
+    if (nblk > (1 << 24) || nnz + (int64_t)kPad * bb->nc > INT32_MAX) return false;
+    bb->nblk = (int)nblk;
+    const size_t cells = (size_t)nblk * bb->nc, cap = (size_t)nnz + (size_t)kPad * bb->nc;
+    const size_t bytes[kBinBuffers] = {cells * 4, cells * 2, (size_t)(bb->nc + 1) * 4, (size_t)kSegments * bb->nc * 4,
+                                       cap * 8,   cap * 2,   cap * 2,                  cap * 8};
+    for (int i = 0; i < kBinBuffers; ++i) bb->bytes[i] = bytes[i];
+    return true;
+}
+
+hipError_t build_bins(const Launch *L, int n, const BinBufs &bb, hipStream_t s) {
+    if (bb.nblk <= 0) return hipSuccess;
+    const BinParts bp = bin_parts(L, n, bb.rb);
+    const int32_t *col = (const int32_t *)L[0].a[1].ptr;
+    const double *val = (const double *)L[0].a[2].ptr;
+    const int per = (bb.nblk + kSegments - 1) / kSegments;
+    const dim3 scan((unsigned)((bb.nc + 63) / 64), kSegments);
+    const size_t lds = (size_t)bb.nc * 4;
+    hipLaunchKernelGGL(bin_count_kernel, dim3(bin_grid(bb.nblk)), dim3(512), lds, s, bp, col, bb.rb, bb.nblk, bb.nc,
+                       bb.cnt());
+    hipLaunchKernelGGL(bin_segments_kernel, scan, dim3(1024), 0, s, bb.cnt(), bb.nblk, bb.nc, per, bb.segs());
+    hipLaunchKernelGGL(bin_bases_kernel, dim3(1), dim3(1024), 0, s, bb.nc, bb.segs(), bb.cbase());
+    hipLaunchKernelGGL(bin_starts_kernel, scan, dim3(1024), 0, s, bb.cnt(), bb.nblk, bb.nc, per, bb.segs(), bb.start());
+    if (bb.nc <= kSortCols)
+        hipLaunchKernelGGL((bin_fill_kernel<true>), dim3(bin_grid(bb.nblk)), dim3(1024), lds, s, bp, col, val, bb.rb,
+                           bb.nblk, bb.nc, bb.start(), bb.cnt(), bb.bval(), bb.bcol(), bb.dst());
+    else
+        hipLaunchKernelGGL((bin_fill_kernel<false>), dim3(bin_grid(bb.nblk)), dim3(1024), lds, s, bp, col, val, bb.rb,
+                           bb.nblk, bb.nc, bb.start(), bb.cnt(), bb.bval(), bb.bcol(), bb.dst());
+    return hipGetLastError();
+}
+
+hipError_t launch_spmv_bins(const Launch *L, int n, const BinBufs &bb, hipStream_t s) {
+    if (bb.nblk <= 0) return hipSuccess;
+    const BinParts bp = bin_parts(L, n, bb.rb);
+    const double *x = (const double *)L[0].a[3].ptr;
+    hipLaunchKernelGGL(bin_multiply_kernel, dim3(kMulGroups), dim3(kMulThreads), 0, s, bb.cbase(), bb.nc, bb.ncols, x,
+                       bb.bval(), bb.bcol(), bb.prod());
+    // lanes per bucket: 16 take up to 64 entries at once, 64 up to 256
+    const bool wide = (int64_t)kBinTarget > (int64_t)48 * bb.nc;
+#define BIN_SUM(G, LB)                                                                                                 \
+    hipLaunchKernelGGL((bin_sum_kernel<G, LB>), dim3(bin_grid(bb.nblk)), dim3(kSumRowThreads), 0, s, bp, bb.rb, bb.nblk, \
+                       bb.nc, bb.start(), bb.cnt(), bb.prod(), bb.dst(), (const int32_t *)L[0].a[1].ptr,               \
+                       (const double *)L[0].a[2].ptr, x)
+#define BIN_SUM_LB(G)       \
+    do {                    \
+        if (wide)           \
+            BIN_SUM(G, 64); \
+        else                \
+            BIN_SUM(G, 16); \
+    } while (0)
+    switch (bb.lanes) {
+        case 4: BIN_SUM_LB(4); break;
+        case 8: BIN_SUM_LB(8); break;
+        default: BIN_SUM_LB(16); break;
+    }
+#undef BIN_SUM_LB
+#undef BIN_SUM
     return hipGetLastError();
 }
 

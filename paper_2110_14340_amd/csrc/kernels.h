@@ -160,25 +160,33 @@ hipError_t launch_finalise(const double *partials, int64_t n, double *out, hipSt
 hipError_t launch_gemm(const Launch &L, hipStream_t s);
 hipError_t launch_spmv(const Launch &L, hipStream_t s);
 
-// Column-banded SpMV of one partition (rows L.lo[0]..L.hi[0]): device
-// buffers of its band-major copy.  bands = 8*S; bptr holds bands*n + 1
-// offsets, sums band_scan_blocks(bands*n) + 1 scan totals, bcol/bval the
-// partition's entries, part bands*n doubles (also the counts' scratch during
-// the build).
-struct BandBufs {
-    int bands;
+// Binned SpMV: the device copy of the matrix rows of one or more partitions'
+// launches, its geometry and buffers (k_spmv.hip).
+constexpr int kBinBuffers = 8;
+struct BinBufs {
     int64_t ncols;
-    int32_t *bptr, *sums, *bcol;
-    double *bval, *part;
+    int nc, rb, nblk, lanes;  // column blocks, rows per row block, row blocks, lanes per row
+    size_t bytes[kBinBuffers];
+    void *mem[kBinBuffers];
+    int32_t *start() const { return (int32_t *)mem[0]; }   // [row block][column block]: a bucket's first entry
+    uint16_t *cnt() const { return (uint16_t *)mem[1]; }   // [row block][column block]: its entries
+    int32_t *cbase() const { return (int32_t *)mem[2]; }   // a column block's first entry
+    int32_t *segs() const { return (int32_t *)mem[3]; }    // scratch of the build's scan
+    double *bval() const { return (double *)mem[4]; }      // the entries: value,
+    uint16_t *bcol() const { return (uint16_t *)mem[5]; }  // column within its block,
+    uint16_t *dst() const { return (uint16_t *)mem[6]; }   // place in its row block
+    double *prod() const { return (double *)mem[7]; }      // products of the last multiply
 };
-int64_t band_width(int64_t ncols, int bands);
-int64_t band_scan_blocks(int64_t len);
-hipError_t build_bands(const Launch &L, const BandBufs &bb, hipStream_t s);
-hipError_t launch_spmv_banded(const Launch &L, const BandBufs &bb, hipStream_t s);
-// The banded products of n partitions (their band-major copies bb[k], the
-// same band count) in one launch, then one combine launch (the same bits as
-// a launch per partition).
-hipError_t launch_spmv_banded_parts(const Launch *L, const BandBufs *bb, int n, hipStream_t s);
+// Lanes per row by the mean row length of the whole matrix (not by
+// partition: the lanes decide the order of a row's sum).
+int spmv_lanes(int64_t nnz, int64_t rows);
+// Geometry and buffer sizes for a matrix of `rows` rows and `nnz` entries (false:
+// this form does not take it).  The launches are the partitions' rows.
+bool bin_geometry(int64_t ncols, int64_t nnz, int64_t rows, const Launch *L, int n, BinBufs *bb);
+// Both read col, val and x through the first launch's arguments (every
+// partition's replica holds the same values).
+hipError_t build_bins(const Launch *L, int n, const BinBufs &bb, hipStream_t s);
+hipError_t launch_spmv_bins(const Launch *L, int n, const BinBufs &bb, hipStream_t s);
 hipError_t launch_scatter(const Launch &L, hipStream_t s);
 hipError_t launch_chain(const Launch &L, hipStream_t s);
 

@@ -39,7 +39,7 @@ constexpr int kSlots = 4096;
 constexpr int kEventRing = 16;
 constexpr int64_t kWgCapacity = 1 << 16;  // workgroup partials per stream
 constexpr int kTaskCapacity = 4096;       // persistent tasks per batch
-constexpr int64_t kBandedMinCols = 1 << 20;  // SpMV x length from which the banded form is the default
+constexpr int64_t kBinnedMinCols = 1 << 20;  // SpMV x length from which the binned form is the default
 
 thread_local std::string g_init_err;  // message of the last failed context-free call (jacc_init, no-alloc step)
 
@@ -288,16 +288,17 @@ struct Batch {
     int groups = 0;
 };
 
-// The column-banded copy of one partition's rows of a CSR matrix, built on
-// the device at its first banded product and kept while row_ptr, col and val
-// are unchanged (their versions).
-struct BandCache {
-    int rp_id = -1, col_id = -1, val_id = -1, p = 0, bands = 0;
+// The binned device copy of rows [lo, hi) of a CSR matrix (one partition's,
+// or with p = -1 those of all partitions of a packed loop), built at its
+// first product and kept while row_ptr, col and val are unchanged (their
+// versions).  Products share its buffers: `last` is the op that used them last.
+struct BinCache {
+    int rp_id = -1, col_id = -1, val_id = -1, p = 0, K = 0;
     int64_t lo = 0, hi = 0;
     uint64_t v_rp = 0, v_col = 0, v_val = 0;
     bool built = false;
-    jk::BandBufs bb{};
-    void *mem[5] = {};
+    SeqRef last;
+    jk::BinBufs bb{};
 };
 
 size_t dtype_size(int dt) {
@@ -373,8 +374,8 @@ struct jacc_ctx {
     bool time_parts = false;
     std::vector<hipEvent_t> kev;
     uint64_t kev_used = 0;  // bit p: partition p launched in the timed call
-    // banded SpMV copies, per partition and matrix
-    std::vector<BandCache> bands;
+    // binned SpMV copies, per matrix and rows
+    std::vector<BinCache> bins;
     // cost model attached by jacc_model_load (owned; released at finalize)
     void *model = nullptr;
     void (*model_release)(void *) = nullptr;
@@ -835,12 +836,12 @@ int gather(jacc_ctx *c, Array *A, Range r) {
     return JACC_OK;
 }
 
-void drop_bands(jacc_ctx *c, int array_id) {
-    for (size_t i = 0; i < c->bands.size();) {
-        BandCache &bc = c->bands[i];
-        if (array_id < 0 || bc.rp_id == array_id || bc.col_id == array_id || bc.val_id == array_id) {
-            for (void *m : bc.mem) dev_free(c, m);
-            c->bands.erase(c->bands.begin() + (long)i);
+void drop_bins(jacc_ctx *c, int array_id) {
+    for (size_t i = 0; i < c->bins.size();) {
+        BinCache &bc = c->bins[i];
+        if (bc.rp_id == array_id || bc.col_id == array_id || bc.val_id == array_id) {
+            for (void *m : bc.bb.mem) dev_free(c, m);
+            c->bins.erase(c->bins.begin() + (long)i);
         } else {
             ++i;
         }
@@ -848,7 +849,7 @@ void drop_bands(jacc_ctx *c, int array_id) {
 }
 
 void free_array(jacc_ctx *c, Array *A) {
-    drop_bands(c, A->id);
+    drop_bins(c, A->id);
     for (int p = 0; p < (A->shared ? 1 : A->K); ++p) {
         trace(c, JACC_OP_FREE, -1, A->id, -1, p, 0, A->slabs[p].rows.lo, A->slabs[p].rows.hi, 0);
         dev_free(c, A->slabs[p].dev);
@@ -1153,12 +1154,13 @@ int prepare_loop(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const j
     if (cfg) cf = {cfg->bx, cfg->by, cfg->tile, cfg->vec, cfg->persistent, cfg->order, cfg->march, cfg->rows};
     if (pd != 0 && cf.persistent)
         return set_err(c, JACC_ERR_UNSUPPORTED, "persistent execution of arrays split along dimension 1");
+    const bool own_tile = cf.tile != 0;
+    if (kind == JACC_LOOP_SPMV_CSR && !own_tile && cf.order != 4) cf.tile = jk::spmv_lanes(arr[1]->E, arr[0]->E - 1);
     L.cfg = jk::default_config(kind, L, cf);
-    if (kind == JACC_LOOP_SPMV_CSR && !cf.order && !c->cur && arr[3]->E >= kBandedMinCols) {
-        // x far larger than an XCD's L2: the column-banded form, one band
-        // per XCD, two lanes per row and band (measured at 2^22 columns)
+    if (kind == JACC_LOOP_SPMV_CSR && !cf.order && !c->cur && arr[3]->E >= kBinnedMinCols) {
+        // x larger than an XCD's L2: the binned form
         L.cfg.order = 4;
-        if (!cf.tile) L.cfg.tile = 2;
+        if (!own_tile) L.cfg.tile = 2;
         if (!cf.by) L.cfg.by = 1;
     }
     if (jk::check_config(L) != 0)
@@ -1167,7 +1169,7 @@ int prepare_loop(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const j
                        L.cfg.bx, L.cfg.by, L.cfg.tile, L.cfg.vec, L.cfg.persistent, L.cfg.order, L.cfg.march,
                        L.cfg.rows, kind);
     if (kind == JACC_LOOP_SPMV_CSR && L.cfg.order == 4 && c->cur)
-        return set_err(c, JACC_ERR_UNSUPPORTED, "the column-banded SpMV form is not captured in batches");
+        return set_err(c, JACC_ERR_UNSUPPORTED, "the binned SpMV form is not captured in batches");
     if (L.cfg.persistent) {
         if (!c->cur) return set_err(c, JACC_ERR_INVALID, "persistent execution needs an open batch");
         if (want_red) return set_err(c, JACC_ERR_UNSUPPORTED, "persistent execution of a reduction");
@@ -1178,14 +1180,18 @@ int prepare_loop(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const j
     return JACC_OK;
 }
 
-// The banded copy of partition p's rows of the CSR matrix in arr[0..2]
-// (row_ptr, col, val) for x = arr[3]: found, marked for a rebuild when the
-// matrix changed since it was built, or allocated.
-int band_cache(jacc_ctx *c, Array **arr, int p, Range rows, int bands, BandCache **out) {
+// The binned copy of the rows of launches L[0..n) of the CSR matrix in
+// arr[0..2] (row_ptr, col, val) for x = arr[3]: found, marked for a rebuild
+// when the matrix changed since it was built, or allocated.  *out is null
+// when the form does not take the matrix or its memory is not to be had: the
+// caller then runs the plain form.
+int bin_cache(jacc_ctx *c, Array **arr, int p, const jk::Launch *L, int n, BinCache **out) {
     Array *rp = arr[0], *col = arr[1], *val = arr[2];
-    for (BandCache &bc : c->bands)
-        if (bc.rp_id == rp->id && bc.col_id == col->id && bc.val_id == val->id && bc.p == p && bc.lo == rows.lo &&
-            bc.hi == rows.hi && bc.bands == bands) {
+    *out = nullptr;
+    const int64_t lo = L[0].lo[0], hi = L[n - 1].hi[0];
+    for (BinCache &bc : c->bins)
+        if (bc.rp_id == rp->id && bc.col_id == col->id && bc.val_id == val->id && bc.p == p && bc.K == n && bc.lo == lo &&
+            bc.hi == hi && bc.bb.ncols == arr[3]->E) {
             if (bc.v_rp != rp->version || bc.v_col != col->version || bc.v_val != val->version) {
                 bc.built = false;
                 bc.v_rp = rp->version;
@@ -1195,38 +1201,51 @@ int band_cache(jacc_ctx *c, Array **arr, int p, Range rows, int bands, BandCache
             *out = &bc;
             return JACC_OK;
         }
-    const int64_t n = rows.hi - rows.lo, len = (int64_t)bands * n;
-    const int64_t nb = jk::band_scan_blocks(len);
-    if (nb > 8192) return set_err(c, JACC_ERR_UNSUPPORTED, "banded SpMV: %lld band rows exceed the scan", (long long)len);
-    BandCache bc;
+    BinCache bc;
+    if (!jk::bin_geometry(arr[3]->E, col->E, rp->E - 1, L, n, &bc.bb)) return JACC_OK;
     bc.rp_id = rp->id;
     bc.col_id = col->id;
     bc.val_id = val->id;
     bc.p = p;
-    bc.bands = bands;
-    bc.lo = rows.lo;
-    bc.hi = rows.hi;
+    bc.K = n;
+    bc.lo = lo;
+    bc.hi = hi;
     bc.v_rp = rp->version;
     bc.v_col = col->version;
     bc.v_val = val->version;
-    const size_t sizes[5] = {(size_t)(len + 1) * 4, (size_t)(nb + 1) * 4, (size_t)col->E * 4, (size_t)col->E * 8,
-                             (size_t)len * 8};
-    for (int i = 0; i < 5; ++i) {
-        int rc = dev_alloc(c, sizes[i], &bc.mem[i]);
-        if (rc) {
-            for (int j = 0; j < i; ++j) dev_free(c, bc.mem[j]);
-            return rc;
+    for (int i = 0; i < jk::kBinBuffers; ++i)
+        if (dev_alloc(c, bc.bb.bytes[i], &bc.bb.mem[i])) {
+            for (int j = 0; j < i; ++j) dev_free(c, bc.bb.mem[j]);
+            return JACC_OK;
         }
+    c->bins.push_back(bc);
+    *out = &c->bins.back();
+    return JACC_OK;
+}
+
+// Issues the products of launches L[0..n) as stream s's next op: binned, after
+// the last product that used the copy's buffers, or plain.
+int issue_spmv(jacc_ctx *c, Array **arr, int p, const jk::Launch *L, int n, int s) {
+    BinCache *bc = nullptr;
+    int rc = bin_cache(c, arr, p, L, n, &bc);
+    if (rc) return rc;
+    if (!bc) {
+        for (int k = 0; k < n; ++k) {
+            jk::Launch P = L[k];
+            P.cfg = jk::default_config(JACC_LOOP_SPMV_CSR, P, jk::Cfg{});
+            P.cfg.tile = jk::spmv_lanes(arr[1]->E, arr[0]->E - 1);
+            if (live(c)) HIPCHK(c, jk::launch_loop(P, c->st[s].s), "kernel launch");
+        }
+        return JACC_OK;
     }
-    bc.bb.bands = bands;
-    bc.bb.ncols = arr[3]->E;
-    bc.bb.bptr = (int32_t *)bc.mem[0];
-    bc.bb.sums = (int32_t *)bc.mem[1];
-    bc.bb.bcol = (int32_t *)bc.mem[2];
-    bc.bb.bval = (double *)bc.mem[3];
-    bc.bb.part = (double *)bc.mem[4];
-    c->bands.push_back(bc);
-    *out = &c->bands.back();
+    rc = ensure_wait(c, s, bc->last.s, bc->last.seq);
+    if (rc) return rc;
+    if (live(c)) {
+        if (!bc->built) HIPCHK(c, jk::build_bins(L, n, bc->bb, c->st[s].s), "binned SpMV build");
+        HIPCHK(c, jk::launch_spmv_bins(L, n, bc->bb, c->st[s].s), "kernel launch");
+    }
+    bc->built = true;
+    bc->last = {s, c->st[s].seq + 1};
     return JACC_OK;
 }
 
@@ -1526,7 +1545,6 @@ int loop_impl(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const jacc
                 }
         }
         std::vector<jk::Launch> lps;
-        std::vector<jk::BandBufs> bbs;  // banded SpMV: each partition's band-major copy
         std::vector<std::vector<std::pair<int, Range>>> mirs((size_t)K);
         for (int p = 0; p < K; ++p) {
             const PartPlan &pp = plan[p];
@@ -1554,27 +1572,20 @@ int loop_impl(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const jacc
                 order.push_back(p);
                 red_streams.push_back(s);
             }
-            if (kind == JACC_LOOP_SPMV_CSR) {
-                BandCache *bc = nullptr;
-                rc = band_cache(c, arr, p, pp.iters, 8 * LP.cfg.by, &bc);
-                if (rc) return rc;
-                if (live(c) && !bc->built) HIPCHK(c, jk::build_bands(LP, bc->bb, c->st[s].s), "banded SpMV build");
-                bc->built = true;
-                bbs.push_back(bc->bb);
-            }
             lps.push_back(LP);
         }
         if (inject_fault(c, 2)) {
             c->status = JACC_ERR_DEVICE;
             return set_err(c, JACC_ERR_DEVICE, "injected fault in launch %lld", (long long)c->fault_count);
         }
-        if (live(c))
+        if (kind == JACC_LOOP_SPMV_CSR) {
+            rc = lps.empty() ? JACC_OK : issue_spmv(c, arr, -1, lps.data(), (int)lps.size(), s);
+            if (rc) return rc;
+        } else if (live(c)) {
             HIPCHK(c,
-                   kind == JACC_LOOP_SPMV_CSR
-                       ? jk::launch_spmv_banded_parts(lps.data(), bbs.data(), (int)lps.size(), c->st[s].s)
-                       : jk::launch_parts(lps.data(), (int)lps.size(), c->wg + (size_t)s * kWgCapacity, kWgCapacity,
-                                          c->st[s].s),
+                   jk::launch_parts(lps.data(), (int)lps.size(), c->wg + (size_t)s * kWgCapacity, kWgCapacity, c->st[s].s),
                    "kernel launch");
+        }
         c->st[s].seq++;
         for (int p = 0; p < K; ++p)
             if (!plan[p].iters.empty())
@@ -1689,15 +1700,9 @@ int loop_impl(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const jacc
         }
         const bool timed = c->time_parts && live(c) && p < kMaxK;
         if (timed) HIPCHK(c, hipEventRecord(c->kev[2 * p], c->st[s].s), "hipEventRecord");
-        if (kind == JACC_LOOP_SPMV_CSR && LP.cfg.order == 4) {  // column-banded product
-            BandCache *bc = nullptr;
-            rc = band_cache(c, arr, p, pp.iters, 8 * LP.cfg.by, &bc);
+        if (kind == JACC_LOOP_SPMV_CSR && LP.cfg.order == 4) {
+            rc = issue_spmv(c, arr, p, &LP, 1, s);
             if (rc) return rc;
-            if (live(c)) {
-                if (!bc->built) HIPCHK(c, jk::build_bands(LP, bc->bb, c->st[s].s), "banded SpMV build");
-                HIPCHK(c, jk::launch_spmv_banded(LP, bc->bb, c->st[s].s), "kernel launch");
-            }
-            bc->built = true;
         } else if (live(c)) {
             HIPCHK(c, jk::launch_loop(LP, c->st[s].s), "kernel launch");
         }

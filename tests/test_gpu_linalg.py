@@ -278,3 +278,73 @@ def test_gemm_tiles_edges_boxes_and_nonfinite_rows(M, N, L):
     got = _gemm_dev(A, B, 1)
     assert np.array_equal(got[:-1, :-1], full[:-1, :-1])
     assert not np.isfinite(got[-1]).any() and np.isnan(got[:, -1]).all()
+
+
+def _rows_matrix(lens, ncols, seed):
+    """CSR matrix with the given row lengths, columns uniform with
+    replacement (unsorted, duplicates kept), values N(0,1)."""
+    r = np.random.default_rng(seed)
+    rp = np.zeros(len(lens) + 1, dtype=np.int32)
+    np.cumsum(lens, out=rp[1:])
+    col = r.integers(0, ncols, size=int(rp[-1])).astype(np.int32)
+    return rp, col, r.standard_normal(int(rp[-1])), r.random(ncols) * 2 - 1
+
+
+@pytest.mark.parametrize("case,ncols", [("empty_rows", 16384), ("long_rows", 16385), ("dense_block", 40000),
+                                        ("short_rows", 300000), ("one_row", 70000), ("wide", (2048 << 14) + 5)])
+def test_binned_spmv_edges(case, ncols):
+    """The binned form where its blocks end: column counts around the
+    16384-column blocks and past the 2048 blocks whose counters fit LDS in the
+    build, empty rows, rows longer than a row block holds, a run of dense
+    rows (whose row blocks are summed from the CSR arrays) whose place in the
+    partitions differs with K, unsorted columns and duplicates.  Every row
+    within the bound, and the same bits for K = 1, 4 and 20."""
+    say(f"binned spmv {case} {ncols} columns")
+    r = np.random.default_rng(len(case))
+    n = 1 if case == "one_row" else 3001
+    lens = {"empty_rows": r.integers(0, 3, n) * r.integers(0, 2, n), "long_rows": r.integers(0, 700, n),
+            "dense_block": np.where((np.arange(n) > 700) & (np.arange(n) < 760), 9000, 3),
+            "short_rows": r.integers(0, 5, n), "one_row": np.array([30000]), "wide": r.integers(0, 40, n)}[case]
+    rp, col, val, x = _rows_matrix(lens, ncols, seed=31)
+    ref = oracle.spmv_csr(rp, col, val, x)
+    bound = 1e-13 * _row_bound(rp, col, val, x)
+    cfg = jacc.config(order=4)
+    ys = [_spmv_dev(rp, col, val, x, K, cfg) for K in (1, 4, 20) if K <= n]
+    assert np.all(np.abs(ys[0] - ref) <= bound)
+    for y in ys[1:]:
+        assert np.array_equal(y, ys[0])
+
+
+def test_binned_products_of_one_matrix_on_two_streams():
+    """Two independent products of one matrix land on different streams and
+    share its device copy: each waits for the other's use of the copy."""
+    say("binned products on two streams")
+    n = 200_000
+    rp, col, val, x1 = inputs.csr_matrix(n, n, 16, seed=33)
+    x2 = inputs.uniform(n, seed=34, lo=-1.0, hi=1.0)
+    y1, y2 = np.zeros(n), np.zeros(n)
+    cfg = jacc.config(order=4)
+    with context(2) as c:
+        c.enter(rp, halo=(1, 1), K=1)
+        for a in (col, val, x1, x2):
+            c.enter(a, whole=True, K=1)
+        for y in (y1, y2):
+            c.enter(y, clause=jacc.CREATE, K=1)
+        for _ in range(30):
+            c.spmv(rp, col, val, x1, y1, cfg=cfg)
+            c.spmv(rp, col, val, x2, y2, cfg=cfg)
+        c.exit(y1)
+        c.exit(y2)
+    for x, y in ((x1, y1), (x2, y2)):
+        ref = oracle.spmv_csr(rp, col, val, x)
+        assert np.all(np.abs(y - ref) <= 1e-13 * _row_bound(rp, col, val, x))
+
+
+@pytest.mark.parametrize("lanes,per_row", [(4, 3), (8, 7), (16, 13)])
+def test_plain_spmv_lanes_follow_the_mean_row_length(lanes, per_row):
+    say(f"spmv default lanes for {per_row} entries a row")
+    rp, col, val, x = _rows_matrix(np.full(5003, per_row), 5003, seed=per_row)
+    y = _spmv_dev(rp, col, val, x, 1)
+    assert np.array_equal(y, _spmv_dev(rp, col, val, x, 1, jacc.config(tile=lanes, order=2)))
+    assert np.array_equal(y, _spmv_dev(rp, col, val, x, 3))
+    assert np.all(np.abs(y - oracle.spmv_csr(rp, col, val, x)) <= 1e-13 * _row_bound(rp, col, val, x))
