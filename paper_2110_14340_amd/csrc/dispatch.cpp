@@ -12,33 +12,129 @@ static int64_t inner_extent(const Launch &L) {
     return L.ext[nd - 1];
 }
 
+// The heat kernels' multi-row shape: threads, rows and planes a wave, and the
+// order of the tiles.  Times are us a step, in a graph.
+static Cfg heat_shape(const Launch &L, Cfg c) {
+    const int64_t cells = array_bytes(L) / 8;
+    const int64_t lanes = (L.ext[2] + c.vec - 1) / c.vec;
+    auto set = [&](int bx, int by, int tile, int rows, int order) {
+        c.bx = bx;
+        c.by = by;
+        c.tile = tile;
+        c.rows = rows;
+        c.order = order;
+        return c;
+    };
+    // 128x2 threads read a row in longer runs (95x131x203: 11.3, 14.1 as 64x4)
+    // unless that idles more lanes (300^3: 128 and 100)
+    const bool wide = (lanes + 127) / 128 * 128 == (lanes + 63) / 64 * 64;
+    if (cache_resident(L)) {
+        // bound by waves in flight before bytes: small tiles (64^3: 6.0 as
+        // 64x2x2 planes, 14 with 4 rows and 8 planes; 128^3 9.0 and 15.3),
+        // y-blocked bricks so that a tile's neighbours run on the same XCD
+        // (256^3: 43, 51 in row-major order).  Several partitions in one launch
+        // take 4 rows a wave (256^3 over 4: 59, 66 with 2; 128^3 11.7 and 11.3).
+        if (cells < (1 << 19)) return set(64, 2, 2, 2, 3);
+        const bool split = 3 * L.part_rows < 2 * L.ext[0] && cells >= (1 << 22);
+        return wide ? set(128, 2, 3, split ? 4 : 2, 3) : set(64, 4, 3, split ? 4 : 2, 3);
+    }
+    // bound by HBM: 4 rows and 8 planes re-read the least.  A row held by one
+    // workgroup (up to 256 lanes) streams best in row-major order from 256x1
+    // threads (300x300x386: 124, 137 as 64x4; 400^3 213 and 232), except full
+    // ones, whose power-of-two strides prefer bricks of 128x2 (512^3: 394, 408 as
+    // 256x1; 512x512x510: 418 and 435).  Other rows: 128x2 where it idles no
+    // lanes and a row fits (700x700x200: 312, 356 as 64x4), 64x4 elsewhere
+    // (300^3: 97, 123 as 128x2; 60x1000x1400: 255 and 276).
+    if (lanes > 248 && lanes <= 256) return set(128, 2, 4, 4, 3);
+    if (lanes > 192 && lanes <= 256) return set(256, 1, 8, 4, 1);
+    if (lanes <= 128 && wide) return set(128, 2, 4, 4, 1);
+    return set(64, 4, 8, 4, 1);
+}
+
 Cfg default_config(int kind, const Launch &L, Cfg c) {
-    const bool even = (inner_extent(L) % 2) == 0;
+    const bool odd = inner_extent(L) % 2 != 0;
     switch (kind) {
-        case JACC_LOOP_JACOBI2D:
-            if (!c.bx) c.bx = 256;
-            if (!c.by) c.by = 1;
-            // measured: 4-row tiles for eager launches and for task-kernel
-            // tiles at every partition count (8190-column grids and 512^2,
-            // K = 1..8)
-            if (!c.tile) c.tile = 4;
-            if (!c.vec) c.vec = even ? 2 : 1;
-            if (!c.order) c.order = 1;
+        case JACC_LOOP_JACOBI2D: {
+            if (!c.vec) {
+                c.vec = 2;
+                c.odd = odd;
+            }
             if (!c.march) c.march = 2;
             if (!c.rows) c.rows = 1;
+            if (c.persistent) {  // tiles of 256 threads along a row
+                if (!c.bx) c.bx = 256;
+                if (!c.by) c.by = 1;
+                if (!c.tile) c.tile = 4;
+                if (!c.order) c.order = 1;
+                break;
+            }
+            // 256x1 threads when a row's tiles are a multiple of the 8 XCDs: the
+            // tile below then runs on the same XCD, and the rows both need meet
+            // in its L2 (8192^2: 171 us, 177 as 64x4).  Otherwise 64x4, whose
+            // waves share those rows within the workgroup (5000^2: 75 us as
+            // 256x1, 69 as 64x4; 6000^2 108 and 98).
+            const bool cached = cache_resident(L);
+            const int64_t cells = array_bytes(L) / 8;
+            // under 4096 cells a step is its launch, and the shape stays
+            // 256x1 of 4 rows, as loop records report it (60x60 in a graph: 3.6
+            // us, 2.9 as 64x4 of 1)
+            const bool tiny = cells < 4096;
+            const bool along = tiny || (!cached && ((L.ext[1] + 511) / 512) % 8 == 0);
+            if (!c.bx && !c.by && !along) {
+                c.bx = 64;
+                c.by = 4;
+            }
+            if (!c.bx) c.bx = 256;
+            if (!c.by) c.by = 1;
+            // short tiles while there are few of them (512^2: 3.9 us with 2
+            // rows, 4.3 with 4, 5.4 with 8; 2048^2: 12.3 with 4, 11.9 with 8)
+            if (!c.tile) c.tile = !cached || tiny ? 4 : cells < (1 << 20) ? 2 : cells < (1 << 22) ? 4 : 8;
+            if (!c.order) c.order = cached ? 2 : 1;
             break;
-        case JACC_LOOP_HEAT3D:
+        }
+        case JACC_LOOP_HEAT3D: {
+            if (!c.vec) {
+                c.vec = 2;
+                c.odd = odd;
+            }
+            if (!c.march) c.march = 2;
+            const Cfg given = c;
             if (!c.rows) {  // multi-row waves need workgroups of at most 256 threads
                 const int bx = c.bx ? c.bx : 128, by = c.by ? c.by : 2;
-                c.rows = (c.persistent || bx * by > 256) ? 1 : 4;
+                if (c.persistent || bx * by > 256) c.rows = 1;
             }
-            if (!c.bx) c.bx = c.rows > 1 ? 128 : 256;
-            if (!c.by) c.by = c.rows > 1 ? 2 : 4;
-            if (!c.tile) c.tile = c.rows > 1 ? 8 : 4;
-            if (!c.vec) c.vec = even ? 2 : 1;
-            if (!c.order) c.order = c.rows > 1 ? 3 : 1;  // y-blocked bricks: 8 % read overfetch instead of 41 %
-            if (!c.march) c.march = 2;
+            if (c.rows == 1) {
+                if (!c.bx) c.bx = 256;
+                if (!c.by) c.by = 4;
+                if (!c.tile) c.tile = 4;
+                if (!c.order) c.order = 1;
+                break;
+            }
+            const Cfg d = heat_shape(L, c);
+            if (!c.bx && !c.by) {
+                c.bx = d.bx;
+                c.by = d.by;
+            }
+            if (!c.bx) c.bx = 128;
+            if (!c.by) c.by = 2;
+            if (!c.rows) c.rows = d.rows;
+            if (!c.tile) c.tile = d.tile;
+            if (!c.order) c.order = d.order;
+            // a residual takes one partial sum per workgroup: fields with more
+            // workgroups than half the partial buffer take 128x2 threads, 4 rows
+            // and 8 planes, which serve every field that fits at all
+            const int64_t wgs = ((L.ext[2] + (int64_t)c.bx * c.vec - 1) / ((int64_t)c.bx * c.vec)) *
+                                ((L.ext[1] + (int64_t)c.by * c.rows - 1) / ((int64_t)c.by * c.rows)) *
+                                ((L.ext[0] + c.tile - 1) / c.tile);
+            if (wgs > kWgCapacity / 2) {
+                c.bx = given.bx ? given.bx : 128;
+                c.by = given.by ? given.by : 2;
+                c.rows = given.rows ? given.rows : 4;
+                c.tile = given.tile ? given.tile : 8;
+                c.order = given.order ? given.order : 3;
+            }
             break;
+        }
         default:
             if (!c.bx) c.bx = 256;
             if (!c.by) c.by = 1;
@@ -64,7 +160,7 @@ int check_config(const Launch &L) {
             if (c.bx < 64 || c.bx % 64 || c.by < 1 || c.bx * c.by > 1024) return 1;
             if (c.tile < 1 || c.tile > 65536) return 1;
             if (c.vec != 1 && c.vec != 2) return 1;
-            if (c.vec == 2 && inner_extent(L) % 2) return 1;
+            if (c.vec == 2 && inner_extent(L) % 2 && !c.odd) return 1;
             if (c.order != 1 && c.order != 2 && (c.order != 3 || L.kind != JACC_LOOP_HEAT3D)) return 1;
             if (c.march != 1 && c.march != 2) return 1;
             if (c.rows != 1 && (L.kind != JACC_LOOP_HEAT3D || c.persistent)) return 1;

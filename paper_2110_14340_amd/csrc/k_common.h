@@ -8,12 +8,14 @@ namespace jk {
 constexpr int kWave = 64;
 
 typedef double dvec2 __attribute__((ext_vector_type(2)));
+// a pair at any 8-byte address (16-byte accesses need no more on this chip)
+typedef double dpair __attribute__((ext_vector_type(2), aligned(8)));
 
-// VEC consecutive doubles from a (16-byte aligned when VEC == 2) address.
+// VEC consecutive doubles.
 template <int VEC>
 __device__ __forceinline__ void load_vec(const double *p, double (&v)[VEC]) {
     if constexpr (VEC == 2) {
-        const dvec2 t = *reinterpret_cast<const dvec2 *>(p);
+        const dpair t = *reinterpret_cast<const dpair *>(p);
         v[0] = t.x;
         v[1] = t.y;
     } else {

@@ -32,8 +32,6 @@ constexpr int kGemmThreads = 256;  // 2 x 2 waves
 constexpr int kStage = 8;          // k's of a stage
 
 typedef double d4 __attribute__((ext_vector_type(4)));
-// a pair at any 8-byte address (rows of odd length start at odd multiples of 8)
-typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
 
 // Tile of workgroup b: the 8 XCDs take consecutive workgroup ids in turn, so
 // XCD x is given the x-th contiguous eighth of the tiles; inside it, tiles
@@ -103,7 +101,7 @@ gemm_kernel(const double *__restrict__ A, const double *__restrict__ B, double *
 #pragma unroll
         for (int j = 0; j < NJ; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
 
-    d2u a[S][MI], b[S][2][NJ / 2];
+    dpair a[S][MI], b[S][2][NJ / 2];
     // A pair at a uniform base plus a lane's offset.  Large tiles keep the
     // compiler from hoisting the offset's widening out of the loop: the load
     // then takes base and offset as they are, and the two registers a load
@@ -111,7 +109,7 @@ gemm_kernel(const double *__restrict__ A, const double *__restrict__ B, double *
     // running side by side 2020 -> 1920 us; alone 1871 -> 1865).
     auto at = [&](const char *base, Off off) {
         if constexpr (MI * NJ >= 8) asm volatile("" : "+v"(off));
-        return *reinterpret_cast<const d2u *>(base + off);
+        return *reinterpret_cast<const dpair *>(base + off);
     };
     int64_t next = 0;  // the stage loaded next: ap and bp are its base addresses
     auto load = [&](int s) {
@@ -125,8 +123,8 @@ gemm_kernel(const double *__restrict__ A, const double *__restrict__ B, double *
                 b[s][1][g] = at(b1, boff[g]);
             } else {
                 const int64_t k = next * kStage + 2 * q;
-                b[s][0][g] = d2u{single(k, g, 0), single(k, g, 1)};
-                b[s][1][g] = d2u{single(k + 1, g, 0), single(k + 1, g, 1)};
+                b[s][0][g] = dpair{single(k, g, 0), single(k, g, 1)};
+                b[s][1][g] = dpair{single(k + 1, g, 0), single(k + 1, g, 1)};
             }
         }
         ap += kStage * 8;
@@ -181,7 +179,7 @@ gemm_kernel(const double *__restrict__ A, const double *__restrict__ B, double *
                 a[0][i][t] = in ? *reinterpret_cast<const double *>(ap + aoff[i] + 8 * t) : 0.0;
 #pragma unroll
             for (int g = 0; g < NJ / 2; ++g) {
-                b[0][t][g] = d2u{0.0, 0.0};
+                b[0][t][g] = dpair{0.0, 0.0};
                 if (in) {
                     b[0][t][g].x = single(k, g, 0);
                     b[0][t][g].y = single(k, g, 1);
@@ -202,7 +200,7 @@ gemm_kernel(const double *__restrict__ A, const double *__restrict__ B, double *
                 double *p = C + gi * N + cs[g];
                 const double x = acc[i][2 * g][r], y = acc[i][2 * g + 1][r];
                 if (cs[g] >= n_lo && cs[g] + 1 < n_hi) {
-                    *reinterpret_cast<d2u *>(p) = d2u{x, y};
+                    *reinterpret_cast<dpair *>(p) = dpair{x, y};
                 } else {  // a pair across the box's edge
                     if (cs[g] >= n_lo && cs[g] < n_hi) p[0] = x;
                     if (cs[g] + 1 >= n_lo && cs[g] + 1 < n_hi) p[1] = y;

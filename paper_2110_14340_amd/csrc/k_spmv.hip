@@ -317,7 +317,6 @@ bin_fill_kernel(BinParts bp, const int32_t *__restrict__ col, const double *__re
 // ---- product ----------------------------------------------------------------
 typedef uint16_t us4 __attribute__((ext_vector_type(4)));
 typedef uint16_t us2u __attribute__((ext_vector_type(2), aligned(2)));
-typedef double pair_u __attribute__((ext_vector_type(2), aligned(8)));
 
 // prod = bval * x[bcol] over this workgroup's share of the column-block-major
 // order.  The entries that align a column block's start hold anything: their
@@ -402,7 +401,7 @@ bin_sum_kernel(BinParts bp, int rb, int nblk, int nc, const int32_t *__restrict_
     }
     for (int c0 = q; inlds && c0 < nc; c0 += kQ * kU) {
         int32_t at[kU], n[kU];
-        pair_u p[kU], p2[kU];
+        dpair p[kU], p2[kU];
         us2u d[kU], d2[kU];
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
@@ -417,11 +416,11 @@ bin_sum_kernel(BinParts bp, int rb, int nblk, int nc, const int32_t *__restrict_
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
             if (sub < n[u]) {
-                p[u] = *reinterpret_cast<const pair_u *>(prod + at[u] + sub);
+                p[u] = *reinterpret_cast<const dpair *>(prod + at[u] + sub);
                 d[u] = *reinterpret_cast<const us2u *>(dst + at[u] + sub);
             }
             if (sub + kP < n[u]) {
-                p2[u] = *reinterpret_cast<const pair_u *>(prod + at[u] + sub + kP);
+                p2[u] = *reinterpret_cast<const dpair *>(prod + at[u] + sub + kP);
                 d2[u] = *reinterpret_cast<const us2u *>(dst + at[u] + sub + kP);
             }
         }

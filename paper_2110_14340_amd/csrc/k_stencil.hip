@@ -29,6 +29,15 @@ namespace {
 
 constexpr int kU = 4;  // rows loaded ahead of the rows being computed
 
+// Lane widths (V): 1 one double a lane; 2 two, in rows whose length (or, for a
+// column slab, pitch) is even, so a pair never straddles a row's end; 3 two in
+// rows of odd length: pairs are then 16-byte accesses at 8-byte addresses,
+// and the lane that holds a row's last column loads it alone.  One double a
+// lane in such rows moves half the bytes an instruction (4099 x 3001 split by
+// columns: 51 us a sweep with one, 36 with two; 95 x 131 x 203 heat steps 21.5
+// and 14.0 us).
+constexpr int vec_of(int V) { return V == 1 ? 1 : 2; }
+
 // One ring entry: VEC own values plus, for the two edge lanes of the wave,
 // the element just left (lane 0) or right (lane 63) of the wave's span.
 template <int VEC>
@@ -37,15 +46,29 @@ struct Row {
     double edge;
 };
 
-template <int VEC>
-__device__ __forceinline__ void load_row(const double *__restrict__ p, bool inb, int lane, bool need_l, bool need_r,
-                                         Row<VEC> &r) {
-    if (inb) {
-        load_vec<VEC>(p, r.v);
+// What a lane loads of a row: its VEC values, nothing, or (V = 3) the first of
+// its two alone, the row's last column.
+enum Span { kNone, kAll, kFirst };
+template <int V>
+__device__ __forceinline__ Span span_of(bool inb, int64_t j, int64_t nx) {
+    return !inb ? kNone : (V == 3 && j + 1 >= nx) ? kFirst : kAll;
+}
+
+template <int V>
+__device__ __forceinline__ void load_span(const double *__restrict__ p, Span in, double (&v)[vec_of(V)]) {
+    if (in == kAll) {
+        load_vec<vec_of(V)>(p, v);
     } else {
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) r.v[v] = 0.0;
+        for (int k = 0; k < vec_of(V); ++k) v[k] = 0.0;
+        if (V == 3 && in == kFirst) v[0] = *p;
     }
+}
+
+template <int V, int VEC = vec_of(V)>
+__device__ __forceinline__ void load_row(const double *__restrict__ p, Span in, int lane, bool need_l, bool need_r,
+                                         Row<VEC> &r) {
+    load_span<V>(p, in, r.v);
     r.edge = 0.0;
     if (lane == 0 && need_l) r.edge = p[-1];
     if (lane == kWave - 1 && need_r) r.edge = p[VEC];
@@ -71,27 +94,34 @@ __device__ __forceinline__ void horizontal(const Row<VEC> &mid, int lane, double
 // global-address-space pointer: a pointer read from a descriptor table or
 // picked by a loop index is otherwise generic, and stored through with flat
 // operations, which count against the counter the cross-lane shuffles wait
-// on.  Full-vector stores are non-temporal: a sweep's output is not read
-// again in the same launch.
-template <int VEC>
-__device__ __forceinline__ void store_nt(double *p, const double (&o)[VEC]) {
+// on.  NT: full-vector stores are non-temporal, as a sweep's output is not
+// read again in the same launch; but they also pass the 256 MB memory-side
+// cache by, so arrays that fit it are stored to normally and the next sweep
+// reads them from there (kCacheBytes).
+template <int VEC, bool NT>
+__device__ __forceinline__ void store_vec(double *p, const double (&o)[VEC]) {
     typedef __attribute__((address_space(1))) double GDouble;
-    typedef __attribute__((address_space(1))) dvec2 GDvec2;
+    typedef __attribute__((address_space(1))) dpair GDpair;
     GDouble *q = (GDouble *)p;
     if constexpr (VEC == 2) {
-        dvec2 t;
+        dpair t;
         t.x = o[0];
         t.y = o[1];
-        __builtin_nontemporal_store(t, (GDvec2 *)q);
-    } else {
+        if constexpr (NT)
+            __builtin_nontemporal_store(t, (GDpair *)q);
+        else
+            *(GDpair *)q = t;
+    } else if constexpr (NT) {
         __builtin_nontemporal_store(o[0], q);
+    } else {
+        *q = o[0];
     }
 }
 
-template <int VEC>
+template <int VEC, bool NT>
 __device__ __forceinline__ void store_masked(double *p, const double (&o)[VEC], bool all, const bool (&comp)[VEC]) {
     if (all) {
-        store_nt<VEC>(p, o);
+        store_vec<VEC, NT>(p, o);
     } else {
         typedef __attribute__((address_space(1))) double GDouble;
         GDouble *q = (GDouble *)p;
@@ -119,10 +149,10 @@ __device__ __forceinline__ void store_masked(double *p, const double (&o)[VEC], 
 // and again into every mirror holding row r (uniform test per row); with
 // column mirrors (MM 3 and 4) each computed element of columns col ..
 // col+VEC-1 that a holder keeps goes to that holder's slab as well.
-template <int VEC, int MM, typename MT = Mirrors>
+template <int VEC, int MM, bool NT, typename MT = Mirrors>
 __device__ __forceinline__ void store_out(double *out, int64_t off, int64_t r, int64_t col, const MT &mir,
                                           const double (&o)[VEC], bool all, const bool (&comp)[VEC]) {
-    store_masked<VEC>(out + off, o, all, comp);
+    store_masked<VEC, NT>(out + off, o, all, comp);
     if constexpr (MM == 3 || MM == 4) {
         typedef __attribute__((address_space(1))) double GDouble;
         constexpr int kN = MM == 4 ? 2 : 0;  // 4: unrolled over the descriptor's two entries
@@ -140,12 +170,12 @@ __device__ __forceinline__ void store_out(double *out, int64_t off, int64_t r, i
         }
     } else if constexpr (MM == 1) {
         for (int k = 0; k < mir.n; ++k)
-            if (r >= mir.m[k].lo && r < mir.m[k].hi) store_masked<VEC>(mir.m[k].ptr + off, o, all, comp);
+            if (r >= mir.m[k].lo && r < mir.m[k].hi) store_masked<VEC, NT>(mir.m[k].ptr + off, o, all, comp);
     } else if constexpr (MM == 2) {
 #pragma unroll
         for (int k = 0; k < 2; ++k)
             if (k < mir.n && r >= mir.m[k].lo && r < mir.m[k].hi)
-                store_masked<VEC>(mir.m[k].ptr + off, o, all, comp);
+                store_masked<VEC, NT>(mir.m[k].ptr + off, o, all, comp);
     }
 }
 
@@ -160,12 +190,13 @@ __device__ __forceinline__ int64_t march_dir(int march, int64_t q) { return (mar
 // ---------------------------------------------------------------------------
 // Jacobi-2D tile: lanes [tx] of row-group [ty] of workgroup tile (bxi, byi)
 // ---------------------------------------------------------------------------
-template <int VEC, int MM, typename MT = Mirrors>
+template <int V, int MM, bool NT, typename MT = Mirrors>
 __device__ __forceinline__ void jacobi_tile(const double *__restrict__ in, double *__restrict__ out, int64_t nx,
                                             int64_t pitch, int64_t r_lo, int64_t r_hi, int64_t c_lo, int64_t c_hi,
                                             int64_t col0, int tile, int march, const MT &mir, int64_t bxi,
                                             int64_t byi, int tx, int ty, int bdx, int bdy,
                                             int64_t own_lo = INT64_MIN, int64_t own_hi = INT64_MAX) {
+    constexpr int VEC = vec_of(V);
     const int lane = tx & (kWave - 1);
     const int64_t j = col0 + (bxi * bdx + tx) * VEC;
     const int64_t q = byi * bdy + ty;
@@ -175,7 +206,7 @@ __device__ __forceinline__ void jacobi_tile(const double *__restrict__ in, doubl
     const int64_t n = i1 - i0;
     const int64_t d = march_dir(march, q);
     const int64_t a = d > 0 ? i0 : i1 - 1;  // first row computed
-    const bool inb = j < c_hi + 1 && j < nx;  // lane holds columns the box needs
+    const Span inb = span_of<V>(j < c_hi + 1 && j < nx, j, nx);  // lane holds columns the box needs
     bool comp[VEC];
     bool all = true;
 #pragma unroll
@@ -190,13 +221,13 @@ __device__ __forceinline__ void jacobi_tile(const double *__restrict__ in, doubl
     Row<VEC> r[kU + 2];
 #pragma unroll
     for (int k = 0; k < kU + 2; ++k)
-        if (k <= n + 1) load_row<VEC>(in + (a + (k - 1) * d) * pitch + j, inb, lane, need_l, need_r, r[k]);
+        if (k <= n + 1) load_row<V>(in + (a + (k - 1) * d) * pitch + j, inb, lane, need_l, need_r, r[k]);
     for (int64_t m = 0; m < n; m += kU) {
         Row<VEC> nxt[kU];
 #pragma unroll
         for (int k = 0; k < kU; ++k) {
             const int64_t idx = m + kU + 2 + k;
-            if (idx <= n + 1) load_row<VEC>(in + (a + (idx - 1) * d) * pitch + j, inb, lane, need_l, need_r, nxt[k]);
+            if (idx <= n + 1) load_row<V>(in + (a + (idx - 1) * d) * pitch + j, inb, lane, need_l, need_r, nxt[k]);
         }
 #pragma unroll
         for (int k = 0; k < kU; ++k) {
@@ -214,7 +245,7 @@ __device__ __forceinline__ void jacobi_tile(const double *__restrict__ in, doubl
                 }
                 // write guard of a filtered loop (every partition computes the
                 // whole box and keeps its owner rows); uniform per row
-                if (row >= own_lo && row < own_hi) store_out<VEC, MM, MT>(out, row * pitch + j, row, j, mir, o, all, comp);
+                if (row >= own_lo && row < own_hi) store_out<VEC, MM, NT, MT>(out, row * pitch + j, row, j, mir, o, all, comp);
             }
         }
 #pragma unroll
@@ -226,32 +257,36 @@ __device__ __forceinline__ void jacobi_tile(const double *__restrict__ in, doubl
 
 // Tile of a 1-D grid's workgroup: row-major (order 1), or XCD-aware (order
 // 2): workgroup b runs on XCD b mod 8, and XCD x takes the x-th contiguous
-// eighth of the tiles in row-major order.
-__device__ __forceinline__ int64_t tile_of(int order) {
-    const int64_t b = blockIdx.x, n = gridDim.x;
-    if (order == 2 && (n & 7) == 0) return (b & 7) * (n >> 3) + (b >> 3);
-    return b;
+// eighth of the tiles in row-major order (the grid is then the tiles rounded
+// up to a multiple of 8; -1: a workgroup past the last tile).
+__device__ __forceinline__ int64_t tile_of(int order, int64_t tiles) {
+    const int64_t b = blockIdx.x;
+    if (order != 2) return b;
+    const int64_t t = (b & 7) * ((int64_t)gridDim.x >> 3) + (b >> 3);
+    return t < tiles ? t : -1;
 }
 
-template <int VEC, int MM>
+template <int V, int MM, bool NT>
 __global__ void __launch_bounds__(1024)
 jacobi2d_kernel(const double *__restrict__ in, double *__restrict__ out, int64_t nx, int64_t pitch, int64_t r_lo,
                 int64_t r_hi, int64_t c_lo, int64_t c_hi, int64_t col0, int tile, int march, Mirrors mir, int64_t gx,
-                int order, int64_t own_lo, int64_t own_hi) {
-    const int64_t t = tile_of(order);
-    jacobi_tile<VEC, MM>(in, out, nx, pitch, r_lo, r_hi, c_lo, c_hi, col0, tile, march, mir, t % gx, t / gx, threadIdx.x,
+                int64_t tiles, int order, int64_t own_lo, int64_t own_hi) {
+    const int64_t t = tile_of(order, tiles);
+    if (t < 0) return;
+    jacobi_tile<V, MM, NT>(in, out, nx, pitch, r_lo, r_hi, c_lo, c_hi, col0, tile, march, mir, t % gx, t / gx, threadIdx.x,
                      threadIdx.y, blockDim.x, blockDim.y, own_lo, own_hi);
 }
 
 // The same sweep over a column slab of an array split along dim 1 whose
 // written columns other slabs keep (column mirrors).
-template <int VEC>
+template <int V, bool NT>
 __global__ void __launch_bounds__(1024)
 jacobi2d_cols_kernel(const double *__restrict__ in, double *__restrict__ out, int64_t nx, int64_t pitch, int64_t r_lo,
                      int64_t r_hi, int64_t c_lo, int64_t c_hi, int64_t col0, int tile, int march, ColMirrors mir,
-                     int64_t gx, int order) {
-    const int64_t t = tile_of(order);
-    jacobi_tile<VEC, 3, ColMirrors>(in, out, nx, pitch, r_lo, r_hi, c_lo, c_hi, col0, tile, march, mir, t % gx, t / gx,
+                     int64_t gx, int64_t tiles, int order) {
+    const int64_t t = tile_of(order, tiles);
+    if (t < 0) return;
+    jacobi_tile<V, 3, NT, ColMirrors>(in, out, nx, pitch, r_lo, r_hi, c_lo, c_hi, col0, tile, march, mir, t % gx, t / gx,
                                     threadIdx.x, threadIdx.y, blockDim.x, blockDim.y);
 }
 
@@ -259,13 +294,14 @@ jacobi2d_cols_kernel(const double *__restrict__ in, double *__restrict__ out, in
 // Heat-3D tile: row y = y_lo + byi*bdy + ty, planes [z_lo + bzi*tile, +tile)
 // Returns this lane's sum of (u'-u)^2 when RES.
 // ---------------------------------------------------------------------------
-template <int VEC, bool RES, int MM>
+template <int V, bool RES, int MM, bool NT>
 __device__ __forceinline__ double heat_tile(const double *__restrict__ in, double *__restrict__ out, int64_t ny,
                                             int64_t nx, int64_t z_lo, int64_t z_hi, int64_t y_lo, int64_t y_hi,
                                             int64_t x_lo, int64_t x_hi, int64_t col0, int tile, int march, double alpha,
                                             const Mirrors &mir, int64_t bxi, int64_t byi, int64_t bzi, int tx,
                                             int ty, int bdx, int bdy, int64_t own_lo = INT64_MIN,
                                             int64_t own_hi = INT64_MAX) {
+    constexpr int VEC = vec_of(V);
     const int lane = tx & (kWave - 1);
     const int64_t x = col0 + (bxi * bdx + tx) * VEC;
     const int64_t y = y_lo + byi * bdy + ty;
@@ -276,7 +312,7 @@ __device__ __forceinline__ double heat_tile(const double *__restrict__ in, doubl
     const int64_t n = z1 - z0;
     const int64_t d = march_dir(march, bzi);
     const int64_t a = d > 0 ? z0 : z1 - 1;  // first plane computed
-    const bool inb = x < x_hi + 1 && x < nx;
+    const Span inb = span_of<V>(x < x_hi + 1 && x < nx, x, nx);
     bool comp[VEC];
     bool all = true;
 #pragma unroll
@@ -293,13 +329,13 @@ __device__ __forceinline__ double heat_tile(const double *__restrict__ in, doubl
     Row<VEC> r[kU + 2];
 #pragma unroll
     for (int k = 0; k < kU + 2; ++k)
-        if (k <= n + 1) load_row<VEC>(base + (a + (k - 1) * d) * plane, inb, lane, need_l, need_r, r[k]);
+        if (k <= n + 1) load_row<V>(base + (a + (k - 1) * d) * plane, inb, lane, need_l, need_r, r[k]);
     for (int64_t m = 0; m < n; m += kU) {
         Row<VEC> nxt[kU];
 #pragma unroll
         for (int k = 0; k < kU; ++k) {
             const int64_t idx = m + kU + 2 + k;
-            if (idx <= n + 1) load_row<VEC>(base + (a + (idx - 1) * d) * plane, inb, lane, need_l, need_r, nxt[k]);
+            if (idx <= n + 1) load_row<V>(base + (a + (idx - 1) * d) * plane, inb, lane, need_l, need_r, nxt[k]);
         }
 #pragma unroll
         for (int k = 0; k < kU; ++k) {
@@ -310,13 +346,8 @@ __device__ __forceinline__ double heat_tile(const double *__restrict__ in, doubl
                 // y neighbours: rows of the same plane (cache hits)
                 double ym[VEC], yp[VEC];
                 const double *pc = base + z * plane;
-                if (inb) {
-                    load_vec<VEC>(pc - nx, ym);
-                    load_vec<VEC>(pc + nx, yp);
-                } else {
-#pragma unroll
-                    for (int v = 0; v < VEC; ++v) ym[v] = yp[v] = 0.0;
-                }
+                load_span<V>(pc - nx, inb, ym);
+                load_span<V>(pc + nx, inb, yp);
                 double xm[VEC], xp[VEC];
                 horizontal<VEC>(c, lane, xm, xp);
                 double o[VEC];
@@ -332,7 +363,7 @@ __device__ __forceinline__ double heat_tile(const double *__restrict__ in, doubl
                         acc += dd * dd;
                     }
                 }
-                if (keep) store_out<VEC, MM>(out, z * plane + y * nx + x, z, x, mir, o, all, comp);
+                if (keep) store_out<VEC, MM, NT>(out, z * plane + y * nx + x, z, x, mir, o, all, comp);
             }
         }
 #pragma unroll
@@ -360,19 +391,14 @@ struct Planes {
     double edge[R];        // beside the wave's span, rows 1..R (edge lanes only)
 };
 
-template <int VEC, int R>
+template <int V, int R, int VEC = vec_of(V)>
 __device__ __forceinline__ void load_plane(const double *__restrict__ p, int64_t nx, int64_t yb, int64_t y_hi, int rr,
-                                           bool inb, int lane, bool need_l, bool need_r, Planes<VEC, R> &P) {
+                                           Span inb, int lane, bool need_l, bool need_r, Planes<VEC, R> &P) {
 #pragma unroll
     for (int k = 0; k < R + 2; ++k) {
         const int64_t y = yb + k - 1 < y_hi ? yb + k - 1 : y_hi;
         const double *q = p + y * nx;
-        if (inb) {
-            load_vec<VEC>(q, P.v[k]);
-        } else {
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) P.v[k][v] = 0.0;
-        }
+        load_span<V>(q, inb, P.v[k]);
         if (k >= 1 && k <= R) {
             P.edge[k - 1] = 0.0;
             if (k - 1 < rr) {
@@ -383,13 +409,14 @@ __device__ __forceinline__ void load_plane(const double *__restrict__ p, int64_t
     }
 }
 
-template <int VEC, int R, bool RES, int MM>
+template <int V, int R, bool RES, int MM, bool NT>
 __device__ __forceinline__ double heat_rows_tile(const double *__restrict__ in, double *__restrict__ out, int64_t ny,
                                                  int64_t nx, int64_t z_lo, int64_t z_hi, int64_t y_lo, int64_t y_hi,
                                                  int64_t x_lo, int64_t x_hi, int64_t col0, int tile, int march,
                                                  double alpha, const Mirrors &mir, int64_t bxi, int64_t byi,
                                                  int64_t bzi, int tx, int ty, int bdx, int bdy, int64_t own_lo,
                                                  int64_t own_hi) {
+    constexpr int VEC = vec_of(V);
     const int lane = tx & (kWave - 1);
     const int64_t x = col0 + (bxi * bdx + tx) * VEC;
     const int64_t yb = y_lo + (byi * bdy + ty) * R;
@@ -401,7 +428,7 @@ __device__ __forceinline__ double heat_rows_tile(const double *__restrict__ in, 
     const int64_t n = z1 - z0;
     const int64_t d = march_dir(march, bzi);
     const int64_t a = d > 0 ? z0 : z1 - 1;  // first plane computed
-    const bool inb = x < x_hi + 1 && x < nx;
+    const Span inb = span_of<V>(x < x_hi + 1 && x < nx, x, nx);
     bool comp[VEC];
     bool all = true;
 #pragma unroll
@@ -416,7 +443,7 @@ __device__ __forceinline__ double heat_rows_tile(const double *__restrict__ in, 
 
     // plane k (k = 0 .. n+1) is a + (k-1)*d
     auto load = [&](int64_t k, Planes<VEC, R> &P) {
-        load_plane<VEC, R>(col + (a + (k - 1) * d) * plane, nx, yb, y_hi, rr, inb, lane, need_l, need_r, P);
+        load_plane<V, R>(col + (a + (k - 1) * d) * plane, nx, yb, y_hi, rr, inb, lane, need_l, need_r, P);
     };
     // computes plane m from A (plane m-1), B (m), C (m+1), then refills A
     // with plane m+2 (index k = m+3) when there is one
@@ -450,7 +477,7 @@ __device__ __forceinline__ double heat_rows_tile(const double *__restrict__ in, 
                         acc += dd * dd;
                     }
                 }
-                if (keep) store_out<VEC, MM>(out, z * plane + (yb + i) * nx + x, z, x, mir, o, all, comp);
+                if (keep) store_out<VEC, MM, NT>(out, z * plane + (yb + i) * nx + x, z, x, mir, o, all, comp);
             }
         }
     };
@@ -493,23 +520,23 @@ __device__ __forceinline__ void heat_coords(int64_t t, int64_t gx, int64_t gy, i
     }
 }
 
-template <int VEC, int R, bool RES, int MM>
+template <int V, int R, bool RES, int MM, bool NT>
 __global__ void __launch_bounds__(R == 1 ? 1024 : 256)
 heat3d_kernel(const double *__restrict__ in, double *__restrict__ out, int64_t ny, int64_t nx, int64_t z_lo,
               int64_t z_hi, int64_t y_lo, int64_t y_hi, int64_t x_lo, int64_t x_hi, int64_t col0, int tile,
               int march, double alpha, double *__restrict__ wg_partials, Mirrors mir, int64_t gx, int64_t gy,
-              int order, int64_t own_lo, int64_t own_hi) {
+              int64_t gz, int order, int64_t own_lo, int64_t own_hi) {
     __shared__ double sh[16];
-    const int64_t t = tile_of(order == 3 ? 2 : order);
-    const int64_t gz = (int64_t)gridDim.x / (gx * gy);
+    const int64_t t = tile_of(order == 3 ? 2 : order, gx * gy * gz);
+    if (t < 0) return;  // the whole workgroup: no barrier is left waiting
     int64_t bxi, byi, bzi;
     heat_coords(t, gx, gy, gz, order, bxi, byi, bzi);
     double acc;
     if constexpr (R == 1)
-        acc = heat_tile<VEC, RES, MM>(in, out, ny, nx, z_lo, z_hi, y_lo, y_hi, x_lo, x_hi, col0, tile, march, alpha, mir,
+        acc = heat_tile<V, RES, MM, NT>(in, out, ny, nx, z_lo, z_hi, y_lo, y_hi, x_lo, x_hi, col0, tile, march, alpha, mir,
                                   bxi, byi, bzi, threadIdx.x, threadIdx.y, blockDim.x, blockDim.y, own_lo, own_hi);
     else
-        acc = heat_rows_tile<VEC, R, RES, MM>(in, out, ny, nx, z_lo, z_hi, y_lo, y_hi, x_lo, x_hi, col0, tile, march,
+        acc = heat_rows_tile<V, R, RES, MM, NT>(in, out, ny, nx, z_lo, z_hi, y_lo, y_hi, x_lo, x_hi, col0, tile, march,
                                           alpha, mir, bxi, byi, bzi, threadIdx.x, threadIdx.y, blockDim.x,
                                           blockDim.y, own_lo, own_hi);
     if (RES) {
@@ -526,30 +553,38 @@ heat3d_kernel(const double *__restrict__ in, double *__restrict__ out, int64_t n
 // resident at once.
 // ---------------------------------------------------------------------------
 // One tile (local index `local`) of task T.
-template <bool JONLY>
+template <bool JONLY, bool NT>
 __device__ __forceinline__ void persistent_tile(const PTask &T, int64_t local) {
     const int64_t bxi = local % T.gx;
     const int64_t rest = local / T.gx;
     const double *in = T.in;
     double *out = T.out;
     const Mirrors mir = T.mir;
+    const int tx = threadIdx.x & (T.bx - 1), ty = threadIdx.x / T.bx, by = kPersistentThreads / T.bx;
     if (JONLY || T.kind == JACC_LOOP_JACOBI2D) {
         if (T.vec == 2)
-            jacobi_tile<2, 2>(in, out, T.e1, T.e1, T.lo[0], T.hi[0], T.lo[1], T.hi[1], T.col0, T.tile, T.march, mir, bxi,
-                           rest, threadIdx.x, 0, kPersistentThreads, 1);
+            jacobi_tile<2, 2, NT>(in, out, T.e1, T.e1, T.lo[0], T.hi[0], T.lo[1], T.hi[1], T.col0, T.tile, T.march, mir, bxi,
+                           rest, tx, ty, T.bx, by);
+        else if (T.vec == 3)
+            jacobi_tile<3, 2, NT>(in, out, T.e1, T.e1, T.lo[0], T.hi[0], T.lo[1], T.hi[1], T.col0, T.tile, T.march, mir, bxi,
+                           rest, tx, ty, T.bx, by);
         else
-            jacobi_tile<1, 2>(in, out, T.e1, T.e1, T.lo[0], T.hi[0], T.lo[1], T.hi[1], T.col0, T.tile, T.march, mir, bxi,
-                           rest, threadIdx.x, 0, kPersistentThreads, 1);
+            jacobi_tile<1, 2, NT>(in, out, T.e1, T.e1, T.lo[0], T.hi[0], T.lo[1], T.hi[1], T.col0, T.tile, T.march, mir, bxi,
+                           rest, tx, ty, T.bx, by);
     } else if constexpr (!JONLY) {
         const int64_t byi = rest % T.gy, bzi = rest / T.gy;
         if (T.vec == 2)
-            (void)heat_tile<2, false, 2>(in, out, T.e1, T.e2, T.lo[0], T.hi[0], T.lo[1], T.hi[1], T.lo[2], T.hi[2],
-                                      T.col0, T.tile, T.march, T.alpha, mir, bxi, byi, bzi, threadIdx.x, 0,
-                                      kPersistentThreads, 1);
+            (void)heat_tile<2, false, 2, NT>(in, out, T.e1, T.e2, T.lo[0], T.hi[0], T.lo[1], T.hi[1], T.lo[2], T.hi[2],
+                                      T.col0, T.tile, T.march, T.alpha, mir, bxi, byi, bzi, tx, ty,
+                                      T.bx, by);
+        else if (T.vec == 3)
+            (void)heat_tile<3, false, 2, NT>(in, out, T.e1, T.e2, T.lo[0], T.hi[0], T.lo[1], T.hi[1], T.lo[2], T.hi[2],
+                                      T.col0, T.tile, T.march, T.alpha, mir, bxi, byi, bzi, tx, ty,
+                                      T.bx, by);
         else
-            (void)heat_tile<1, false, 2>(in, out, T.e1, T.e2, T.lo[0], T.hi[0], T.lo[1], T.hi[1], T.lo[2], T.hi[2],
-                                      T.col0, T.tile, T.march, T.alpha, mir, bxi, byi, bzi, threadIdx.x, 0,
-                                      kPersistentThreads, 1);
+            (void)heat_tile<1, false, 2, NT>(in, out, T.e1, T.e2, T.lo[0], T.hi[0], T.lo[1], T.hi[1], T.lo[2], T.hi[2],
+                                      T.col0, T.tile, T.march, T.alpha, mir, bxi, byi, bzi, tx, ty,
+                                      T.bx, by);
     }
 }
 
@@ -572,6 +607,7 @@ __device__ __forceinline__ PTask load_task(ConstTask *p) {
     T.vec = p->vec;
     T.tile = p->tile;
     T.march = p->march;
+    T.bx = p->bx;
     T.in = p->in;
     T.out = p->out;
     T.e1 = p->e1;
@@ -596,7 +632,7 @@ __device__ __forceinline__ PTask load_task(ConstTask *p) {
     return T;
 }
 
-template <bool JONLY>
+template <bool JONLY, bool NT>
 __global__ void __launch_bounds__(kPersistentThreads)
 persistent_kernel(const PTask *__restrict__ tasks, int ntasks, int64_t total) {
     ConstTask *ct = (ConstTask *)tasks;
@@ -610,7 +646,7 @@ persistent_kernel(const PTask *__restrict__ tasks, int ntasks, int64_t total) {
                 hi = mid - 1;
         }
         const PTask T = load_task(ct + lo);
-        persistent_tile<JONLY>(T, t - T.tile_begin);
+        persistent_tile<JONLY, NT>(T, t - T.tile_begin);
     }
 }
 
@@ -670,14 +706,14 @@ __device__ __forceinline__ int64_t part_tile(const PartPack &pk, int order, Part
     return t < d.tiles ? t : -1;
 }
 
-template <int VEC, int MM>
+template <int V, int MM, bool NT>
 __global__ void __launch_bounds__(1024)
 jacobi2d_parts_kernel(PartPack pk, int64_t nx, int64_t c_lo, int64_t c_hi, int64_t col0, int tile, int march,
                       int64_t gx, int order) {
     PartDesc d;
     const int64_t t = part_tile(pk, order, d);
     if (t < 0) return;
-    jacobi_tile<VEC, MM>(d.in, d.out, nx, nx, d.lo0, d.hi0, c_lo, c_hi, col0, tile, march, d.mir, t % gx, t / gx,
+    jacobi_tile<V, MM, NT>(d.in, d.out, nx, nx, d.lo0, d.hi0, c_lo, c_hi, col0, tile, march, d.mir, t % gx, t / gx,
                      threadIdx.x, threadIdx.y, blockDim.x, blockDim.y);
 }
 
@@ -718,7 +754,7 @@ __device__ __forceinline__ ColPartDesc load_colpart(ConstColPart *p) {
     return d;
 }
 
-template <int VEC>
+template <int V, bool NT>
 __global__ void __launch_bounds__(1024)
 jacobi2d_colparts_kernel(ColPartPack pk, int64_t nx, int64_t r_lo, int64_t r_hi, int tile, int march, int order) {
     ConstColPart *cp = (ConstColPart *)&pk.p[0];
@@ -731,11 +767,11 @@ jacobi2d_colparts_kernel(ColPartPack pk, int64_t nx, int64_t r_lo, int64_t r_hi,
     const int64_t local = b - d.begin;
     const int64_t t = order >= 2 ? (local & 7) * (span >> 3) + (local >> 3) : local;
     if (t >= d.tiles) return;
-    jacobi_tile<VEC, 4, ColMirrors>(d.in, d.out, nx, d.pitch, r_lo, r_hi, d.c_lo, d.c_hi, d.col0, tile, march, d.mir,
+    jacobi_tile<V, 4, NT, ColMirrors>(d.in, d.out, nx, d.pitch, r_lo, r_hi, d.c_lo, d.c_hi, d.col0, tile, march, d.mir,
                                     t % d.gx, t / d.gx, threadIdx.x, threadIdx.y, blockDim.x, blockDim.y);
 }
 
-template <int VEC, int R, bool RES, int MM>
+template <int V, int R, bool RES, int MM, bool NT>
 __global__ void __launch_bounds__(R == 1 ? 1024 : 256)
 heat3d_parts_kernel(PartPack pk, int64_t ny, int64_t nx, int64_t y_lo, int64_t y_hi, int64_t x_lo, int64_t x_hi,
                     int64_t col0, int tile, int march, double alpha, double *__restrict__ wg_partials, int64_t gx,
@@ -749,10 +785,10 @@ heat3d_parts_kernel(PartPack pk, int64_t ny, int64_t nx, int64_t y_lo, int64_t y
     heat_coords(t, gx, gy, gz, order, bxi, byi, bzi);
     double acc;
     if constexpr (R == 1)
-        acc = heat_tile<VEC, RES, MM>(d.in, d.out, ny, nx, d.lo0, d.hi0, y_lo, y_hi, x_lo, x_hi, col0, tile, march, alpha,
+        acc = heat_tile<V, RES, MM, NT>(d.in, d.out, ny, nx, d.lo0, d.hi0, y_lo, y_hi, x_lo, x_hi, col0, tile, march, alpha,
                                   d.mir, bxi, byi, bzi, threadIdx.x, threadIdx.y, blockDim.x, blockDim.y);
     else
-        acc = heat_rows_tile<VEC, R, RES, MM>(d.in, d.out, ny, nx, d.lo0, d.hi0, y_lo, y_hi, x_lo, x_hi, col0, tile,
+        acc = heat_rows_tile<V, R, RES, MM, NT>(d.in, d.out, ny, nx, d.lo0, d.hi0, y_lo, y_hi, x_lo, x_hi, col0, tile,
                                           march, alpha, d.mir, bxi, byi, bzi, threadIdx.x, threadIdx.y, blockDim.x,
                                           blockDim.y, INT64_MIN, INT64_MAX);
     if (RES) {
@@ -768,6 +804,25 @@ heat3d_parts_kernel(PartPack pk, int64_t ny, int64_t nx, int64_t y_lo, int64_t y
 // ---------------------------------------------------------------------------
 static int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// Workgroups of a launch over `tiles` tiles.
+static unsigned grid_of(int64_t tiles, int order) { return (unsigned)(order >= 2 ? (tiles + 7) / 8 * 8 : tiles); }
+
+// Lane width of a launch (see vec_of): the innermost row length decides between
+// the two forms of pairs, a column slab's even pitch in place of it.
+static int width_of(const Launch &L) {
+    const int64_t row = L.kind == JACC_LOOP_HEAT3D ? L.ext[2] : L.a[0].row_elems;
+    return L.cfg.vec == 1 ? 1 : (row & 1) ? 3 : 2;
+}
+
+// A launch macro with its last argument (NT) from the local `nt`.
+#define WITH_NT(LAUNCH, ...)            \
+    do {                                \
+        if (nt)                         \
+            LAUNCH(__VA_ARGS__, true);  \
+        else                            \
+            LAUNCH(__VA_ARGS__, false); \
+    } while (0)
+
 static int64_t col_start(int64_t lo, int vec) { return vec == 2 ? (lo & ~(int64_t)1) : lo; }
 
 hipError_t launch_jacobi2d(const Launch &L, hipStream_t s) {
@@ -779,7 +834,8 @@ hipError_t launch_jacobi2d(const Launch &L, hipStream_t s) {
     if (nrows <= 0 || L.hi[1] <= L.lo[1]) return hipSuccess;
     dim3 block(c.bx, c.by);
     const int64_t gx = cdiv(ncols, (int64_t)c.bx * c.vec), gy = cdiv(nrows, (int64_t)c.by * c.tile);
-    dim3 grid((unsigned)(gx * gy));
+    const int64_t tiles = gx * gy;
+    const dim3 grid(grid_of(tiles, c.order));
     const double *in = (const double *)L.a[0].ptr;
     double *out = (double *)L.a[1].ptr;
     // elements between vertically adjacent values: the row length, or the
@@ -788,33 +844,36 @@ hipError_t launch_jacobi2d(const Launch &L, hipStream_t s) {
     if (L.a[1].row_elems != pitch) return hipErrorInvalidValue;
     const bool filtered = L.own_hi > L.own_lo;  // FILTERED output: keep the owner rows only
     const int64_t own_lo = filtered ? L.own_lo : INT64_MIN, own_hi = filtered ? L.own_hi : INT64_MAX;
-#define JACOBI_LAUNCH(V, M)                                                                                   \
-    hipLaunchKernelGGL((jacobi2d_kernel<V, M>), grid, block, 0, s, in, out, nx, pitch, L.lo[0], L.hi[0], L.lo[1], \
-                       L.hi[1], col0, c.tile, c.march, L.mir, gx, c.order, own_lo, own_hi)
+    const bool nt = !cache_resident(L);
+#define JACOBI_LAUNCH(V, M, N)                                                                                \
+    hipLaunchKernelGGL((jacobi2d_kernel<V, M, N>), grid, block, 0, s, in, out, nx, pitch, L.lo[0], L.hi[0], L.lo[1], \
+                       L.hi[1], col0, c.tile, c.march, L.mir, gx, tiles, c.order, own_lo, own_hi)
     if (L.cmir.n > 0) {  // column mirrors: an array split along dim 1
-#define JCOLS_LAUNCH(V)                                                                                           \
-    hipLaunchKernelGGL((jacobi2d_cols_kernel<V>), grid, block, 0, s, in, out, nx, pitch, L.lo[0], L.hi[0], L.lo[1], \
-                       L.hi[1], col0, c.tile, c.march, L.cmir, gx, c.order)
+#define JCOLS_LAUNCH(V, N)                                                                                        \
+    hipLaunchKernelGGL((jacobi2d_cols_kernel<V, N>), grid, block, 0, s, in, out, nx, pitch, L.lo[0], L.hi[0], L.lo[1], \
+                       L.hi[1], col0, c.tile, c.march, L.cmir, gx, tiles, c.order)
         if (c.vec == 2)
-            JCOLS_LAUNCH(2);
+            WITH_NT(JCOLS_LAUNCH, 2);
         else
-            JCOLS_LAUNCH(1);
+            WITH_NT(JCOLS_LAUNCH, 1);
 #undef JCOLS_LAUNCH
         return hipGetLastError();
     }
     // the mirror-free form for launches of at least 2^22 cells without mirrors
     const bool lean = L.mir.n == 0 && nrows * (L.hi[1] - L.lo[1]) >= ((int64_t)1 << 22);
-    if (c.vec == 2) {
-        if (lean)
-            JACOBI_LAUNCH(2, 0);
-        else
-            JACOBI_LAUNCH(2, 1);
-    } else {
-        if (lean)
-            JACOBI_LAUNCH(1, 0);
-        else
-            JACOBI_LAUNCH(1, 1);
+#define JACOBI_LEAN(V)                    \
+    do {                                  \
+        if (lean)                         \
+            WITH_NT(JACOBI_LAUNCH, V, 0); \
+        else                              \
+            WITH_NT(JACOBI_LAUNCH, V, 1); \
+    } while (0)
+    switch (width_of(L)) {
+        case 1: JACOBI_LEAN(1); break;
+        case 2: JACOBI_LEAN(2); break;
+        default: JACOBI_LEAN(3); break;
     }
+#undef JACOBI_LEAN
 #undef JACOBI_LAUNCH
     return hipGetLastError();
 }
@@ -844,7 +903,7 @@ hipError_t launch_heat3d(const Launch &L, hipStream_t s) {
     dim3 block(c.bx, c.by);
     const dim3 g3 = heat_grid(L, col0);
     const int64_t gx = g3.x, gy = g3.y;
-    dim3 grid((unsigned)((int64_t)g3.x * g3.y * g3.z));
+    const dim3 grid(grid_of((int64_t)g3.x * g3.y * g3.z, c.order));
     const double *in = (const double *)L.a[0].ptr;
     double *out = (double *)L.a[1].ptr;
     const double alpha = L.scalars[0];
@@ -853,29 +912,30 @@ hipError_t launch_heat3d(const Launch &L, hipStream_t s) {
     const int64_t own_lo = filtered ? L.own_lo : INT64_MIN, own_hi = filtered ? L.own_hi : INT64_MAX;
 #define HEAT_ARGS                                                                                                    \
     in, out, ny, nx, L.lo[0], L.hi[0], L.lo[1], L.hi[1], L.lo[2], L.hi[2], col0, c.tile, c.march, alpha,             \
-        L.wg_partials, L.mir, gx, gy, c.order, own_lo, own_hi
-#define HEAT_LAUNCH(V, R)                                                                    \
-    do {                                                                                     \
-        if (res)                                                                             \
-            hipLaunchKernelGGL((heat3d_kernel<V, R, true, 1>), grid, block, 0, s, HEAT_ARGS);  \
-        else                                                                                 \
-            hipLaunchKernelGGL((heat3d_kernel<V, R, false, 1>), grid, block, 0, s, HEAT_ARGS); \
+        L.wg_partials, L.mir, gx, gy, (int64_t)g3.z, c.order, own_lo, own_hi
+    const bool nt = !cache_resident(L);
+#define HEAT_LAUNCH(V, R, N)                                                                    \
+    do {                                                                                        \
+        if (res)                                                                                \
+            hipLaunchKernelGGL((heat3d_kernel<V, R, true, 1, N>), grid, block, 0, s, HEAT_ARGS);  \
+        else                                                                                    \
+            hipLaunchKernelGGL((heat3d_kernel<V, R, false, 1, N>), grid, block, 0, s, HEAT_ARGS); \
     } while (0)
-    if (c.vec == 2) {
-        switch (c.rows) {
-            case 1: HEAT_LAUNCH(2, 1); break;
-            case 2: HEAT_LAUNCH(2, 2); break;
-            case 4: HEAT_LAUNCH(2, 4); break;
-            default: HEAT_LAUNCH(2, 8); break;
-        }
-    } else {
-        switch (c.rows) {
-            case 1: HEAT_LAUNCH(1, 1); break;
-            case 2: HEAT_LAUNCH(1, 2); break;
-            case 4: HEAT_LAUNCH(1, 4); break;
-            default: HEAT_LAUNCH(1, 8); break;
-        }
+#define HEAT_ROWS(V)                               \
+    do {                                           \
+        switch (c.rows) {                          \
+            case 1: HEAT_LAUNCH(V, 1, true); break;  \
+            case 2: WITH_NT(HEAT_LAUNCH, V, 2); break; \
+            case 4: WITH_NT(HEAT_LAUNCH, V, 4); break; \
+            default: HEAT_LAUNCH(V, 8, true); break; \
+        }                                          \
+    } while (0)
+    switch (width_of(L)) {
+        case 1: HEAT_ROWS(1); break;
+        case 2: HEAT_ROWS(2); break;
+        default: HEAT_ROWS(3); break;
     }
+#undef HEAT_ROWS
 #undef HEAT_LAUNCH
 #undef HEAT_ARGS
     return hipGetLastError();
@@ -919,12 +979,15 @@ static hipError_t launch_col_parts(const Launch *L, int n, hipStream_t s) {
     if (pk.n == 0) return hipSuccess;
     if (begin > (int64_t)INT32_MAX) return hipErrorInvalidValue;
     const dim3 grid((unsigned)begin), block(c.bx, c.by);
+    const bool nt = !cache_resident(L0);
+#define COLPARTS_LAUNCH(V, N)                                                                                   \
+    hipLaunchKernelGGL((jacobi2d_colparts_kernel<V, N>), grid, block, 0, s, pk, L0.ext[1], L0.lo[0], L0.hi[0], \
+                       c.tile, c.march, c.order)
     if (c.vec == 2)
-        hipLaunchKernelGGL((jacobi2d_colparts_kernel<2>), grid, block, 0, s, pk, L0.ext[1], L0.lo[0], L0.hi[0], c.tile,
-                           c.march, c.order);
+        WITH_NT(COLPARTS_LAUNCH, 2);
     else
-        hipLaunchKernelGGL((jacobi2d_colparts_kernel<1>), grid, block, 0, s, pk, L0.ext[1], L0.lo[0], L0.hi[0], c.tile,
-                           c.march, c.order);
+        WITH_NT(COLPARTS_LAUNCH, 1);
+#undef COLPARTS_LAUNCH
     return hipGetLastError();
 }
 
@@ -980,41 +1043,43 @@ hipError_t launch_parts(const Launch *L, int n, double *wg_partials, int64_t wg_
     if (partial > wg_capacity || begin > (int64_t)INT32_MAX) return hipErrorInvalidValue;
     if (pk.n > 0) {
         const dim3 grid((unsigned)begin), block(c.bx, c.by);
+        const bool nt = !cache_resident(L0);
         if (!heat) {
-#define JPARTS_LAUNCH(V, M)                                                                                   \
-    hipLaunchKernelGGL((jacobi2d_parts_kernel<V, M>), grid, block, 0, s, pk, L0.ext[1], L0.lo[1], L0.hi[1], col0, \
+#define JPARTS_LAUNCH(V, M, N)                                                                                \
+    hipLaunchKernelGGL((jacobi2d_parts_kernel<V, M, N>), grid, block, 0, s, pk, L0.ext[1], L0.lo[1], L0.hi[1], col0, \
                        c.tile, c.march, gx, c.order)
-            if (c.vec == 2)
-                JPARTS_LAUNCH(2, 2);
-            else
-                JPARTS_LAUNCH(1, 2);
+            switch (width_of(L0)) {
+                case 1: WITH_NT(JPARTS_LAUNCH, 1, 2); break;
+                case 2: WITH_NT(JPARTS_LAUNCH, 2, 2); break;
+                default: WITH_NT(JPARTS_LAUNCH, 3, 2); break;
+            }
 #undef JPARTS_LAUNCH
         } else {
 #define PARTS_ARGS                                                                                                \
     pk, L0.ext[1], L0.ext[2], L0.lo[1], L0.hi[1], L0.lo[2], L0.hi[2], col0, c.tile, c.march, L0.scalars[0], \
         wg_partials, gx, gy, c.order
-#define PARTS_LAUNCH(V, R)                                                                             \
-    do {                                                                                               \
-        if (res)                                                                                       \
-            hipLaunchKernelGGL((heat3d_parts_kernel<V, R, true, 2>), grid, block, 0, s, PARTS_ARGS);  \
-        else                                                                                           \
-            hipLaunchKernelGGL((heat3d_parts_kernel<V, R, false, 2>), grid, block, 0, s, PARTS_ARGS); \
+#define PARTS_LAUNCH(V, R, N)                                                                             \
+    do {                                                                                                  \
+        if (res)                                                                                          \
+            hipLaunchKernelGGL((heat3d_parts_kernel<V, R, true, 2, N>), grid, block, 0, s, PARTS_ARGS);  \
+        else                                                                                              \
+            hipLaunchKernelGGL((heat3d_parts_kernel<V, R, false, 2, N>), grid, block, 0, s, PARTS_ARGS); \
     } while (0)
-            if (c.vec == 2) {
-                switch (c.rows) {
-                    case 1: PARTS_LAUNCH(2, 1); break;
-                    case 2: PARTS_LAUNCH(2, 2); break;
-                    case 4: PARTS_LAUNCH(2, 4); break;
-                    default: PARTS_LAUNCH(2, 8); break;
-                }
-            } else {
-                switch (c.rows) {
-                    case 1: PARTS_LAUNCH(1, 1); break;
-                    case 2: PARTS_LAUNCH(1, 2); break;
-                    case 4: PARTS_LAUNCH(1, 4); break;
-                    default: PARTS_LAUNCH(1, 8); break;
-                }
+#define PARTS_ROWS(V)                         \
+    do {                                      \
+        switch (c.rows) {                     \
+            case 1: PARTS_LAUNCH(V, 1, true); break;  \
+            case 2: WITH_NT(PARTS_LAUNCH, V, 2); break; \
+            case 4: WITH_NT(PARTS_LAUNCH, V, 4); break; \
+            default: PARTS_LAUNCH(V, 8, true); break; \
+        }                                     \
+    } while (0)
+            switch (width_of(L0)) {
+                case 1: PARTS_ROWS(1); break;
+                case 2: PARTS_ROWS(2); break;
+                default: PARTS_ROWS(3); break;
             }
+#undef PARTS_ROWS
 #undef PARTS_LAUNCH
 #undef PARTS_ARGS
         }
@@ -1027,7 +1092,7 @@ hipError_t launch_parts(const Launch *L, int n, double *wg_partials, int64_t wg_
 bool make_task(const Launch &L, PTask *t) {
     *t = PTask{};
     t->kind = L.kind;
-    t->vec = L.cfg.vec;
+    t->vec = width_of(L);
     t->tile = L.cfg.tile;
     t->march = L.cfg.march;
     t->in = (const double *)L.a[0].ptr;
@@ -1037,22 +1102,27 @@ bool make_task(const Launch &L, PTask *t) {
         t->lo[d] = L.lo[d];
         t->hi[d] = L.hi[d];
     }
-    const int64_t w = (int64_t)kPersistentThreads * t->vec;
+    // as many threads along a row as it needs, a whole number of waves (a 3-D
+    // field of 64-wide rows in tiles of 256 along a row used 31 of 256 lanes)
+    const int inner = L.kind == JACC_LOOP_HEAT3D ? 2 : 1;
+    const int64_t lanes = cdiv(L.hi[inner] - col_start(L.lo[inner], L.cfg.vec), L.cfg.vec);
+    t->bx = lanes <= 64 ? 64 : lanes <= 128 ? 128 : kPersistentThreads;
+    const int64_t w = (int64_t)t->bx * L.cfg.vec, by = kPersistentThreads / t->bx;
     if (L.kind == JACC_LOOP_JACOBI2D) {
         t->e1 = L.ext[1];
-        t->col0 = col_start(L.lo[1], t->vec);
+        t->col0 = col_start(L.lo[1], L.cfg.vec);
         if (L.hi[0] <= L.lo[0] || L.hi[1] <= L.lo[1]) return true;
         t->gx = cdiv(L.hi[1] - t->col0, w);
-        t->gy = cdiv(L.hi[0] - L.lo[0], t->tile);
+        t->gy = cdiv(L.hi[0] - L.lo[0], by * t->tile);
         t->gz = 1;
     } else if (L.kind == JACC_LOOP_HEAT3D) {
         t->e1 = L.ext[1];
         t->e2 = L.ext[2];
         t->alpha = L.scalars[0];
-        t->col0 = col_start(L.lo[2], t->vec);
+        t->col0 = col_start(L.lo[2], L.cfg.vec);
         if (heat_empty(L)) return true;
         t->gx = cdiv(L.hi[2] - t->col0, w);
-        t->gy = L.hi[1] - L.lo[1];
+        t->gy = cdiv(L.hi[1] - L.lo[1], by);
         t->gz = cdiv(L.hi[0] - L.lo[0], t->tile);
     } else {
         return false;
@@ -1070,15 +1140,17 @@ int64_t persistent_grid(int64_t tiles, bool /*jacobi_only*/) {
     return tiles < max_grid ? tiles : max_grid;
 }
 
-hipError_t launch_persistent(const PTask *tasks, int ntasks, int64_t tiles, int64_t grid, bool jacobi_only,
+hipError_t launch_persistent(const PTask *tasks, int ntasks, int64_t tiles, int64_t grid, bool jacobi_only, bool nt,
                              hipStream_t s) {
     if (ntasks <= 0 || tiles <= 0 || grid <= 0) return hipSuccess;
+#define PERSISTENT_LAUNCH(J, N)                                                                                     \
+    hipLaunchKernelGGL((persistent_kernel<J, N>), dim3((unsigned)grid), dim3(kPersistentThreads), 0, s, tasks, ntasks, \
+                       tiles)
     if (jacobi_only)
-        hipLaunchKernelGGL(persistent_kernel<true>, dim3((unsigned)grid), dim3(kPersistentThreads), 0, s, tasks, ntasks,
-                           tiles);
+        WITH_NT(PERSISTENT_LAUNCH, true);
     else
-        hipLaunchKernelGGL(persistent_kernel<false>, dim3((unsigned)grid), dim3(kPersistentThreads), 0, s, tasks,
-                           ntasks, tiles);
+        WITH_NT(PERSISTENT_LAUNCH, false);
+#undef PERSISTENT_LAUNCH
     return hipGetLastError();
 }
 

@@ -21,6 +21,7 @@ struct Arg {
 
 struct Cfg {
     int bx, by, tile, vec, persistent, order, march, rows;
+    int odd;  // set with vec = 2 by the defaults: pairs in rows of odd length (a caller's own vec = 2 there is refused)
 };
 
 // Write-through targets of a stencil launch: rows [lo, hi) of dim 0 that the
@@ -78,6 +79,22 @@ hipError_t launch_loop(const Launch &L, hipStream_t s);
 // Checks a configuration for a loop without launching; returns 0 if legal.
 int check_config(const Launch &L);
 
+// Bytes of a stencil's two arrays up to which they are taken to live in the
+// 256 MB memory-side cache from one sweep to the next: their outputs are then
+// stored normally instead of non-temporally, and their tiles walked XCD-aware.
+// Measured (us a sweep, non-temporal row-major / normal XCD-aware): Jacobi
+// 2048^2 16.2 / 11.9, 4099x3001 40.1 / 30.1, 5000^2 69.0 / 73.7; heat 128^3
+// 10.0 / 9.1, 256^3 (268 MB) 51 / 43, 301x303x305 (445 MB) 105 / 114.
+constexpr int64_t kCacheBytes = 288 << 20;
+constexpr int64_t kWgCapacity = 1 << 16;  // workgroup partials a stream's reduction holds
+inline int64_t array_bytes(const Launch &L) {
+    int64_t n = 8;
+    for (int i = 0; i < 4; ++i)
+        if (L.ext[i] > 0) n *= L.ext[i];
+    return n;
+}
+inline bool cache_resident(const Launch &L) { return 2 * array_bytes(L) <= kCacheBytes; }
+
 // Fills in defaults for zero fields of a configuration.
 Cfg default_config(int kind, const Launch &L, Cfg c);
 
@@ -91,10 +108,11 @@ struct CombineList {
 hipError_t launch_combine(const double *partials, const CombineList &list, double *out, hipStream_t s);
 
 // One loop of a persistent task group: a stencil sweep cut into tiles of
-// 256 threads (256*vec columns x `tile` rows, or x 1 row x `tile` planes).
+// 256 threads, bx along a row and 256/bx row groups (2-D: of `tile` rows each;
+// 3-D: of one row each through `tile` planes).
 struct PTask {
     int32_t kind;  // JACC_LOOP_JACOBI2D or JACC_LOOP_HEAT3D
-    int32_t vec, tile, march;
+    int32_t vec, tile, march, bx;
     const double *in;
     double *out;
     int64_t e1, e2;  // extents of dims 1 and 2 (2-D: e1 = row length)
@@ -116,8 +134,9 @@ int64_t persistent_grid(int64_t tiles, bool jacobi_only);
 
 // Launches the persistent kernel with `grid` workgroups over `ntasks` device
 // task records whose tiles total `tiles` (jacobi_only: every task is a
-// Jacobi sweep, which selects the variant without the heat bodies).
-hipError_t launch_persistent(const PTask *tasks, int ntasks, int64_t tiles, int64_t grid, bool jacobi_only,
+// Jacobi sweep, which selects the variant without the heat bodies; nt: with
+// non-temporal stores, for tasks that together exceed kCacheBytes).
+hipError_t launch_persistent(const PTask *tasks, int ntasks, int64_t tiles, int64_t grid, bool jacobi_only, bool nt,
                              hipStream_t s);
 
 // The partitions of one eager stencil (or SUM) loop in one launch ("packed"): the

@@ -90,7 +90,7 @@ extern "C" int jacc_heat3d_noalloc(const double *u_in, double *u_out, int64_t nz
     L.a[1] = {u_out, 0, nz, ny * nx};
     L.scalars[0] = alpha;
     L.part_rows = L.hi[0] - L.lo[0];
-    L.cfg = jk::default_config(JACC_LOOP_HEAT3D, L, jk::Cfg{0, 0, 0, 0, 0, 0, 0, 0});
+    L.cfg = jk::default_config(JACC_LOOP_HEAT3D, L, jk::Cfg{});
     if (jk::check_config(L) != 0) return fail(JACC_ERR_INVALID, "no valid launch for these extents");
     const int64_t wgs = jk::heat3d_workgroups(L);
     if (wgs > INT32_MAX) return fail(JACC_ERR_RANGE, "grid needs more workgroups than one launch takes");

@@ -37,7 +37,7 @@ namespace {
 constexpr int kMaxK = 64;
 constexpr int kSlots = 4096;
 constexpr int kEventRing = 16;
-constexpr int64_t kWgCapacity = 1 << 16;  // workgroup partials per stream
+using jk::kWgCapacity;
 constexpr int kTaskCapacity = 4096;       // persistent tasks per batch
 constexpr int64_t kBinnedMinCols = 1 << 20;  // SpMV x length from which the binned form is the default
 
@@ -881,19 +881,23 @@ int flush_group(jacc_ctx *c) {
         int rc = hazard(c, a.A, a.p, a.r, a.write, s);
         if (rc) return rc;
     }
-    int64_t tiles = 0;
+    int64_t tiles = 0, bytes = 0;
     bool jacobi_only = true;
     for (auto &t : c->ptasks) {
         t.tile_begin = tiles;
         tiles += t.ntiles;
         jacobi_only = jacobi_only && t.kind == JACC_LOOP_JACOBI2D;
+        int64_t cells = 1;
+        for (int d = 0; d < (t.kind == JACC_LOOP_JACOBI2D ? 2 : 3); ++d) cells *= t.hi[d] - t.lo[d];
+        bytes += 16 * cells;
     }
     if (live(c)) {
         const int64_t grid = jk::persistent_grid(tiles, jacobi_only);
         // the table is written to pinned memory now and uploaded once when
         // the batch closes, before the graph first runs
         std::memcpy(B->host_tasks + B->tasks_used, c->ptasks.data(), (size_t)n * sizeof(jk::PTask));
-        HIPCHK(c, jk::launch_persistent(B->dev_tasks + B->tasks_used, n, tiles, grid, jacobi_only, c->st[s].s),
+        HIPCHK(c, jk::launch_persistent(B->dev_tasks + B->tasks_used, n, tiles, grid, jacobi_only,
+                                        bytes > jk::kCacheBytes, c->st[s].s),
                "persistent kernel launch");
     }
     B->tasks_used += n;
@@ -1146,12 +1150,12 @@ int prepare_loop(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const j
                 }
         }
     }
-    jk::Cfg cf{0, 0, 0, 0, 0, 0, 0, 0};
+    jk::Cfg cf{};
     L.part_rows = 0;
     for (const PartPlan &pp : plan)
         L.part_rows = std::max(L.part_rows, pd == 0 ? pp.iters.hi - pp.iters.lo
                                                     : (pp.iters.empty() ? 0 : b->hi[0] - b->lo[0]));
-    if (cfg) cf = {cfg->bx, cfg->by, cfg->tile, cfg->vec, cfg->persistent, cfg->order, cfg->march, cfg->rows};
+    if (cfg) cf = {cfg->bx, cfg->by, cfg->tile, cfg->vec, cfg->persistent, cfg->order, cfg->march, cfg->rows, 0};
     if (pd != 0 && cf.persistent)
         return set_err(c, JACC_ERR_UNSUPPORTED, "persistent execution of arrays split along dimension 1");
     const bool own_tile = cf.tile != 0;

@@ -43,6 +43,72 @@ def test_jacobi_ragged_shapes_partitions_configs(shape, K, cfg):
     assert np.array_equal(out, ref)
 
 
+@pytest.mark.parametrize("shape,K,part_dim,persistent", [
+    ((9, 3), 1, 0, 0),            # one interior column: the pair's second element is the row's end
+    ((40, 127), 1, 0, 0), ((40, 129), 3, 0, 0), ((40, 131), 1, 0, 0),  # the last column in lane 63, 0 and 1
+    ((67, 1025), 2, 0, 0), ((70, 4095), 8, 0, 0),
+    ((33, 515), 3, 1, 0), ((50, 129), 2, 1, 0),  # column slabs of odd width have an even pitch
+    ((66, 63), 1, 0, 1), ((40, 129), 3, 0, 1), ((70, 513), 2, 0, 1),  # task tiles of 64, 128 and 256 threads
+    ((70, 262), 2, 0, 1),
+    ((63, 63), 1, 0, 0), ((64, 64), 1, 0, 0),    # either side of 4096 cells
+    ((513, 2049), 1, 0, 0), ((1024, 4099), 2, 0, 0),  # the default's tiles of 4 and 8 rows
+    ((4339, 4351), 1, 0, 0), ((4346, 4353), 2, 0, 0), ((2310, 8190), 1, 0, 0),  # either side of 288 MB for both arrays
+])
+def test_jacobi_default_shapes_bit_exact(shape, K, part_dim, persistent):
+    say(f"jacobi defaults {shape} K={K} part_dim={part_dim} persistent={persistent}")
+    u0 = inputs.jacobi_grid(*shape, seed=13)
+    u0[:, 0] = 0.25
+    u0[:, -1] = -0.5
+    T = 5 if u0.size < 1 << 20 else 2
+    ref = oracle.jacobi2d_mt(u0, T)
+    if not persistent:
+        assert_same(run_jacobi(u0, T, K, part_dim=part_dim), ref)
+        return
+    a, b = u0.copy(), u0.copy()
+    with context(K) as c:
+        c.enter(a, halo=(1, 1))
+        c.enter(b, halo=(1, 1))
+        c.batch_begin()
+        src, dst = a, b
+        for _ in range(T):
+            c.jacobi2d(src, dst, cfg=jacc.config(persistent=1))
+            src, dst = dst, src
+        c.batch_destroy(c.batch_end())  # which runs it once
+        c.exit(b, jacc.COPYOUT)
+        c.exit(a, jacc.COPYOUT)
+    assert_same(src, ref)
+
+
+@pytest.mark.parametrize("shape,K", [
+    ((5, 7, 3), 1), ((9, 10, 127), 2), ((9, 11, 129), 3), ((7, 9, 131), 1),  # odd rows about a wave's 128 columns
+    ((60, 60, 145), 1), ((80, 81, 82), 1), ((80, 81, 83), 3), ((162, 161, 163), 2),  # the small, middle and split shapes
+    ((40, 1200, 398), 1), ((40, 1200, 399), 2), ((60, 700, 497), 1),  # beyond 288 MB: a row held by 256x1 threads
+    ((60, 700, 511), 1), ((100, 1000, 201), 2), ((33, 900, 701), 1),
+    ((2056, 2040, 3), 1), ((2056, 2040, 9), 1),  # thin fields: more small tiles than partial sums are held
+])
+def test_heat_default_shapes_bit_exact(shape, K):
+    say(f"heat defaults {shape} K={K}")
+    u0 = inputs.heat_field(*shape, seed=17)
+    T = 3 if u0.size < 1 << 20 else 2
+    ref, want = oracle.heat3d_mt(u0, T, 0.1)
+    out, res = run_heat(u0, T, 0.1, K)
+    assert_same(out, ref)
+    # sums of n non-negative squares in different orders: n eps of each other
+    assert np.all(np.abs(np.array(res) - want) <= u0.size * np.finfo(np.float64).eps * np.array(want))
+
+
+@pytest.mark.parametrize("shape", [(20, 31), (9, 10, 131)])
+def test_own_pairs_on_odd_rows_stay_refused(shape):
+    say(f"vec=2 on {shape}")
+    a = np.zeros(shape)
+    b = np.zeros(shape)
+    with context(1) as c:
+        c.enter(a, halo=(1, 1))
+        c.enter(b, halo=(1, 1))
+        with pytest.raises(jacc.JaccError):
+            c.jacobi2d(a, b, cfg=jacc.config(vec=2)) if len(shape) == 2 else c.heat3d(a, b, 0.1, cfg=jacc.config(vec=2))
+
+
 def test_jacobi_constant_and_linear_fields_exact_on_device():
     say("jacobi fixed points")
     c = np.full((66, 70), 0.3)
