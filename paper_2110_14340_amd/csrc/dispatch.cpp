@@ -204,7 +204,7 @@ hipError_t launch_loop(const Launch &L, hipStream_t s) {
         case JACC_LOOP_HEAT3D: {
             hipError_t e = launch_heat3d(L, s);
             if (e != hipSuccess || !L.wg_partials) return e;
-            return launch_finalise(L.wg_partials, heat3d_workgroups(L), L.part_out, s);
+            return launch_result(L, heat3d_workgroups(L), s);
         }
         case JACC_LOOP_SUM: return launch_sum(L, s);
         case JACC_LOOP_GEMM: return launch_gemm(L, s);

@@ -23,11 +23,31 @@ __device__ __forceinline__ void load_vec(const double *p, double (&v)[VEC]) {
     }
 }
 
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, true);
+    return __hiloint2double(hi, lo);
+}
+
+// Sum over each aligned group of G lanes by the butterfly xor 1, 2, 4, 8.  Once
+// the lanes of a quad hold the same value, mirroring 8 lanes reaches the
+// same value as xor 4 does, and mirroring 16 as xor 8.
+template <int G>
+__device__ __forceinline__ double group_sum(double s) {
+    s += dpp<0xB1>(s);                          // quad_perm 1 0 3 2
+    s += dpp<0x4E>(s);                          // quad_perm 2 3 0 1
+    if constexpr (G >= 8) s += dpp<0x141>(s);   // row_half_mirror
+    if constexpr (G >= 16) s += dpp<0x140>(s);  // row_mirror
+    return s;
+}
+
 // Sum of `v` over the 64 lanes of a wave by a fixed butterfly (xor 1, 2, 4,
 // ..., 32); every lane ends with the same value.
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int m = 1; m < kWave; m <<= 1) v += __shfl_xor(v, m, kWave);
+    v = group_sum<16>(v);
+    v += __shfl_xor(v, 16, kWave);
+    v += __shfl_xor(v, 32, kWave);
     return v;
 }
 

@@ -15,25 +15,6 @@ namespace {
 constexpr int kSpmvThreads = 256;
 
 // v of another lane of its row of 16 lanes, by a DPP pattern.
-template <int CTRL>
-__device__ __forceinline__ double dpp(double v) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, true);
-    return __hiloint2double(hi, lo);
-}
-
-// Sum over each aligned group of G lanes by the butterfly xor 1, 2, 4, 8.  Once
-// the lanes of a quad hold the same value, mirroring 8 lanes reaches the
-// same value as xor 4 does, and mirroring 16 as xor 8.
-template <int G>
-__device__ __forceinline__ double group_sum(double s) {
-    s += dpp<0xB1>(s);                          // quad_perm 1 0 3 2
-    s += dpp<0x4E>(s);                          // quad_perm 2 3 0 1
-    if constexpr (G >= 8) s += dpp<0x141>(s);   // row_half_mirror
-    if constexpr (G >= 16) s += dpp<0x140>(s);  // row_mirror
-    return s;
-}
-
 template <int G, bool NT>
 __global__ void __launch_bounds__(kSpmvThreads)
 spmv_kernel(const int32_t *__restrict__ rp, const int32_t *__restrict__ col, const double *__restrict__ val,

@@ -1086,7 +1086,9 @@ hipError_t launch_parts(const Launch *L, int n, double *wg_partials, int64_t wg_
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    return res ? launch_finalise_many(wg_partials, seg, s) : hipSuccess;
+    if (!res) return hipSuccess;
+    return L0.total ? launch_total(wg_partials, seg, L0.ticket, L0.total, L0.total_host, s)
+                    : launch_finalise_many(wg_partials, seg, s);
 }
 
 bool make_task(const Launch &L, PTask *t) {

@@ -68,6 +68,10 @@ struct Launch {
     double *wg_partials;
     int64_t wg_capacity;
     double *part_out;
+    // set when the loop's partitions are all in this launch (or pack): the sum
+    // over them, written by the finaliser; `total_host`, pinned, may be null
+    double *total, *total_host;
+    unsigned *ticket;  // for packed launches: zero, and zero again when the finaliser ends
     int64_t part_rows;  // iterations along dim 0 of the largest partition (for defaults)
 };
 
@@ -105,7 +109,7 @@ struct CombineList {
     int n;
     int idx[64];
 };
-hipError_t launch_combine(const double *partials, const CombineList &list, double *out, hipStream_t s);
+hipError_t launch_combine(const double *partials, const CombineList &list, double *out, double *host, hipStream_t s);
 
 // One loop of a persistent task group: a stencil sweep cut into tiles of
 // 256 threads, bx along a row and 256/bx row groups (2-D: of `tile` rows each;
@@ -161,6 +165,11 @@ struct Segments {
     int32_t count;
 };
 hipError_t launch_finalise_many(const double *base, const Segments &seg, hipStream_t s);
+// Finaliser and combine in one launch: *total (and *host, unless null) = the
+// segments' ordered sums added in segment order.  Each segment's sum also goes
+// to its `out`, and `ticket` is used, when there are several.
+hipError_t launch_total(const double *base, const Segments &seg, unsigned *ticket, double *total, double *host,
+                        hipStream_t s);
 // The partitions of one SUM loop in one launch, then their finalisers (the
 // same bits as a launch per partition).
 hipError_t launch_sum_parts(const Launch *L, int n, double *wg_partials, int64_t wg_capacity, hipStream_t s);
@@ -176,6 +185,9 @@ int64_t heat3d_workgroups(const Launch &L);
 hipError_t launch_sum(const Launch &L, hipStream_t s);
 int64_t sum_workgroups(const Launch &L);
 hipError_t launch_finalise(const double *partials, int64_t n, double *out, hipStream_t s);
+// The sum of one launch's n workgroup partials: to L.total when that is set,
+// else to L.part_out.
+hipError_t launch_result(const Launch &L, int64_t n, hipStream_t s);
 hipError_t launch_gemm(const Launch &L, hipStream_t s);
 hipError_t launch_spmv(const Launch &L, hipStream_t s);
 

@@ -358,8 +358,10 @@ struct jacc_ctx {
     uintptr_t fake_next = (uintptr_t)1 << 44;
     // reductions (buffers indexed by stream)
     double *slots = nullptr;             // kSlots doubles
+    double *host_total = nullptr;        // pinned: the last synchronous reduction's result
     double *partials = nullptr;          // kSlots * kMaxK doubles: per slot, one per partition
     double *wg = nullptr;                // streams * kWgCapacity doubles
+    unsigned *tickets = nullptr;         // one per stream, zero between its launches
     std::vector<SeqRef> partial_reader;  // last combine that read partials[slot][p]
     std::vector<SeqRef> slot_src;        // op that produced each slot
     // batches
@@ -1427,6 +1429,18 @@ int loop_impl(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const jacc
     const int red_slot = slot >= 0 ? slot : kSlots - 1;  // a synchronous-only reduction uses the last slot
     std::vector<int> order;       // partitions that reduce, in partition order
     std::vector<int> red_streams;  // their streams
+    // Partitions that share one launch (or are one) have their sums added by
+    // the launch's finaliser: no combine kernel follows.
+    bool combined = false;
+    auto combine_in_launch = [&](jk::Launch &first, int s) -> int {
+        const int e = ensure_wait(c, s, c->slot_src[red_slot].s, c->slot_src[red_slot].seq);  // earlier writer of the slot
+        if (e) return e;
+        first.total = c->slots + red_slot;
+        first.total_host = red_host ? c->host_total : nullptr;
+        first.ticket = c->tickets + s;
+        combined = true;
+        return JACC_OK;
+    };
     // pieces: one per partition, or (split mode) first every partition's
     // rows whose reads stay inside its own block, then the edge rows that
     // read a neighbour's rows
@@ -1578,6 +1592,10 @@ int loop_impl(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const jacc
             }
             lps.push_back(LP);
         }
+        if (want_red && !lps.empty()) {
+            rc = combine_in_launch(lps[0], s);
+            if (rc) return rc;
+        }
         if (inject_fault(c, 2)) {
             c->status = JACC_ERR_DEVICE;
             return set_err(c, JACC_ERR_DEVICE, "injected fault in launch %lld", (long long)c->fault_count);
@@ -1697,6 +1715,10 @@ int loop_impl(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const jacc
                                (long long)kWgCapacity);
             order.push_back(p);
             red_streams.push_back(s);
+            if (K == 1) {
+                rc = combine_in_launch(LP, s);
+                if (rc) return rc;
+            }
         }
         if (inject_fault(c, 2)) {
             c->status = JACC_ERR_DEVICE;
@@ -1784,11 +1806,12 @@ int loop_impl(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const jacc
         const int sl = red_slot;
         rc = ensure_wait(c, s0, c->slot_src[sl].s, c->slot_src[sl].seq);  // earlier writer of the slot
         if (rc) return rc;
-        if (live(c)) {
+        if (live(c) && !combined) {
             jk::CombineList cl{};
             cl.n = (int)order.size();
             for (size_t k = 0; k < order.size(); ++k) cl.idx[k] = order[k];
-            HIPCHK(c, jk::launch_combine(c->partials + (size_t)sl * kMaxK, cl, c->slots + sl, c->st[s0].s),
+            HIPCHK(c, jk::launch_combine(c->partials + (size_t)sl * kMaxK, cl, c->slots + sl,
+                                          red_host ? c->host_total : nullptr, c->st[s0].s),
                    "combine launch");
         }
         c->st[s0].seq++;
@@ -1800,10 +1823,7 @@ int loop_impl(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const jacc
         if (red_host) {
             rc = sync_stream(c, s0);
             if (rc) return rc;
-            if (live(c))
-                HIPCHK(c, hipMemcpy(red_host, c->slots + sl, sizeof(double), hipMemcpyDeviceToHost), "hipMemcpy(D2H)");
-            else
-                *red_host = 0.0;
+            *red_host = live(c) ? *(volatile double *)c->host_total : 0.0;
         }
     }
     if (note && note->e1) HIPCHK(c, hipEventRecord(note->e1, c->st[stream_for(0)].s), "hipEventRecord");
@@ -2084,10 +2104,13 @@ int jacc_init(jacc_ctx **out, int K, void *const *streams, const jacc_allocator 
         if (!rc) rc = dev_alloc(c, kSlots * sizeof(double), (void **)&c->slots);
         if (!rc) rc = dev_alloc(c, (size_t)kSlots * kMaxK * sizeof(double), (void **)&c->partials);
         if (!rc) rc = dev_alloc(c, (size_t)ns * kWgCapacity * sizeof(double), (void **)&c->wg);
+        if (!rc) rc = dev_alloc(c, ns * sizeof(unsigned), (void **)&c->tickets);
         if (!rc && !c->dry) {
-            hipError_t e = hipMemset(c->slots, 0, kSlots * sizeof(double));
+            hipError_t e = hipHostMalloc((void **)&c->host_total, sizeof(double), hipHostMallocCoherent);
+            if (e == hipSuccess) e = hipMemset(c->slots, 0, kSlots * sizeof(double));
+            if (e == hipSuccess) e = hipMemset(c->tickets, 0, ns * sizeof(unsigned));
             if (e == hipSuccess) e = hipDeviceSynchronize();
-            if (e != hipSuccess) rc = dev_fail(c, e, "hipMemset");
+            if (e != hipSuccess) rc = dev_fail(c, e, "reduction buffers");
         }
         if (rc) {
             g_init_err = c->err;
@@ -2152,9 +2175,11 @@ int jacc_finalize(jacc_ctx *c) {
         c->batches.clear();
         for (auto &kv : c->present) free_array(c, kv.second);
         c->present.clear();
+        if (c->host_total) (void)hipHostFree(c->host_total);
         dev_free(c, c->slots);
         dev_free(c, c->partials);
         dev_free(c, c->wg);
+        dev_free(c, c->tickets);
         if (!c->dry) {
             for (auto &S : c->st) {
                 for (auto &E : S.ring)

@@ -376,3 +376,30 @@ def test_heat_residuals_packed_equal_a_launch_per_partition(shape, K):
     assert np.array_equal(packed[0], per_part[0]) and np.array_equal(packed[1], per_part[1])
     ref, ref_res = oracle.heat3d(u0, 6, 0.1)
     assert np.array_equal(packed[0], ref) and _rel_close(packed[1], ref_res)
+
+
+@pytest.mark.parametrize("K", [1, 2, 5, 16])
+def test_packed_totals_have_the_unpacked_bits(K):
+    """The finaliser that also adds the partitions against one launch per
+    partition and a combine: sums through the host copy and through slots,
+    and residuals, repeated so that its ticket is reused."""
+    say(f"packed totals K={K}")
+    x = inputs.uniform(70001, seed=3)
+    h = inputs.heat_field(40, 21, 67, seed=4)
+    got = []
+    for flags in (0, jacc.INIT_NO_PACK):
+        u, v = h.copy(), h.copy()
+        with context(K, flags) as c:
+            c.enter(x)
+            c.enter(u, halo=(1, 1))
+            c.enter(v, halo=(1, 1))
+            vals = []
+            for i in range(12):
+                s, d = (u, v) if i % 2 == 0 else (v, u)
+                c.heat3d(s, d, 0.1, slot=i)
+                vals.append(c.sum(x, squares=bool(i % 2), rows=(i, 70001 - 3 * i)))
+                c.sum(x, slot=20 + i, rows=(0, 1000 * i), sync=False)
+            vals.append(c.sum(x, rows=(5, 5)))  # no rows
+            vals += list(c.reductions(0, 12)) + list(c.reductions(20, 12))
+        got.append(np.array(vals))
+    assert np.array_equal(got[0], got[1])
