@@ -397,7 +397,9 @@ const char *jacc_last_error(const jacc_ctx *ctx);
  * configuration has persistent = 1 are not launched one by one: they gather
  * into one persistent-kernel launch that walks a task table of all their
  * tiles, launched when a later loop touches one of their arrays or the
- * batch ends (loops on other arrays are recorded ahead of it).  No
+ * batch ends (loops on other arrays are recorded ahead of it).  Jacobi loops
+ * that step back and forth between two arrays count one group each, and share
+ * launches of several steps; both arrays end as the single steps leave them.  No
  * data_enter/exit, update, wait or synchronous reduction is allowed inside.
  *
  * jacc_batch_end closes the capture, instantiates the graph, runs it once

@@ -154,6 +154,25 @@ hipError_t launch_persistent(const PTask *tasks, int ntasks, int64_t tiles, int6
 // for more than kMaxPack launches or more than wg_capacity partials.
 constexpr int kMaxPack = 16;
 hipError_t launch_parts(const Launch *L, int n, double *wg_partials, int64_t wg_capacity, hipStream_t s);
+
+// `steps` (odd, at most kChainMax) Jacobi sweeps of the box [lo, hi) from the
+// `in` array to the `out` array of the partitions' slabs, which split the rows
+// [0, ny) in order; afterwards `out` holds the last sweep's result, in the rows
+// [lo, hi) of each partition and in its mirrors, as after that sweep alone.
+constexpr int kChainMax = 9;
+struct ChainPart {
+    const double *in;  // biased so that in[row * nx + column] is global (row, column)
+    double *out;
+    int64_t lo, hi;  // the rows the partition owns
+    Mirrors mir;     // of `out`
+};
+struct Chain {
+    ChainPart p[kMaxPack];
+    int32_t n;
+    int64_t ny, nx, lo[2], hi[2];
+};
+hipError_t launch_steps(const Chain &ch, int steps, hipStream_t s);
+
 // Workgroup partials a packed heat launch with a residual writes.
 int64_t parts_partials(const Launch *L, int n);
 

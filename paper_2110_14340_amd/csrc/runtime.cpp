@@ -272,6 +272,18 @@ struct PendingAccess {
     bool write;
 };
 
+// A pending persistent group that is one Jacobi loop, or several in a row that
+// step between the same two arrays: `parts`, `tasks` and `accs` of the steps
+// from `src` to `dst` (0) and back (1).
+struct StepChain {
+    int steps = 0;  // 0: the group is something else
+    Array *src = nullptr, *dst = nullptr;  // of step 0
+    jacc_bounds b{};
+    jk::Chain ch[2];
+    std::vector<jk::PTask> tasks[2];
+    std::vector<PendingAccess> accs[2];
+};
+
 struct Batch {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -370,6 +382,7 @@ struct jacc_ctx {
     std::vector<jk::PTask> ptasks;  // pending persistent group
     std::vector<PendingAccess> paccs;
     std::vector<Array *> parrays;
+    StepChain chain;
     hipEvent_t fork_ev = nullptr, t0 = nullptr, t1 = nullptr;
     // per-partition kernel timing (jacc_time_loop_parts): events around each
     // partition's launch; kev[2p] before, kev[2p+1] after
@@ -872,20 +885,19 @@ bool desc_equal(const jacc_array_desc &a, const jacc_array_desc &b) {
 // Launches the pending persistent tasks as one persistent kernel on stream 0:
 // a grid sized to the chip walks all tasks' tiles, reading the task records
 // from the batch's device table.
-int flush_group(jacc_ctx *c) {
-    if (c->ptasks.empty()) return JACC_OK;
+int launch_tasks(jacc_ctx *c, std::vector<jk::PTask> &tasks, const std::vector<PendingAccess> &accs, bool launch) {
     Batch *B = c->cur;
     const int s = 0;
-    const int n = (int)c->ptasks.size();
+    const int n = (int)tasks.size();
     if (!B || B->tasks_used + n > kTaskCapacity)
         return set_err(c, JACC_ERR_UNSUPPORTED, "more than %d persistent tasks in one batch", kTaskCapacity);
-    for (const PendingAccess &a : c->paccs) {
+    for (const PendingAccess &a : accs) {
         int rc = hazard(c, a.A, a.p, a.r, a.write, s);
         if (rc) return rc;
     }
     int64_t tiles = 0, bytes = 0;
     bool jacobi_only = true;
-    for (auto &t : c->ptasks) {
+    for (auto &t : tasks) {
         t.tile_begin = tiles;
         tiles += t.ntiles;
         jacobi_only = jacobi_only && t.kind == JACC_LOOP_JACOBI2D;
@@ -893,11 +905,11 @@ int flush_group(jacc_ctx *c) {
         for (int d = 0; d < (t.kind == JACC_LOOP_JACOBI2D ? 2 : 3); ++d) cells *= t.hi[d] - t.lo[d];
         bytes += 16 * cells;
     }
-    if (live(c)) {
+    if (live(c) && launch) {
         const int64_t grid = jk::persistent_grid(tiles, jacobi_only);
         // the table is written to pinned memory now and uploaded once when
         // the batch closes, before the graph first runs
-        std::memcpy(B->host_tasks + B->tasks_used, c->ptasks.data(), (size_t)n * sizeof(jk::PTask));
+        std::memcpy(B->host_tasks + B->tasks_used, tasks.data(), (size_t)n * sizeof(jk::PTask));
         HIPCHK(c, jk::launch_persistent(B->dev_tasks + B->tasks_used, n, tiles, grid, jacobi_only,
                                         bytes > jk::kCacheBytes, c->st[s].s),
                "persistent kernel launch");
@@ -906,9 +918,55 @@ int flush_group(jacc_ctx *c) {
     B->groups++;
     c->st[s].seq++;
     trace(c, JACC_OP_KERNEL, s, -1, -1, -1, -n, 0, tiles, c->st[s].seq);
+    return JACC_OK;
+}
+
+// Issues the first `steps` steps of the pending chain.  The last is a launch
+// of its own, so that both arrays end as the single steps leave them: its input
+// array holds the step before.  Those before it run as launches of an odd
+// number of steps each (an even number would end in the array it reads), as few
+// as kChainMax allows and of near equal length.
+int issue_chain(jacc_ctx *c, int steps) {
+    StepChain &C = c->chain;
+    const int before = steps - 1;
+    int launches = (before + jk::kChainMax - 1) / jk::kChainMax;
+    if ((before - launches) % 2) ++launches;
+    for (int l = 0, done = 0; l <= launches; ++l) {
+        const int pairs = l < launches ? (before - launches) / 2 : 0;
+        const int len = l == launches ? 1 : 1 + 2 * (pairs / launches + (l < pairs % launches ? 1 : 0));
+        for (int k = 0; k < len; ++k) {
+            const int par = (done + k) & 1;
+            int rc = launch_tasks(c, C.tasks[par], C.accs[par], len == 1);
+            if (rc) return rc;
+        }
+        if (len > 1 && live(c)) HIPCHK(c, jk::launch_steps(C.ch[done & 1], len, c->st[0].s), "chained steps launch");
+        done += len;
+    }
+    return JACC_OK;
+}
+
+int flush_group(jacc_ctx *c) {
+    if (c->ptasks.empty()) return JACC_OK;
+    int rc = c->chain.steps > 1 ? issue_chain(c, c->chain.steps) : launch_tasks(c, c->ptasks, c->paccs, true);
+    if (rc) return rc;
     c->ptasks.clear();
     c->paccs.clear();
     c->parrays.clear();
+    c->chain.steps = 0;
+    return JACC_OK;
+}
+
+// Before other loops join the pending group: issues all of a chain but its last
+// step, which stays pending like any loop.
+int end_chain(jacc_ctx *c) {
+    StepChain &C = c->chain;
+    if (C.steps > 1) {
+        int rc = issue_chain(c, C.steps - 1);
+        if (rc) return rc;
+        c->ptasks = C.tasks[(C.steps - 1) & 1];
+        c->paccs = C.accs[(C.steps - 1) & 1];
+    }
+    C.steps = 0;
     return JACC_OK;
 }
 
@@ -942,6 +1000,34 @@ struct PartPlan {
     Range iters;
     std::vector<Range> rng;  // per argument
 };
+
+// Loops that may be steps of a chain: Jacobi sweeps between two arrays split
+// alike by rows.
+bool chain_kind(int kind, const jacc_arg *args, Array **arr) {
+    if (kind != JACC_LOOP_JACOBI2D || arr[0] == arr[1] || ((args[0].mode | args[1].mode) & JACC_FILTERED)) return false;
+    for (int i = 0; i < 2; ++i)
+        if (arr[i]->pdim != 0 || arr[i]->whole || arr[i]->shared || arr[i]->K > jk::kMaxPack) return false;
+    return arr[0]->K == arr[1]->K && arr[0]->E == arr[1]->E && arr[0]->row_elems == arr[1]->row_elems;
+}
+
+// Whether a loop of that kind continues the pending chain: it reads what the
+// chain's last step writes and writes back, over the same box, and every row it
+// and the chain's launches read (those of the box and beside it, from their
+// owners) is valid where it is, so that no copy would go between the steps.
+bool chain_extends(const jacc_ctx *c, const jacc_bounds *b, Array **arr, const std::vector<PartPlan> &plan) {
+    const StepChain &C = c->chain;
+    if (C.steps < 1) return false;
+    if (arr[0] != (C.steps & 1 ? C.dst : C.src) || arr[1] != (C.steps & 1 ? C.src : C.dst)) return false;
+    for (int d = 0; d < 2; ++d)
+        if (b->lo[d] != C.b.lo[d] || b->hi[d] != C.b.hi[d]) return false;
+    for (int p = 0; p < arr[0]->K; ++p) {
+        if (!plan[p].iters.empty() && !arr[0]->valid[p].missing(plan[p].rng[0]).empty()) return false;
+        const Range own = isect(arr[0]->block(p), Range{b->lo[0] - 1, b->hi[0] + 1});
+        for (int i = 0; i < 2; ++i)
+            if (!own.empty() && !arr[i]->valid[p].missing(own).empty()) return false;
+    }
+    return true;
+}
 
 #define GUARD(c)                           \
     do {                                   \
@@ -1304,10 +1390,18 @@ int loop_impl(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const jacc
     // its arrays; loops on other arrays (persistent or not) go ahead of it,
     // so the small loops of a batch gather into few launches whatever the
     // order they are issued in
+    // a Jacobi loop that steps back over the arrays of the pending one extends it
+    const bool chains = persistent && c->cur && !dup && chain_kind(kind, args, arr);
+    const bool extends = chains && chain_extends(c, b, arr, plan);
     bool conflict = false;
     for (int i = 0; i < nargs && !conflict; ++i) conflict = pending_touches(c, arr[i]);
-    if (conflict) {
+    if (conflict && !extends) {
         rc = flush_group(c);
+        if (rc) return rc;
+    }
+    const bool starts = chains && c->ptasks.empty();
+    if (persistent && !extends && !starts) {
+        rc = end_chain(c);
         if (rc) return rc;
     }
     if (c->cur && !c->plan_only) {
@@ -1659,13 +1753,18 @@ int loop_impl(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const jacc
             jk::PTask t;
             if (!jk::make_task(LP, &t))
                 return set_err(c, JACC_ERR_UNSUPPORTED, "loop kind %d cannot run persistent", kind);
-            if (t.ntiles > 0) c->ptasks.push_back(t);
-            for (int i = 0; i < nargs; ++i) {
-                if (args[i].mode & JACC_READ) c->paccs.push_back({arr[i], p, pp.rng[i], false});
-                if (args[i].mode & JACC_WRITE) c->paccs.push_back({arr[i], p, write_span(i, pp), true});
-                c->parrays.push_back(arr[i]);
+            // a chain keeps the first step of either direction; later ones are those again
+            const bool again = extends && c->chain.steps > 1;
+            auto &tasks = extends ? c->chain.tasks[1] : c->ptasks;
+            auto &accs = extends ? c->chain.accs[1] : c->paccs;
+            if (t.ntiles > 0 && !again) tasks.push_back(t);
+            for (int i = 0; i < nargs && !again; ++i) {
+                if (args[i].mode & JACC_READ) accs.push_back({arr[i], p, pp.rng[i], false});
+                if (args[i].mode & JACC_WRITE) accs.push_back({arr[i], p, write_span(i, pp), true});
+                if (!extends) c->parrays.push_back(arr[i]);
             }
-            for (auto &m : mirrors) c->paccs.push_back({P, m.first, m.second, true});
+            if (!again)
+                for (auto &m : mirrors) accs.push_back({P, m.first, m.second, true});
             for (int i = 0; i < nargs; ++i)
                 if (args[i].mode & JACC_WRITE) {
                     if (dup)
@@ -1756,6 +1855,38 @@ int loop_impl(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const jacc
                     note_write(arr[i], p, pp.rng[i]);
             }
         note_mirrors();
+    }
+    if (extends || (starts && !c->ptasks.empty())) {
+        StepChain &C = c->chain;
+        if (extends) {
+            ++C.steps;
+        } else {
+            C.steps = 1;
+            C.src = arr[0];
+            C.dst = arr[1];
+            C.b = *b;
+            C.tasks[0] = c->ptasks;
+            C.accs[0] = c->paccs;
+            C.tasks[1].clear();
+            C.accs[1].clear();
+        }
+        if (C.steps <= 2) {
+            jk::Chain &ch = C.ch[C.steps - 1];
+            ch = jk::Chain{};
+            ch.n = K;
+            ch.ny = arr[0]->E;
+            ch.nx = arr[0]->row_elems;
+            for (int d = 0; d < 2; ++d) {
+                ch.lo[d] = b->lo[d];
+                ch.hi[d] = b->hi[d];
+            }
+            for (int p = 0; p < K; ++p) {
+                std::vector<std::pair<int, Range>> mirrors;
+                const jk::Launch LP = piece_launch(p, plan[p], mirrors);
+                const Range own = arr[0]->block(p);
+                ch.p[p] = {(const double *)LP.a[0].ptr, (double *)LP.a[1].ptr, own.lo, own.hi, LP.mir};
+            }
+        }
     }
     // the paper's coherence: every partition sends the rows it wrote to every
     // other slab that holds them, on its own stream after its kernel

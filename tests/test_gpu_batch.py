@@ -170,3 +170,89 @@ def test_graph_of_partitioned_steps_as_persistent_tasks_k8():
         c.exit(b)
         c.exit(a)
     assert np.array_equal(a, oracle.jacobi2d(u0, 40))
+
+
+@pytest.mark.parametrize("shape,K,steps", [
+    ((3, 3), 1, 4), ((9, 9), 4, 5), ((40, 66), 1, 2), ((40, 66), 2, 3), ((33, 43), 3, 12), ((34, 44), 1, 13),
+    ((12, 300), 5, 24), ((300, 12), 16, 23), ((130, 127), 2, 20), ((257, 200), 4, 40),
+    ((2100, 1300), 3, 25), ((1500, 2200), 8, 9),  # enough regions for the tall ones
+])
+def test_chained_steps_bit_exact(shape, K, steps):
+    """Persistent steps between two arrays whose boundaries differ, as a graph,
+    replayed: both arrays afterwards, every partition's slabs included."""
+    say(f"chained steps {shape} K={K} steps={steps}")
+    a = inputs.jacobi_grid(*shape, seed=61)
+    b = inputs.jacobi_grid(*shape, seed=62)
+    for u, v in ((a, 0.25), (b, -0.75)):
+        u[0], u[-1], u[:, 0], u[:, -1] = v, 2 * v, 3 * v, 4 * v
+    ref = [a.copy(), b.copy()]
+    cfg = jacc.config(persistent=1)
+    with context(K) as c:
+        c.enter(a, halo=(1, 1))
+        c.enter(b, halo=(1, 1))
+        c.batch_begin()
+        for t in range(steps):
+            c.jacobi2d(*((a, b) if t % 2 == 0 else (b, a)), cfg=cfg)
+        g = c.batch_end()
+        assert c.batch_info(g) == {"loops": steps, "persistent_groups": steps, "replay_safe": True}
+        c.batch_launch(g, 2)
+        c.jacobi2d(a, b)  # reads every partition's halo rows
+        c.jacobi2d(b, a)
+        c.exit(b, jacc.COPYOUT)
+        c.exit(a, jacc.COPYOUT)
+    for t in [t for _ in range(3) for t in range(steps)] + [0, 1]:
+        oracle.jacobi2d_sweep(ref[t % 2], ref[1 - t % 2])
+    assert np.array_equal(a, ref[0]) and np.array_equal(b, ref[1])
+
+
+@pytest.mark.parametrize("K,box", [(1, ((5, 40), (7, 100))), (3, ((20, 61), (1, 129))), (4, ((30, 33), (60, 62)))])
+def test_chained_steps_of_an_inner_box_between_other_loops(K, box):
+    """A box inside the grid keeps what either array holds around it; a sum, a
+    loop on other arrays and a step of another box end or join the chain."""
+    say(f"chained steps box={box} K={K}")
+    a, b = inputs.uniform((64, 130), seed=63), inputs.uniform((64, 130), seed=64)
+    p, q = inputs.jacobi_grid(50, 70, seed=65), inputs.jacobi_grid(50, 70, seed=66)
+    ref = [x.copy() for x in (a, b, p, q)]
+    cfg = jacc.config(persistent=1)
+    whole = ((1, 63), (1, 129))
+
+    def sweep(u, v, bx):
+        oracle.jacobi2d_sweep(u, v, bx)
+
+    with context(K) as c:
+        for x in (a, b, p, q):
+            c.enter(x, halo=(1, 1))
+
+        def step(u, v, bx):
+            c.loop(jacc.JACOBI2D, jacc.bounds(*bx), [(u, jacc.READ, -1, 1, 0), (v, jacc.WRITE, 0, 0, 0)], cfg=cfg)
+
+        c.batch_begin()
+        for t in range(8):
+            step(*((a, b) if t % 2 == 0 else (b, a)), box)
+        step(p, q, ((1, 49), (1, 69)))            # joins the last step's group
+        step(q, p, ((1, 49), (1, 69)))
+        for t in range(5):
+            step(*((a, b) if t % 2 == 0 else (b, a)), box)
+        c.sum(a, slot=0, sync=False)              # ends the chain
+        for t in range(5, 12):
+            step(*((a, b) if t % 2 == 0 else (b, a)), whole if t == 8 else box)
+        step(a, b, box)
+        step(a, b, box)                           # not a step back
+        g = c.batch_end()
+        got = c.reductions(0, 1)[0]
+        for x in (a, b, p, q):
+            c.exit(x, jacc.COPYOUT)
+    for t in range(8):
+        sweep(*((ref[0], ref[1]) if t % 2 == 0 else (ref[1], ref[0])), box)
+    sweep(ref[2], ref[3], ((1, 49), (1, 69)))
+    sweep(ref[3], ref[2], ((1, 49), (1, 69)))
+    for t in range(5):
+        sweep(*((ref[0], ref[1]) if t % 2 == 0 else (ref[1], ref[0])), box)
+    total = ref[0].sum()
+    for t in range(5, 12):
+        sweep(*((ref[0], ref[1]) if t % 2 == 0 else (ref[1], ref[0])), whole if t == 8 else box)
+    sweep(ref[0], ref[1], box)
+    for x, y in zip((a, b, p, q), ref):
+        assert np.array_equal(x, y)
+    # two sums of n values in different orders: n eps of the sum of their magnitudes
+    assert abs(got - total) <= a.size * np.finfo(np.float64).eps * np.abs(ref[0]).sum() * 2
