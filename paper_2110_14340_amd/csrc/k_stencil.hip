@@ -608,6 +608,7 @@ __device__ __forceinline__ PTask load_task(ConstTask *p) {
     T.tile = p->tile;
     T.march = p->march;
     T.bx = p->bx;
+    T.order = p->order;
     T.in = p->in;
     T.out = p->out;
     T.e1 = p->e1;
@@ -648,6 +649,57 @@ persistent_kernel(const PTask *__restrict__ tasks, int ntasks, int64_t total) {
         const PTask T = load_task(ct + lo);
         persistent_tile<JONLY, NT>(T, t - T.tile_begin);
     }
+}
+
+// ---------------------------------------------------------------------------
+// Merged loops: the independent stencil loops of a batch in one launch, each
+// with the body its own launch would run.  A small loop's kernel is mostly its
+// launch, its first loads' latency and its last workgroups' tail (64x128x128
+// heat: 8 us for 5 us of traffic); merged, they fill each other's.
+// ---------------------------------------------------------------------------
+template <bool NT>
+__global__ void __launch_bounds__(kPersistentThreads)
+merged_kernel(const PTask *__restrict__ tasks, int ntasks) {
+    ConstTask *ct = (ConstTask *)tasks;
+    const int64_t b = blockIdx.x;
+    int q = 0, hi = ntasks - 1;  // last task whose first workgroup is <= b
+    while (q < hi) {
+        const int mid = (q + hi + 1) >> 1;
+        if (ct[mid].tile_begin <= b)
+            q = mid;
+        else
+            hi = mid - 1;
+    }
+    const PTask T = load_task(ct + q);
+    const int64_t span = (q + 1 < ntasks ? ct[q + 1].tile_begin : (int64_t)gridDim.x) - T.tile_begin;
+    const int64_t local = b - T.tile_begin;
+    const int64_t t = T.order >= 2 ? (local & 7) * (span >> 3) + (local >> 3) : local;
+    if (t >= T.ntiles) return;
+    const int tx = threadIdx.x & (T.bx - 1), ty = threadIdx.x / T.bx, by = kPersistentThreads / T.bx;
+    Mirrors none;
+    none.n = 0;
+    if (T.kind == JACC_LOOP_JACOBI2D) {
+#define MERGED_JACOBI(V)                                                                                             \
+    jacobi_tile<V, 0, NT>(T.in, T.out, T.e1, T.e1, T.lo[0], T.hi[0], T.lo[1], T.hi[1], T.col0, T.tile, T.march, none, \
+                          t % T.gx, t / T.gx, tx, ty, T.bx, by)
+        if (T.vec == 2)
+            MERGED_JACOBI(2);
+        else
+            MERGED_JACOBI(3);
+#undef MERGED_JACOBI
+        return;
+    }
+    int64_t bxi, byi, bzi;
+    heat_coords(t, T.gx, T.gy, T.gz, T.order, bxi, byi, bzi);
+#define MERGED_HEAT(V)                                                                                                \
+    (void)heat_rows_tile<V, 2, false, 0, NT>(T.in, T.out, T.e1, T.e2, T.lo[0], T.hi[0], T.lo[1], T.hi[1], T.lo[2],     \
+                                             T.hi[2], T.col0, T.tile, T.march, T.alpha, none, bxi, byi, bzi, tx, ty, \
+                                             T.bx, by, INT64_MIN, INT64_MAX)
+    if (T.vec == 2)
+        MERGED_HEAT(2);
+    else
+        MERGED_HEAT(3);
+#undef MERGED_HEAT
 }
 
 // ---------------------------------------------------------------------------
@@ -1131,6 +1183,45 @@ bool make_task(const Launch &L, PTask *t) {
     }
     t->ntiles = t->gx * t->gy * t->gz;
     return true;
+}
+
+bool make_merged(const Launch &L, PTask *t) {
+    const bool heat = L.kind == JACC_LOOP_HEAT3D;
+    if (!heat && L.kind != JACC_LOOP_JACOBI2D) return false;
+    const Cfg &c = L.cfg;
+    if (L.mir.n || L.cmir.n || L.own_hi > L.own_lo || L.part_dim != 0 || c.vec != 2 || c.bx > kPersistentThreads ||
+        kPersistentThreads % c.bx != 0 || (heat && c.rows != 2))
+        return false;
+    if (!make_task(L, t)) return false;
+    if (t->ntiles == 0) return true;
+    t->bx = c.bx;
+    t->order = c.order;
+    // other loops fill the chip, so tiles are longer than a launch of the
+    // loop's own would take (24 heat and 16 Jacobi fields of 338 MB: 101 us with
+    // 3 planes and 2 rows, 93 with these)
+    t->tile = heat ? (array_bytes(L) >= (8 << 19) ? 8 : 4) : (c.tile < 4 ? 4 : c.tile);
+    const int64_t w = (int64_t)c.bx * c.vec, by = kPersistentThreads / c.bx;
+    t->gx = cdiv(L.hi[heat ? 2 : 1] - t->col0, w);
+    if (heat) {
+        t->gy = cdiv(L.hi[1] - L.lo[1], by * c.rows);
+        t->gz = cdiv(L.hi[0] - L.lo[0], t->tile);
+    } else {
+        t->gy = cdiv(L.hi[0] - L.lo[0], by * t->tile);
+    }
+    t->ntiles = t->gx * t->gy * t->gz;
+    return true;
+}
+
+hipError_t launch_merged(const PTask *tasks, int ntasks, int64_t workgroups, bool nt, hipStream_t s) {
+    if (ntasks < 1 || workgroups < 1 || workgroups > (int64_t)INT32_MAX) return hipErrorInvalidValue;
+#define MERGED_LAUNCH(N) \
+    hipLaunchKernelGGL(merged_kernel<N>, dim3((unsigned)workgroups), dim3(kPersistentThreads), 0, s, tasks, ntasks)
+    if (nt)
+        MERGED_LAUNCH(true);
+    else
+        MERGED_LAUNCH(false);
+#undef MERGED_LAUNCH
+    return hipGetLastError();
 }
 
 // One workgroup per tile (measured: 2.5-5 % faster on 8192^2 steps than a

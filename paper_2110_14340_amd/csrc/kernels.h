@@ -72,6 +72,7 @@ struct Launch {
     // over them, written by the finaliser; `total_host`, pinned, may be null
     double *total, *total_host;
     unsigned *ticket;  // for packed launches: zero, and zero again when the finaliser ends
+    bool streamed;      // other loops' arrays pass through the caches between its runs
     int64_t part_rows;  // iterations along dim 0 of the largest partition (for defaults)
 };
 
@@ -97,7 +98,7 @@ inline int64_t array_bytes(const Launch &L) {
         if (L.ext[i] > 0) n *= L.ext[i];
     return n;
 }
-inline bool cache_resident(const Launch &L) { return 2 * array_bytes(L) <= kCacheBytes; }
+inline bool cache_resident(const Launch &L) { return !L.streamed && 2 * array_bytes(L) <= kCacheBytes; }
 
 // Fills in defaults for zero fields of a configuration.
 Cfg default_config(int kind, const Launch &L, Cfg c);
@@ -117,6 +118,7 @@ hipError_t launch_combine(const double *partials, const CombineList &list, doubl
 struct PTask {
     int32_t kind;  // JACC_LOOP_JACOBI2D or JACC_LOOP_HEAT3D
     int32_t vec, tile, march, bx;
+    int32_t order;  // merged loops only
     const double *in;
     double *out;
     int64_t e1, e2;  // extents of dims 1 and 2 (2-D: e1 = row length)
@@ -142,6 +144,14 @@ int64_t persistent_grid(int64_t tiles, bool jacobi_only);
 // non-temporal stores, for tasks that together exceed kCacheBytes).
 hipError_t launch_persistent(const PTask *tasks, int ntasks, int64_t tiles, int64_t grid, bool jacobi_only, bool nt,
                              hipStream_t s);
+
+// Independent stencil loops of a batch in one launch ("merged"): each has its own
+// default shape (256 threads, cfg.bx along a row) and its tiles a run of
+// workgroups starting at a multiple of 8.  make_merged gives a loop's task, with
+// tile_begin unset; false: a loop this cannot run (mirrors, a filtered output, a
+// shape of the caller's).  `workgroups` is the total with every run rounded up.
+bool make_merged(const Launch &L, PTask *t);
+hipError_t launch_merged(const PTask *tasks, int ntasks, int64_t workgroups, bool nt, hipStream_t s);
 
 // The partitions of one eager stencil (or SUM) loop in one launch ("packed"): the
 // launches of its partitions (the same kind, configuration and box apart

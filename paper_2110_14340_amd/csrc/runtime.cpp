@@ -39,6 +39,7 @@ constexpr int kSlots = 4096;
 constexpr int kEventRing = 16;
 using jk::kWgCapacity;
 constexpr int kTaskCapacity = 4096;       // persistent tasks per batch
+constexpr int kMergeCapacity = 1024;      // loops per batch that share launches; further ones are launched alone
 constexpr int64_t kBinnedMinCols = 1 << 20;  // SpMV x length from which the binned form is the default
 
 thread_local std::string g_init_err;  // message of the last failed context-free call (jacc_init, no-alloc step)
@@ -294,9 +295,9 @@ struct Batch {
     // leaves the data region the graph is stale and is never replayed again
     std::vector<int> array_ids;
     bool stale = false;
-    jk::PTask *dev_tasks = nullptr;   // kTaskCapacity device task records
+    jk::PTask *dev_tasks = nullptr;   // kTaskCapacity device task records, then kMergeCapacity of merged loops
     jk::PTask *host_tasks = nullptr;  // pinned staging of the same size
-    int tasks_used = 0;
+    int tasks_used = 0, merged_used = 0;
     int groups = 0;
 };
 
@@ -383,6 +384,8 @@ struct jacc_ctx {
     std::vector<PendingAccess> paccs;
     std::vector<Array *> parrays;
     StepChain chain;
+    std::vector<jk::Launch> mloops;  // loops of the open batch that wait to share a launch
+    std::vector<Array *> marrays;
     hipEvent_t fork_ev = nullptr, t0 = nullptr, t1 = nullptr;
     // per-partition kernel timing (jacc_time_loop_parts): events around each
     // partition's launch; kev[2p] before, kev[2p+1] after
@@ -945,6 +948,51 @@ int issue_chain(jacc_ctx *c, int steps) {
     return JACC_OK;
 }
 
+// Launches the batch's waiting loops, which touch no array in common: those that
+// can in one launch, the largest first so that the small ones fill its end.
+int flush_merged(jacc_ctx *c) {
+    Batch *B = c->cur;
+    std::vector<jk::Launch> loops;
+    loops.swap(c->mloops);
+    c->marrays.clear();
+    if (loops.empty()) return JACC_OK;
+    std::stable_sort(loops.begin(), loops.end(), [](const jk::Launch &x, const jk::Launch &y) {
+        return jk::array_bytes(x) > jk::array_bytes(y);
+    });
+    jk::PTask *const table = B->host_tasks + kTaskCapacity + B->merged_used;
+    int n = 0;
+    int64_t workgroups = 0, bytes = 0, all = 0;
+    for (const jk::Launch &L : loops) all += 2 * jk::array_bytes(L);
+    for (jk::Launch &L : loops) {
+        jk::PTask t;
+        // where the loops together exceed the cache, a large one (more than half
+        // of it) runs alone as the streaming shape (a batch of 16 + 16 uneven
+        // fields, 1.7 GB: 425 us, 493 with those of 300 and 600 MB merged)
+        if (all > jk::kCacheBytes && 2 * jk::array_bytes(L) > jk::kCacheBytes / 2) {
+            L.streamed = true;
+            L.cfg = jk::default_config(L.kind, L, jk::Cfg{});
+            HIPCHK(c, jk::launch_loop(L, c->st[0].s), "kernel launch");
+            continue;
+        }
+        const bool fits = loops.size() > 1 && B->merged_used + n < kMergeCapacity && jk::make_merged(L, &t) &&
+                          workgroups + t.ntiles < INT32_MAX - 8;
+        if (!fits) {
+            HIPCHK(c, jk::launch_loop(L, c->st[0].s), "kernel launch");
+        } else if (t.ntiles > 0) {
+            t.tile_begin = workgroups;
+            workgroups += (t.ntiles + 7) / 8 * 8;
+            bytes += 2 * jk::array_bytes(L);
+            table[n++] = t;
+        }
+    }
+    if (n)
+        HIPCHK(c, jk::launch_merged(B->dev_tasks + kTaskCapacity + B->merged_used, n, workgroups,
+                                    bytes > jk::kCacheBytes, c->st[0].s),
+               "merged loops launch");
+    B->merged_used += n;
+    return JACC_OK;
+}
+
 int flush_group(jacc_ctx *c) {
     if (c->ptasks.empty()) return JACC_OK;
     int rc = c->chain.steps > 1 ? issue_chain(c, c->chain.steps) : launch_tasks(c, c->ptasks, c->paccs, true);
@@ -1399,6 +1447,11 @@ int loop_impl(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const jacc
         rc = flush_group(c);
         if (rc) return rc;
     }
+    for (int i = 0; i < nargs; ++i)
+        if (std::find(c->marrays.begin(), c->marrays.end(), arr[i]) != c->marrays.end()) {
+            rc = flush_merged(c);
+            if (rc) return rc;
+        }
     const bool starts = chains && c->ptasks.empty();
     if (persistent && !extends && !starts) {
         rc = end_chain(c);
@@ -1734,6 +1787,10 @@ int loop_impl(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const jacc
             }
         }
     }
+    // a stencil loop of a batch that gave no configuration waits for others it
+    // can share a launch with
+    const bool waits = c->cur && one_stream && !cfg && K == 1 && !want_red && !persistent && !dup && !c->serialize &&
+                       (kind == JACC_LOOP_JACOBI2D || kind == JACC_LOOP_HEAT3D);
     for (const Piece &piece_ : pieces) {
         const int p = piece_.p;
         const PartPlan &pp = piece_.pp;
@@ -1828,6 +1885,9 @@ int loop_impl(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const jacc
         if (kind == JACC_LOOP_SPMV_CSR && LP.cfg.order == 4) {
             rc = issue_spmv(c, arr, p, &LP, 1, s);
             if (rc) return rc;
+        } else if (live(c) && waits) {
+            c->mloops.push_back(LP);
+            c->marrays.insert(c->marrays.end(), arr, arr + nargs);
         } else if (live(c)) {
             HIPCHK(c, jk::launch_loop(LP, c->st[s].s), "kernel launch");
         }
@@ -2281,6 +2341,7 @@ int jacc_finalize(jacc_ctx *c) {
         if (c->model && c->model_release) c->model_release(c->model);  // its buffers come from this context
         c->model = nullptr;
         if (c->cur) {  // abandon an open capture (its op log goes with it)
+            c->mloops.clear();
             c->oplog = nullptr;
             if (live(c)) {
                 hipGraph_t g = nullptr;
@@ -2563,13 +2624,14 @@ int jacc_batch_begin(jacc_ctx *c) {
     Marker mk(c, "jacc batch begin");
     if (c->cur) return set_err(c, JACC_ERR_INVALID, "a batch is already open");
     Batch *B = new Batch();
-    int rc = dev_alloc(c, kTaskCapacity * sizeof(jk::PTask), (void **)&B->dev_tasks);
+    int rc = dev_alloc(c, (kTaskCapacity + kMergeCapacity) * sizeof(jk::PTask), (void **)&B->dev_tasks);
     if (rc) {
         delete B;
         return rc;
     }
     if (!c->dry) {
-        hipError_t e = hipHostMalloc((void **)&B->host_tasks, kTaskCapacity * sizeof(jk::PTask), hipHostMallocDefault);
+        hipError_t e = hipHostMalloc((void **)&B->host_tasks, (kTaskCapacity + kMergeCapacity) * sizeof(jk::PTask),
+                                     hipHostMallocDefault);
         if (e != hipSuccess) {
             dev_free(c, B->dev_tasks);
             delete B;
@@ -2594,6 +2656,7 @@ int jacc_batch_end(jacc_ctx *c, int *graph_id) {
     if (!graph_id) return set_err(c, JACC_ERR_INVALID, "NULL graph id");
     Batch *B = c->cur;
     int rc = flush_group(c);
+    if (!rc && live(c)) rc = flush_merged(c);
     c->oplog = nullptr;
     if (rc) return rc;
     if (live(c)) {
@@ -2602,6 +2665,10 @@ int jacc_batch_end(jacc_ctx *c, int *graph_id) {
         if (B->tasks_used > 0)
             HIPCHK(c, hipMemcpy(B->dev_tasks, B->host_tasks, (size_t)B->tasks_used * sizeof(jk::PTask),
                                 hipMemcpyHostToDevice),
+                   "hipMemcpy(task tables)");
+        if (B->merged_used > 0)
+            HIPCHK(c, hipMemcpy(B->dev_tasks + kTaskCapacity, B->host_tasks + kTaskCapacity,
+                                (size_t)B->merged_used * sizeof(jk::PTask), hipMemcpyHostToDevice),
                    "hipMemcpy(task tables)");
     }
     c->cur = nullptr;

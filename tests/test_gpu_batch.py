@@ -256,3 +256,63 @@ def test_chained_steps_of_an_inner_box_between_other_loops(K, box):
         assert np.array_equal(x, y)
     # two sums of n values in different orders: n eps of the sum of their magnitudes
     assert abs(got - total) <= a.size * np.finfo(np.float64).eps * np.abs(ref[0]).sum() * 2
+
+
+def _check_merged(shapes, K=1, replays=2, chain=False):
+    """One loop per field, no configuration; with `chain` also the step back and
+    a second output from the same input.  All bits as the oracle's sweeps."""
+    ins = [inputs.jacobi_grid(*s, seed=200 + i) if len(s) == 2 else inputs.heat_field(*s, seed=200 + i)
+           for i, s in enumerate(shapes)]
+    outs, more = [u + 0.5 for u in ins], [u - 0.5 for u in ins]
+    refs = [[x.copy() for x in t] for t in zip(ins, outs, more)]
+
+    def sweep(u, v):
+        oracle.jacobi2d_sweep(u, v) if u.ndim == 2 else oracle.heat3d_sweep(u, v, 0.1)
+
+    with context(max(K, 2)) as c:
+        for x in (*ins, *outs, *more):
+            c.enter(x, halo=(1, 1), K=K)
+
+        def step(u, v):
+            c.jacobi2d(u, v) if u.ndim == 2 else c.heat3d(u, v, 0.1)
+
+        c.batch_begin()
+        for u, v, w in zip(ins, outs, more):
+            step(u, v)
+        if chain:
+            for u, v, w in zip(ins, outs, more):
+                step(u, w)
+                step(w, u)
+        g = c.batch_end()
+        n = len(shapes) * (3 if chain else 1)
+        assert c.batch_info(g) == {"loops": n, "persistent_groups": 0, "replay_safe": True}
+        c.batch_launch(g, replays)
+        for x in (*ins, *outs, *more):
+            c.exit(x, jacc.COPYOUT)
+    for u, v, w in refs:
+        for _ in range(1 + replays):
+            sweep(u, v)
+            if chain:
+                sweep(u, w)
+                sweep(w, u)
+    for i, t in enumerate(zip(ins, outs, more)):
+        for x, y in zip(t, refs[i]):
+            assert np.array_equal(x, y), (i, shapes[i])
+
+
+@pytest.mark.parametrize("K,chain", [(1, False), (1, True), (2, True)])
+def test_merged_loops_bit_exact(K, chain):
+    """Independent loops that share a launch: odd and even rows, every default
+    shape's edges, fields of one cell, one that is nothing but boundary."""
+    say(f"merged loops K={K} chain={chain}")
+    _check_merged([(3, 3), (65, 64), (64, 65), (130, 1027), (1030, 517), (9, 4100), (3, 3, 3), (9, 10, 11), (33, 34, 129),
+                   (66, 67, 121), (60, 70, 260), (17, 200, 301), (82, 80, 82), (2, 40), (5, 2, 9)], K=K, chain=chain)
+
+
+def test_merged_loops_beyond_the_cache_and_the_table():
+    """More than 288 MB together, with a field that then runs alone as the
+    streaming shape; and more loops than the table holds."""
+    say("merged loops: 330 MB")
+    _check_merged([(230, 240, 181), (3000, 2001), (100, 101, 102), (4, 70), (1500, 1400), (30, 31, 32)], replays=1)
+    say("merged loops: 1100 small ones")
+    _check_merged([(5 + i % 7, 6 + i % 66) for i in range(1100)], replays=1)
