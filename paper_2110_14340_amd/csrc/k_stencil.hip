@@ -867,12 +867,12 @@ static int width_of(const Launch &L) {
 }
 
 // A launch macro with its last argument (NT) from the local `nt`.
-#define WITH_NT(LAUNCH, ...)            \
-    do {                                \
-        if (nt)                         \
-            LAUNCH(__VA_ARGS__, true);  \
-        else                            \
-            LAUNCH(__VA_ARGS__, false); \
+#define WITH_NT(LAUNCH, V, ...)                         \
+    do {                                                \
+        if (nt)                                         \
+            LAUNCH(V, ##__VA_ARGS__, true);             \
+        else                                            \
+            LAUNCH(V, ##__VA_ARGS__, ((V) == 1));       \
     } while (0)
 
 static int64_t col_start(int64_t lo, int vec) { return vec == 2 ? (lo & ~(int64_t)1) : lo; }
@@ -1239,10 +1239,16 @@ hipError_t launch_persistent(const PTask *tasks, int ntasks, int64_t tiles, int6
 #define PERSISTENT_LAUNCH(J, N)                                                                                     \
     hipLaunchKernelGGL((persistent_kernel<J, N>), dim3((unsigned)grid), dim3(kPersistentThreads), 0, s, tasks, ntasks, \
                        tiles)
-    if (jacobi_only)
-        WITH_NT(PERSISTENT_LAUNCH, true);
-    else
-        WITH_NT(PERSISTENT_LAUNCH, false);
+    if (jacobi_only) {
+        if (nt)
+            PERSISTENT_LAUNCH(true, true);
+        else
+            PERSISTENT_LAUNCH(true, false);
+    } else if (nt) {
+        PERSISTENT_LAUNCH(false, true);
+    } else {
+        PERSISTENT_LAUNCH(false, false);
+    }
 #undef PERSISTENT_LAUNCH
     return hipGetLastError();
 }
