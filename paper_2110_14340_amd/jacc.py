@@ -7,6 +7,7 @@ in-tree (``python -m paper_2110_14340_amd.build``); loading fails loudly
 when it is missing — there is no fallback.
 """
 import ctypes
+import operator
 import os
 
 import numpy as np
@@ -183,6 +184,10 @@ def lib():
     return L
 
 
+_INTERIOR2 = (None, None)
+_INTERIOR3 = (None, None, None)
+
+
 class JaccError(RuntimeError):
     def __init__(self, status, msg):
         super().__init__(f"{STATUS_NAMES.get(status, status)}: {msg}")
@@ -348,7 +353,9 @@ class Context:
         self._ids = {}  # id(array) -> (array, host address) of entered arrays
         self._calls = {}
         self._no_scalars = (ctypes.c_double * 1)(0.0)
-        self._loop_fn = self.L.jacc_parallel_loop
+        # the same entry point without declared argument types: a stencil call's
+        # arguments are built here, and checking them again took 0.65 us
+        self._loop_fn = self.L["jacc_parallel_loop"]
 
     # -- helpers ---------------------------------------------------------
     def _check(self, st):
@@ -432,39 +439,54 @@ class Context:
         self._check(st)
         return out.value if sync else None
 
-    def _stencil_call(self, kind, u_in, u_out, pairs, scalars, slot, sync, cfg, raw):
-        """Marshalled arguments of a stencil call, cached per (arrays, box)
-        so that a time-stepping loop pays the ctypes construction once."""
-        key = (kind, self._ptr(u_in), self._ptr(u_out), pairs)
+    def _stencil_call(self, kind, u_in, u_out, rngs, scalars, slot, sync, cfg, raw):
+        """One stencil call; `rngs` gives a range per dimension, None the
+        interior.  Its marshalled arguments are cached per (arrays, shape,
+        ranges), so that a time-stepping loop pays the ctypes construction
+        once (2.2 us a call without a device, 0.65 of them the planner's;
+        3.1 with the ranges and checks of every call)."""
+        get = self._ids.get
+        ent = get(id(u_in))
+        p_in = ent[1] if ent is not None and ent[0] is u_in else self._ptr(u_in)
+        ent = get(id(u_out))
+        p_out = ent[1] if ent is not None and ent[0] is u_out else self._ptr(u_out)
+        key = (kind, p_in, p_out, u_in.shape, rngs)
         ent = self._calls.get(key)
         if ent is None:
+            if len(u_in.shape) != len(rngs):
+                raise ValueError(f"a field of {len(rngs)} dimensions is expected, not {len(u_in.shape)}")
             if len(self._calls) > 512:
                 self._calls.clear()
             A = (Arg * 2)()
-            A[0] = Arg(key[1], READ, -1, 1, 0)
-            A[1] = Arg(key[2], WRITE, 0, 0, 0)
-            b = bounds(*pairs)
+            A[0] = Arg(p_in, READ, -1, 1, 0)
+            A[1] = Arg(p_out, WRITE, 0, 0, 0)
+            b = bounds(*[tuple(r or (1, n - 1)) for r, n in zip(rngs, u_in.shape)])
             ent = self._calls[key] = (A, b, ctypes.byref(b))
-        A, _, bref = ent
         S = (ctypes.c_double * len(scalars))(*scalars) if scalars else self._no_scalars
-        out = ctypes.c_double(0.0) if sync else None
-        st = self._loop_fn(self.ctx, kind, bref, 2, A, S, len(scalars), slot, ctypes.byref(out) if sync else None,
-                           ctypes.byref(cfg) if cfg is not None else None)
+        if sync or cfg is not None:
+            out = ctypes.c_double(0.0)
+            st = self.L.jacc_parallel_loop(self.ctx, kind, ent[2], 2, ent[0], S, len(scalars), slot,
+                                           ctypes.byref(out) if sync else None,
+                                           None if cfg is None else ctypes.byref(cfg))
+        else:
+            st = self._loop_fn(self.ctx, kind, ent[2], 2, ent[0], S, len(scalars), operator.index(slot), None, None)
         if raw:
             return st
-        self._check(st)
+        if st != OK:
+            self._check(st)
         return out.value if sync else None
 
     # convenience wrappers for the loop kinds (declared access ranges)
     def jacobi2d(self, u_in, u_out, rows=None, cols=None, cfg=None, raw=False):
-        ny, nx = u_in.shape
-        pairs = (tuple(rows or (1, ny - 1)), tuple(cols or (1, nx - 1)))
-        return self._stencil_call(JACOBI2D, u_in, u_out, pairs, (), -1, False, cfg, raw)
+        if rows or cols:
+            ny, nx = u_in.shape
+            rngs = (tuple(rows or (1, ny - 1)), tuple(cols or (1, nx - 1)))
+        else:
+            rngs = _INTERIOR2
+        return self._stencil_call(JACOBI2D, u_in, u_out, rngs, (), -1, False, cfg, raw)
 
     def heat3d(self, u_in, u_out, alpha, slot=-1, sync=False, cfg=None, raw=False):
-        nz, ny, nx = u_in.shape
-        return self._stencil_call(HEAT3D, u_in, u_out, ((1, nz - 1), (1, ny - 1), (1, nx - 1)), (alpha,), slot, sync,
-                                  cfg, raw)
+        return self._stencil_call(HEAT3D, u_in, u_out, _INTERIOR3, (alpha,), slot, sync, cfg, raw)
 
     def sum(self, x, squares=False, slot=-1, sync=True, rows=None, raw=False):
         b = bounds(rows or (0, x.shape[0]))
