@@ -88,7 +88,9 @@ Cfg default_config(int kind, const Launch &L, Cfg c) {
             if (!c.by) c.by = 1;
             // short tiles while there are few of them (512^2: 3.9 us with 2
             // rows, 4.3 with 4, 5.4 with 8; 2048^2: 12.3 with 4, 11.9 with 8)
-            if (!c.tile) c.tile = !cached || tiny ? 4 : cells < (1 << 20) ? 2 : cells < (1 << 22) ? 4 : 8;
+            // (several partitions in a launch: 4, 1175x780 over 8 8.5 us, 8.9 with 2)
+            const bool split = 3 * L.part_rows < 2 * L.ext[0];
+            if (!c.tile) c.tile = !cached || tiny ? 4 : cells < (1 << 20) && !split ? 2 : cells < (1 << 22) ? 4 : 8;
             if (!c.order) c.order = cached ? 2 : 1;
             break;
         }

@@ -255,6 +255,11 @@ __device__ __forceinline__ void jacobi_tile(const double *__restrict__ in, doubl
     }
 }
 
+// Tile counts and indices stay below 2^31 (a grid's limit), where a division
+// takes a tenth of the instructions of a 64-bit one.
+__device__ __forceinline__ int64_t div32(int64_t a, int64_t b) { return (uint32_t)a / (uint32_t)b; }
+__device__ __forceinline__ int64_t mod32(int64_t a, int64_t b) { return (uint32_t)a % (uint32_t)b; }
+
 // Tile of a 1-D grid's workgroup: row-major (order 1), or XCD-aware (order
 // 2): workgroup b runs on XCD b mod 8, and XCD x takes the x-th contiguous
 // eighth of the tiles in row-major order (the grid is then the tiles rounded
@@ -273,7 +278,7 @@ jacobi2d_kernel(const double *__restrict__ in, double *__restrict__ out, int64_t
                 int64_t tiles, int order, int64_t own_lo, int64_t own_hi) {
     const int64_t t = tile_of(order, tiles);
     if (t < 0) return;
-    jacobi_tile<V, MM, NT>(in, out, nx, pitch, r_lo, r_hi, c_lo, c_hi, col0, tile, march, mir, t % gx, t / gx, threadIdx.x,
+    jacobi_tile<V, MM, NT>(in, out, nx, pitch, r_lo, r_hi, c_lo, c_hi, col0, tile, march, mir, mod32(t, gx), div32(t, gx), threadIdx.x,
                      threadIdx.y, blockDim.x, blockDim.y, own_lo, own_hi);
 }
 
@@ -286,7 +291,7 @@ jacobi2d_cols_kernel(const double *__restrict__ in, double *__restrict__ out, in
                      int64_t gx, int64_t tiles, int order) {
     const int64_t t = tile_of(order, tiles);
     if (t < 0) return;
-    jacobi_tile<V, 3, NT, ColMirrors>(in, out, nx, pitch, r_lo, r_hi, c_lo, c_hi, col0, tile, march, mir, t % gx, t / gx,
+    jacobi_tile<V, 3, NT, ColMirrors>(in, out, nx, pitch, r_lo, r_hi, c_lo, c_hi, col0, tile, march, mir, mod32(t, gx), div32(t, gx),
                                     threadIdx.x, threadIdx.y, blockDim.x, blockDim.y);
 }
 
@@ -501,22 +506,22 @@ __device__ __forceinline__ double heat_rows_tile(const double *__restrict__ in, 
 constexpr int64_t kHeatYBlock = 8;
 __device__ __forceinline__ void heat_coords(int64_t t, int64_t gx, int64_t gy, int64_t gz, int order, int64_t &bxi,
                                             int64_t &byi, int64_t &bzi) {
-    bxi = t % gx;
-    const int64_t r = t / gx;
+    bxi = mod32(t, gx);
+    const int64_t r = div32(t, gx);
     if (order != 3) {
-        byi = r % gy;
-        bzi = r / gy;
+        byi = mod32(r, gy);
+        bzi = div32(r, gy);
         return;
     }
     const int64_t full = gy / kHeatYBlock;  // complete y-blocks
     if (r < full * kHeatYBlock * gz) {
-        const int64_t blk = r / (kHeatYBlock * gz), q = r % (kHeatYBlock * gz);
+        const int64_t blk = div32(r, kHeatYBlock * gz), q = mod32(r, kHeatYBlock * gz);
         bzi = q / kHeatYBlock;
         byi = blk * kHeatYBlock + q % kHeatYBlock;
     } else {
         const int64_t r2 = r - full * kHeatYBlock * gz, rem = gy - full * kHeatYBlock;
-        bzi = r2 / rem;
-        byi = full * kHeatYBlock + r2 % rem;
+        bzi = div32(r2, rem);
+        byi = full * kHeatYBlock + mod32(r2, rem);
     }
 }
 
@@ -555,8 +560,8 @@ heat3d_kernel(const double *__restrict__ in, double *__restrict__ out, int64_t n
 // One tile (local index `local`) of task T.
 template <bool JONLY, bool NT>
 __device__ __forceinline__ void persistent_tile(const PTask &T, int64_t local) {
-    const int64_t bxi = local % T.gx;
-    const int64_t rest = local / T.gx;
+    const int64_t bxi = mod32(local, T.gx);
+    const int64_t rest = div32(local, T.gx);
     const double *in = T.in;
     double *out = T.out;
     const Mirrors mir = T.mir;
@@ -572,7 +577,7 @@ __device__ __forceinline__ void persistent_tile(const PTask &T, int64_t local) {
             jacobi_tile<1, 2, NT>(in, out, T.e1, T.e1, T.lo[0], T.hi[0], T.lo[1], T.hi[1], T.col0, T.tile, T.march, mir, bxi,
                            rest, tx, ty, T.bx, by);
     } else if constexpr (!JONLY) {
-        const int64_t byi = rest % T.gy, bzi = rest / T.gy;
+        const int64_t byi = mod32(rest, T.gy), bzi = div32(rest, T.gy);
         if (T.vec == 2)
             (void)heat_tile<2, false, 2, NT>(in, out, T.e1, T.e2, T.lo[0], T.hi[0], T.lo[1], T.hi[1], T.lo[2], T.hi[2],
                                       T.col0, T.tile, T.march, T.alpha, mir, bxi, byi, bzi, tx, ty,
@@ -681,7 +686,7 @@ merged_kernel(const PTask *__restrict__ tasks, int ntasks) {
     if (T.kind == JACC_LOOP_JACOBI2D) {
 #define MERGED_JACOBI(V)                                                                                             \
     jacobi_tile<V, 0, NT>(T.in, T.out, T.e1, T.e1, T.lo[0], T.hi[0], T.lo[1], T.hi[1], T.col0, T.tile, T.march, none, \
-                          t % T.gx, t / T.gx, tx, ty, T.bx, by)
+                          mod32(t, T.gx), div32(t, T.gx), tx, ty, T.bx, by)
         if (T.vec == 2)
             MERGED_JACOBI(2);
         else
@@ -715,14 +720,35 @@ struct PartDesc {
     const double *in;
     double *out;
     int64_t lo0, hi0;     // the partition's iterations along dim 0
-    int64_t tiles, begin;  // its tile count and first workgroup
+    int64_t tiles;         // its tile count
     int64_t partial_off;   // its first workgroup partial (heat residual)
     Mirrors mir;
 };
 struct PartPack {
+    int32_t begin[kMaxPack];  // the first workgroups again, INT32_MAX past the last partition
     PartDesc p[kMaxPack];
     int32_t n;
 };
+typedef const __attribute__((address_space(4))) int32_t ConstInt;
+
+// Partition of workgroup b of a pack, its first workgroup and that of the next
+// one (`end` past the last).  The table is one wide scalar load and no branch: a
+// walk over the descriptors took two dependent loads a partition (over 8
+// partitions, 20 sweeps: 2000x900 178 us and 153, 1175x780 166 and 141).
+__device__ __forceinline__ int pack_part(ConstInt *begin, int32_t b, int32_t end, int32_t &first, int32_t &next) {
+    int q = 0;
+    first = 0;
+    next = end;
+#pragma unroll
+    for (int k = 1; k < kMaxPack; ++k) {
+        const int32_t at = begin[k];
+        const bool mine = at <= b;
+        q += mine ? 1 : 0;
+        first = mine ? at : first;
+        next = !mine && at < next ? at : next;
+    }
+    return q;
+}
 typedef const __attribute__((address_space(4))) PartDesc ConstPart;
 
 __device__ __forceinline__ PartDesc load_part(ConstPart *p) {
@@ -732,7 +758,6 @@ __device__ __forceinline__ PartDesc load_part(ConstPart *p) {
     d.lo0 = p->lo0;
     d.hi0 = p->hi0;
     d.tiles = p->tiles;
-    d.begin = p->begin;
     d.partial_off = p->partial_off;
     d.mir.n = p->mir.n;
     for (int k = 0; k < 2; ++k) {
@@ -747,13 +772,10 @@ __device__ __forceinline__ PartDesc load_part(ConstPart *p) {
 // a padding workgroup).
 __device__ __forceinline__ int64_t part_tile(const PartPack &pk, int order, PartDesc &d) {
     ConstPart *cp = (ConstPart *)&pk.p[0];
-    const int64_t b = blockIdx.x;
-    int q = 0;
-    for (int k = 1; k < pk.n; ++k)
-        if (cp[k].begin <= b) q = k;
+    int32_t first, next;
+    const int q = pack_part((ConstInt *)&pk.begin[0], blockIdx.x, gridDim.x, first, next);
     d = load_part(cp + q);
-    const int64_t span = (q + 1 < pk.n ? cp[q + 1].begin : (int64_t)gridDim.x) - d.begin;
-    const int64_t local = b - d.begin;
+    const int32_t span = next - first, local = (int32_t)blockIdx.x - first;
     const int64_t t = order >= 2 ? (local & 7) * (span >> 3) + (local >> 3) : local;
     return t < d.tiles ? t : -1;
 }
@@ -765,7 +787,7 @@ jacobi2d_parts_kernel(PartPack pk, int64_t nx, int64_t c_lo, int64_t c_hi, int64
     PartDesc d;
     const int64_t t = part_tile(pk, order, d);
     if (t < 0) return;
-    jacobi_tile<V, MM, NT>(d.in, d.out, nx, nx, d.lo0, d.hi0, c_lo, c_hi, col0, tile, march, d.mir, t % gx, t / gx,
+    jacobi_tile<V, MM, NT>(d.in, d.out, nx, nx, d.lo0, d.hi0, c_lo, c_hi, col0, tile, march, d.mir, mod32(t, gx), div32(t, gx),
                      threadIdx.x, threadIdx.y, blockDim.x, blockDim.y);
 }
 
@@ -774,12 +796,13 @@ jacobi2d_parts_kernel(PartPack pk, int64_t nx, int64_t c_lo, int64_t c_hi, int64
 struct ColPartDesc {
     const double *in;
     double *out;
-    int64_t tiles, begin;              // its tile count and first workgroup
+    int64_t tiles;                     // its tile count
     int64_t c_lo, c_hi, col0, pitch;  // its columns, first lane column, slab row pitch
     int64_t gx;                        // tiles per row of tiles
     ColMirrors mir;
 };
 struct ColPartPack {
+    int32_t begin[kMaxPack];  // as in PartPack
     ColPartDesc p[kMaxPack];
     int32_t n;
 };
@@ -790,7 +813,6 @@ __device__ __forceinline__ ColPartDesc load_colpart(ConstColPart *p) {
     d.in = p->in;
     d.out = p->out;
     d.tiles = p->tiles;
-    d.begin = p->begin;
     d.c_lo = p->c_lo;
     d.c_hi = p->c_hi;
     d.col0 = p->col0;
@@ -810,17 +832,14 @@ template <int V, bool NT>
 __global__ void __launch_bounds__(1024)
 jacobi2d_colparts_kernel(ColPartPack pk, int64_t nx, int64_t r_lo, int64_t r_hi, int tile, int march, int order) {
     ConstColPart *cp = (ConstColPart *)&pk.p[0];
-    const int64_t b = blockIdx.x;
-    int q = 0;
-    for (int k = 1; k < pk.n; ++k)
-        if (cp[k].begin <= b) q = k;
+    int32_t first, next;
+    const int q = pack_part((ConstInt *)&pk.begin[0], blockIdx.x, gridDim.x, first, next);
     const ColPartDesc d = load_colpart(cp + q);
-    const int64_t span = (q + 1 < pk.n ? cp[q + 1].begin : (int64_t)gridDim.x) - d.begin;
-    const int64_t local = b - d.begin;
+    const int32_t span = next - first, local = (int32_t)blockIdx.x - first;
     const int64_t t = order >= 2 ? (local & 7) * (span >> 3) + (local >> 3) : local;
     if (t >= d.tiles) return;
     jacobi_tile<V, 4, NT, ColMirrors>(d.in, d.out, nx, d.pitch, r_lo, r_hi, d.c_lo, d.c_hi, d.col0, tile, march, d.mir,
-                                    t % d.gx, t / d.gx, threadIdx.x, threadIdx.y, blockDim.x, blockDim.y);
+                                    mod32(t, d.gx), div32(t, d.gx), threadIdx.x, threadIdx.y, blockDim.x, blockDim.y);
 }
 
 template <int V, int R, bool RES, int MM, bool NT>
@@ -832,7 +851,7 @@ heat3d_parts_kernel(PartPack pk, int64_t ny, int64_t nx, int64_t y_lo, int64_t y
     PartDesc d;
     const int64_t t = part_tile(pk, order == 3 ? 2 : order, d);
     if (t < 0) return;  // the whole workgroup: no barrier is left waiting
-    const int64_t gz = d.tiles / (gx * gy);
+    const int64_t gz = div32(d.tiles, gx * gy);
     int64_t bxi, byi, bzi;
     heat_coords(t, gx, gy, gz, order, bxi, byi, bzi);
     double acc;
@@ -1007,6 +1026,7 @@ static hipError_t launch_col_parts(const Launch *L, int n, hipStream_t s) {
     const bool xcd = c.order == 2;
     ColPartPack pk{};
     int64_t begin = 0;
+    for (int32_t &at : pk.begin) at = INT32_MAX;
     for (int k = 0; k < n; ++k) {
         const Launch &Lk = L[k];
         if (Lk.a[1].row_elems != Lk.a[0].row_elems || Lk.lo[0] != L0.lo[0] || Lk.hi[0] != L0.hi[0])
@@ -1019,7 +1039,7 @@ static hipError_t launch_col_parts(const Launch *L, int n, hipStream_t s) {
         d.in = (const double *)Lk.a[0].ptr;
         d.out = (double *)Lk.a[1].ptr;
         d.tiles = tiles;
-        d.begin = begin;
+        pk.begin[pk.n - 1] = (int32_t)begin;
         d.c_lo = Lk.lo[1];
         d.c_hi = Lk.hi[1];
         d.col0 = col0;
@@ -1064,6 +1084,7 @@ hipError_t launch_parts(const Launch *L, int n, double *wg_partials, int64_t wg_
         gx = cdiv(L0.hi[1] - col0, (int64_t)c.bx * c.vec);
     }
     PartPack pk{};
+    for (int32_t &at : pk.begin) at = INT32_MAX;
     Segments seg{};
     int64_t begin = 0, partial = 0;
     for (int k = 0; k < n; ++k) {
@@ -1086,7 +1107,7 @@ hipError_t launch_parts(const Launch *L, int n, double *wg_partials, int64_t wg_
         d.lo0 = Lk.lo[0];
         d.hi0 = Lk.hi[0];
         d.tiles = tiles;
-        d.begin = begin;
+        pk.begin[pk.n - 1] = (int32_t)begin;
         d.partial_off = partial;
         d.mir = Lk.mir;
         begin += xcd ? (tiles + 7) / 8 * 8 : tiles;

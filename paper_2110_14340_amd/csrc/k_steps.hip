@@ -52,7 +52,8 @@ jacobi_chain_kernel(Chain ch, int T, int64_t gx, int64_t tiles) {
     const int64_t nx = cc->nx, ny = cc->ny, r_lo = cc->lo[0], r_hi = cc->hi[0], c_lo = cc->lo[1], c_hi = cc->hi[1];
     const int lane = threadIdx.x & (kWave - 1);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int64_t tile_r = r_lo + (t / gx) * (kChainWaves * R - 2 * T), tile_c = c_lo + (t % gx) * (kWave - 2 * T);
+    const uint32_t ty = (uint32_t)t / (uint32_t)gx, tx = (uint32_t)t % (uint32_t)gx;
+    const int64_t tile_r = r_lo + (int64_t)ty * (kChainWaves * R - 2 * T), tile_c = c_lo + (int64_t)tx * (kWave - 2 * T);
     const int64_t row0 = tile_r - T + (int64_t)w * R, col = tile_c - T + lane;
     const bool in_row = col >= 0 && col < nx, box_col = col >= c_lo && col < c_hi;
     const bool sides = tile_r - T < r_lo || tile_r - T + kChainWaves * R > r_hi || tile_c - T < c_lo ||

@@ -88,9 +88,10 @@ int check_config(const Launch &L);
 // 256 MB memory-side cache from one sweep to the next: their outputs are then
 // stored normally instead of non-temporally, and their tiles walked XCD-aware.
 // Measured (us a sweep, non-temporal row-major / normal XCD-aware): Jacobi
-// 2048^2 16.2 / 11.9, 4099x3001 40.1 / 30.1, 5000^2 69.0 / 73.7; heat 128^3
-// 10.0 / 9.1, 256^3 (268 MB) 51 / 43, 301x303x305 (445 MB) 105 / 114.
-constexpr int64_t kCacheBytes = 288 << 20;
+// 2048^2 16.2 / 11.9, 4099x3001 40.1 / 30.1, 4150x4100 (272 MB) 51.4 / 45.6,
+// 4200^2 (282 MB) 51.9 / 54.5, 5000^2 69.0 / 73.7; heat 128^3 10.0 / 9.1, 256^3
+// (268 MB) 51 / 43, 301x303x305 (445 MB) 105 / 114.
+constexpr int64_t kCacheBytes = 264 << 20;
 constexpr int64_t kWgCapacity = 1 << 16;  // workgroup partials a stream's reduction holds
 inline int64_t array_bytes(const Launch &L) {
     int64_t n = 8;

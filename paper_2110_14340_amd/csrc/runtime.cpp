@@ -1579,8 +1579,6 @@ int loop_impl(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const jacc
     // Partitions that share one launch (or are one) have their sums added by
     // the launch's finaliser: no combine kernel follows.
     bool combined = false;
-    if (red_host && live(c) && !c->host_total)  // kept with the context
-        HIPCHK(c, hipHostMalloc((void **)&c->host_total, sizeof(double), hipHostMallocCoherent), "hipHostMalloc");
     auto combine_in_launch = [&](jk::Launch &first, int s) -> int {
         const int e = ensure_wait(c, s, c->slot_src[red_slot].s, c->slot_src[red_slot].seq);  // earlier writer of the slot
         if (e) return e;
@@ -2299,7 +2297,8 @@ int jacc_init(jacc_ctx **out, int K, void *const *streams, const jacc_allocator 
         if (!rc) rc = dev_alloc(c, (size_t)ns * kWgCapacity * sizeof(double), (void **)&c->wg);
         if (!rc) rc = dev_alloc(c, ns * sizeof(unsigned), (void **)&c->tickets);
         if (!rc && !c->dry) {
-            hipError_t e = hipMemset(c->slots, 0, kSlots * sizeof(double));
+            hipError_t e = hipHostMalloc((void **)&c->host_total, sizeof(double), hipHostMallocCoherent);
+            if (e == hipSuccess) e = hipMemset(c->slots, 0, kSlots * sizeof(double));
             if (e == hipSuccess) e = hipMemset(c->tickets, 0, ns * sizeof(unsigned));
             if (e == hipSuccess) e = hipDeviceSynchronize();
             if (e != hipSuccess) rc = dev_fail(c, e, "reduction buffers");

@@ -52,7 +52,7 @@ def test_jacobi_ragged_shapes_partitions_configs(shape, K, cfg):
     ((70, 262), 2, 0, 1),
     ((63, 63), 1, 0, 0), ((64, 64), 1, 0, 0),    # either side of 4096 cells
     ((513, 2049), 1, 0, 0), ((1024, 4099), 2, 0, 0),  # the default's tiles of 4 and 8 rows
-    ((4339, 4351), 1, 0, 0), ((4346, 4353), 2, 0, 0), ((2310, 8190), 1, 0, 0),  # either side of 288 MB for both arrays
+    ((4159, 4159), 1, 0, 0), ((4160, 4161), 2, 0, 0), ((2310, 8190), 1, 0, 0),  # either side of 264 MiB for both arrays
 ])
 def test_jacobi_default_shapes_bit_exact(shape, K, part_dim, persistent):
     say(f"jacobi defaults {shape} K={K} part_dim={part_dim} persistent={persistent}")
@@ -82,7 +82,7 @@ def test_jacobi_default_shapes_bit_exact(shape, K, part_dim, persistent):
 @pytest.mark.parametrize("shape,K", [
     ((5, 7, 3), 1), ((9, 10, 127), 2), ((9, 11, 129), 3), ((7, 9, 131), 1),  # odd rows about a wave's 128 columns
     ((60, 60, 145), 1), ((80, 81, 82), 1), ((80, 81, 83), 3), ((162, 161, 163), 2),  # the small, middle and split shapes
-    ((40, 1200, 398), 1), ((40, 1200, 399), 2), ((60, 700, 497), 1),  # beyond 288 MB: a row held by 256x1 threads
+    ((40, 1200, 398), 1), ((40, 1200, 399), 2), ((60, 700, 497), 1),  # beyond 264 MiB: a row held by 256x1 threads
     ((60, 700, 511), 1), ((100, 1000, 201), 2), ((33, 900, 701), 1),
     ((2056, 2040, 3), 1), ((2056, 2040, 9), 1),  # thin fields: more small tiles than partial sums are held
 ])
