@@ -184,7 +184,7 @@ typedef struct {
  *              memory of the copy (20 bytes an entry) is not to be had, the
  *              plain form runs.
  *   vec        1 or 2 consecutive FP64 elements per lane (2 needs an even row
- *              length)
+ *              length; the default takes two in rows of either parity)
  *   persistent 1 = run the loop inside the batched persistent kernel
  *   order      workgroup-to-tile order: 1 = row-major, 2 = XCD-aware (the
  *              chip hands consecutive workgroup ids to its 8 XCDs in turn; with

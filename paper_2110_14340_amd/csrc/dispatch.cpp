@@ -40,12 +40,15 @@ static Cfg heat_shape(const Launch &L, Cfg c) {
     }
     // bound by HBM: 4 rows and 8 planes re-read the least.  A row held by one
     // workgroup (up to 256 lanes) streams best in row-major order from 256x1
-    // threads (300x300x386: 124, 137 as 64x4; 400^3 213 and 232), except full
-    // ones, whose power-of-two strides prefer bricks of 128x2 (512^3: 394, 408 as
-    // 256x1; 512x512x510: 418 and 435).  Other rows: 128x2 where it idles no
+    // threads (300x300x386: 124, 137 as 64x4; 400^3 213 and 232; 175x435x501 131,
+    // 143 as bricks), except full ones, whose power-of-two strides prefer 128x2
+    // (300x400x512: 192, 199 as 256x1), in bricks where two planes fill an XCD's
+    // L2 (512^3: 394, 408 as 256x1; 512x512x510 418 and 435; 300x400x510 214 in
+    // bricks, 202 in row-major order).  Other rows: 128x2 where it idles no
     // lanes and a row fits (700x700x200: 312, 356 as 64x4), 64x4 elsewhere
     // (300^3: 97, 123 as 128x2; 60x1000x1400: 255 and 276).
-    if (lanes > 248 && lanes <= 256) return set(128, 2, 4, 4, 3);
+    if (lanes > 253 && lanes <= 256)
+        return 8 * L.ext[1] * L.ext[2] > 2000000 ? set(128, 2, 4, 4, 3) : set(128, 2, 8, 4, 1);
     if (lanes > 192 && lanes <= 256) return set(256, 1, 8, 4, 1);
     if (lanes <= 128 && wide) return set(128, 2, 4, 4, 1);
     return set(64, 4, 8, 4, 1);

@@ -84,6 +84,7 @@ def test_jacobi_default_shapes_bit_exact(shape, K, part_dim, persistent):
     ((60, 60, 145), 1), ((80, 81, 82), 1), ((80, 81, 83), 3), ((162, 161, 163), 2),  # the small, middle and split shapes
     ((40, 1200, 398), 1), ((40, 1200, 399), 2), ((60, 700, 497), 1),  # beyond 264 MiB: a row held by 256x1 threads
     ((60, 700, 511), 1), ((100, 1000, 201), 2), ((33, 900, 701), 1),
+    ((90, 400, 510), 1), ((90, 400, 506), 2),  # full rows in small planes, and rows just short of full
     ((2056, 2040, 3), 1), ((2056, 2040, 9), 1),  # thin fields: more small tiles than partial sums are held
 ])
 def test_heat_default_shapes_bit_exact(shape, K):
