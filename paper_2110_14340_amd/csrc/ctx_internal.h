@@ -23,6 +23,8 @@ void set_thread_error(const char *msg);
 // descriptor, byte size and partition count of the array whose host copy
 // starts at `host` (JACC_ERR_NOT_PRESENT when there is none)
 int array_info(jacc_ctx *c, const void *host, jacc_array_desc *d, size_t *bytes, int *K);
+// whether a batch's persistent Jacobi steps each take a launch of their own
+void single_steps(jacc_ctx *c, bool on);
 // the cost model attached to the context (owned by it: `release_model` is
 // called at finalize or when another model is attached)
 void *attached_model(const jacc_ctx *c);

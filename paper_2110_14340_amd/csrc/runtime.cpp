@@ -384,6 +384,7 @@ struct jacc_ctx {
     std::vector<PendingAccess> paccs;
     std::vector<Array *> parrays;
     StepChain chain;
+    bool single_steps = false;  // no chains: every step a launch of its own (the tuner's timing)
     std::vector<jk::Launch> mloops;  // loops of the open batch that wait to share a launch
     std::vector<Array *> marrays;
     hipEvent_t fork_ev = nullptr, t0 = nullptr, t1 = nullptr;
@@ -1439,7 +1440,7 @@ int loop_impl(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const jacc
     // so the small loops of a batch gather into few launches whatever the
     // order they are issued in
     // a Jacobi loop that steps back over the arrays of the pending one extends it
-    const bool chains = persistent && c->cur && !dup && chain_kind(kind, args, arr);
+    const bool chains = persistent && c->cur && !c->single_steps && !dup && chain_kind(kind, args, arr);
     const bool extends = chains && chain_extends(c, b, arr, plan);
     bool conflict = false;
     for (int i = 0; i < nargs && !conflict; ++i) conflict = pending_touches(c, arr[i]);
@@ -2916,6 +2917,7 @@ int array_info(jacc_ctx *c, const void *host, jacc_array_desc *d, size_t *bytes,
     return JACC_OK;
 }
 void set_thread_error(const char *msg) { g_init_err = msg ? msg : ""; }
+void single_steps(jacc_ctx *c, bool on) { c->single_steps = on; }
 void *attached_model(const jacc_ctx *c) { return c->model; }
 std::map<std::vector<int64_t>, jacc_config> &tuned_picks(jacc_ctx *c) { return c->tuned; }
 const char *tune_db(const jacc_ctx *c) { return c->tune_db.c_str(); }

@@ -279,11 +279,14 @@ int make_replica(jacc_ctx *c, const jacc_arg *args, int K, Replica &r) {
 // between the two scratch arrays, replayed `warmup` times untimed and
 // `reps` times timed; ms receives the per-sweep time of each replay (the
 // graph launch's own cost spread over the sweeps, so that small loops are
-// not timed as launch overhead).
+// not timed as launch overhead).  Persistent sweeps are not chained into common
+// launches: that would time another loop, one that steps back and forth, and
+// made the tuner prefer any persistent candidate.
 int time_candidate(jacc_ctx *c, int kind, const jacc_bounds *b, const jacc_arg *args, const double *scalars,
                    int nscalars, const jacc_config &cfg, int warmup, int reps, int sweeps, std::vector<double> &ms) {
     int rc = jacc_batch_begin(c);
     if (rc) return rc;
+    jr::single_steps(c, true);
     jacc_arg back[2] = {args[0], args[1]};  // the reverse sweep: out read, in written
     back[0].host = args[1].host;
     back[1].host = args[0].host;
@@ -291,6 +294,7 @@ int time_candidate(jacc_ctx *c, int kind, const jacc_bounds *b, const jacc_arg *
         rc = jacc_parallel_loop(c, kind, b, 2, (k & 1) ? back : args, scalars, nscalars, -1, nullptr, &cfg);
     int g = -1;
     const int rc_end = jacc_batch_end(c, &g);
+    jr::single_steps(c, false);
     if (!rc) rc = rc_end;
     ms.assign((size_t)reps, 0.0);
     if (!rc) rc = jacc_batch_time(c, g, warmup, reps, ms.data());
