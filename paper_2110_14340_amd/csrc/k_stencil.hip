@@ -256,7 +256,9 @@ __device__ __forceinline__ void jacobi_tile(const double *__restrict__ in, doubl
 }
 
 // Tile counts and indices stay below 2^31 (a grid's limit), where a division
-// takes a tenth of the instructions of a 64-bit one.
+// takes a tenth of the instructions of a 64-bit one.  The plain Jacobi kernel
+// keeps the longer one: with this its workgroups start closer together and an
+// 8192^2 sweep took 174.5 us instead of 170.7.
 __device__ __forceinline__ int64_t div32(int64_t a, int64_t b) { return (uint32_t)a / (uint32_t)b; }
 __device__ __forceinline__ int64_t mod32(int64_t a, int64_t b) { return (uint32_t)a % (uint32_t)b; }
 
@@ -278,7 +280,7 @@ jacobi2d_kernel(const double *__restrict__ in, double *__restrict__ out, int64_t
                 int64_t tiles, int order, int64_t own_lo, int64_t own_hi) {
     const int64_t t = tile_of(order, tiles);
     if (t < 0) return;
-    jacobi_tile<V, MM, NT>(in, out, nx, pitch, r_lo, r_hi, c_lo, c_hi, col0, tile, march, mir, mod32(t, gx), div32(t, gx), threadIdx.x,
+    jacobi_tile<V, MM, NT>(in, out, nx, pitch, r_lo, r_hi, c_lo, c_hi, col0, tile, march, mir, t % gx, t / gx, threadIdx.x,
                      threadIdx.y, blockDim.x, blockDim.y, own_lo, own_hi);
 }
 
