@@ -180,9 +180,10 @@ typedef struct {
  *              SpMV bound, and the same bits for every partition count.  It
  *              is the default when x has at least 2^20 elements, except
  *              inside batches, which capture the plain form (an explicit
- *              order 4 there returns JACC_ERR_UNSUPPORTED); where the device
- *              memory of the copy (20 bytes an entry) is not to be had, the
- *              plain form runs.
+ *              order 4 there returns JACC_ERR_UNSUPPORTED).  The plain form
+ *              runs instead, also with order 4, where several partitions do
+ *              not declare col, val and x whole, or where the device memory
+ *              of the copy (20 bytes an entry) is not to be had.
  *   vec        1 or 2 consecutive FP64 elements per lane (2 needs an even row
  *              length; the default takes two in rows of either parity)
  *   persistent 1 = run the loop inside the batched persistent kernel

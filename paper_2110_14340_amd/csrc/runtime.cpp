@@ -1364,17 +1364,35 @@ int bin_cache(jacc_ctx *c, Array **arr, int p, const jk::Launch *L, int n, BinCa
     return JACC_OK;
 }
 
+// What a loop call did, for its JACC_LOG record.
+struct LoopNote {
+    int K = 0, nrun = 0;
+    bool packed = false;
+    jk::Cfg cfg{};
+    double cells = 0;  // iterations of the box
+    double work = 0;   // algorithmic bytes (flop for GEMM); 0 where none is defined
+    bool flop = false;
+    hipEvent_t e0 = nullptr, e1 = nullptr;  // around the loop's work on its one stream
+};
+
 // Issues the products of launches L[0..n) as stream s's next op: binned, after
-// the last product that used the copy's buffers, or plain.
-int issue_spmv(jacc_ctx *c, Array **arr, int p, const jk::Launch *L, int n, int s) {
+// the last product that used the copy's buffers, or plain.  The binned form
+// reads x by whole column blocks and a packed one takes col, val and x from the
+// first partition, so over several partitions it needs these arguments whole:
+// a matrix whose x is entered with a halo runs the plain form, which touches
+// the referenced elements of each partition's own slabs only.
+int issue_spmv(jacc_ctx *c, Array **arr, const jacc_arg *args, int p, const jk::Launch *L, int n, int s,
+               LoopNote *note) {
     BinCache *bc = nullptr;
-    int rc = bin_cache(c, arr, p, L, n, &bc);
+    int rc = JACC_OK;
+    if (arr[0]->K == 1 || (args[1].whole && args[2].whole && args[3].whole)) rc = bin_cache(c, arr, p, L, n, &bc);
     if (rc) return rc;
     if (!bc) {
         for (int k = 0; k < n; ++k) {
             jk::Launch P = L[k];
             P.cfg = jk::default_config(JACC_LOOP_SPMV_CSR, P, jk::Cfg{});
             P.cfg.tile = jk::spmv_lanes(arr[1]->E, arr[0]->E - 1);
+            if (note) note->cfg = P.cfg;
             if (live(c)) HIPCHK(c, jk::launch_loop(P, c->st[s].s), "kernel launch");
         }
         return JACC_OK;
@@ -1389,17 +1407,6 @@ int issue_spmv(jacc_ctx *c, Array **arr, int p, const jk::Launch *L, int n, int 
     bc->last = {s, c->st[s].seq + 1};
     return JACC_OK;
 }
-
-// What a loop call did, for its JACC_LOG record.
-struct LoopNote {
-    int K = 0, nrun = 0;
-    bool packed = false;
-    jk::Cfg cfg{};
-    double cells = 0;  // iterations of the box
-    double work = 0;   // algorithmic bytes (flop for GEMM); 0 where none is defined
-    bool flop = false;
-    hipEvent_t e0 = nullptr, e1 = nullptr;  // around the loop's work on its one stream
-};
 
 int loop_impl(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const jacc_arg *args, const double *scalars,
               int nscalars, int slot, double *red_host, const jacc_config *cfg, LoopNote *note = nullptr) {
@@ -1749,7 +1756,7 @@ int loop_impl(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const jacc
             return set_err(c, JACC_ERR_DEVICE, "injected fault in launch %lld", (long long)c->fault_count);
         }
         if (kind == JACC_LOOP_SPMV_CSR) {
-            rc = lps.empty() ? JACC_OK : issue_spmv(c, arr, -1, lps.data(), (int)lps.size(), s);
+            rc = lps.empty() ? JACC_OK : issue_spmv(c, arr, args, -1, lps.data(), (int)lps.size(), s, note);
             if (rc) return rc;
         } else if (live(c)) {
             HIPCHK(c,
@@ -1884,7 +1891,7 @@ int loop_impl(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const jacc
         const bool timed = c->time_parts && live(c) && p < kMaxK;
         if (timed) HIPCHK(c, hipEventRecord(c->kev[2 * p], c->st[s].s), "hipEventRecord");
         if (kind == JACC_LOOP_SPMV_CSR && LP.cfg.order == 4) {
-            rc = issue_spmv(c, arr, p, &LP, 1, s);
+            rc = issue_spmv(c, arr, args, p, &LP, 1, s, note);
             if (rc) return rc;
         } else if (live(c) && waits) {
             c->mloops.push_back(LP);

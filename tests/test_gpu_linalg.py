@@ -348,3 +348,41 @@ def test_plain_spmv_lanes_follow_the_mean_row_length(lanes, per_row):
     assert np.array_equal(y, _spmv_dev(rp, col, val, x, 1, jacc.config(tile=lanes, order=2)))
     assert np.array_equal(y, _spmv_dev(rp, col, val, x, 3))
     assert np.all(np.abs(y - oracle.spmv_csr(rp, col, val, x)) <= 1e-13 * _row_bound(rp, col, val, x))
+
+
+@pytest.mark.parametrize("flags", [0, jacc.INIT_NO_PACK])
+def test_banded_matrix_with_a_halo_x(flags):
+    """2^20 rows of up to 5 neighbours with x entered with a halo: every
+    partition reads its own slab, so a second product after x changed by a
+    loop of the partitions is that of the new x (by default and with order 4,
+    K = 1 and 4)."""
+    say(f"banded matrix, halo x, flags={flags}")
+    n = (1 << 20) + 3
+    cols = np.arange(n)[:, None] + np.arange(-2, 3)[None, :]
+    keep = (cols >= 0) & (cols < n)
+    rp = np.concatenate([[0], np.cumsum(keep.sum(axis=1))]).astype(np.int32)
+    col = cols[keep].astype(np.int32)
+    val = inputs.uniform(col.size, seed=41, lo=-1.0, hi=1.0)
+    x0 = inputs.uniform(n, seed=42, lo=-1.0, hi=1.0)
+    ref1 = oracle.spmv_csr(rp, col, val, x0)
+    ref2 = oracle.spmv_csr(rp, col, val, ref1)
+    bound1 = 1e-13 * _row_bound(rp, col, val, x0)
+    # the second product's error carries the first's through |A|
+    bound2 = 1e-13 * _row_bound(rp, col, val, ref1) + oracle.spmv_csr(rp, col, np.abs(val), bound1)
+    for K in (1, 4):
+        for cfg in (None, jacc.config(order=4)):
+            x, y = x0.copy(), np.zeros(n)
+            with context(K, flags) as c:
+                c.enter(rp, halo=(1, 1))
+                for a in (col, val):
+                    c.enter(a, whole=True)
+                c.enter(x, halo=(2, 2))
+                c.enter(y, halo=(2, 2), clause=jacc.CREATE)
+                for src, dst in ((x, y), (y, x)):
+                    c.loop(jacc.SPMV_CSR, jacc.bounds((0, n)),
+                           [(rp, jacc.READ, 0, 1, 0), (col, jacc.READ, 0, 0, 1), (val, jacc.READ, 0, 0, 1),
+                            (src, jacc.READ, -2, 2, 0), (dst, jacc.WRITE, 0, 0, 0)], cfg=cfg)
+                c.exit(y)
+                c.exit(x)
+            assert np.all(np.abs(y - ref1) <= bound1), K
+            assert np.all(np.abs(x - ref2) <= bound2), K

@@ -1154,3 +1154,30 @@ def test_packed_loop_events_recorded_only_when_waited_on():
     assert all(t["seq"] == last_sweep for t in waits)  # no GEMM partition waits for another's kernel
     assert race_check(tr) == []
     assert freshness_check(tr) == []
+
+
+@pytest.mark.parametrize("whole,order", [(True, 4), (False, 2)])
+@pytest.mark.parametrize("cfg", [None, jacc.config(order=4)])
+def test_binned_spmv_needs_its_arguments_whole(whole, order, cfg, monkeypatch, tmp_path):
+    """A product over several partitions whose x is entered with a halo (a
+    banded matrix) runs the plain form, by default and with order 4: the
+    binned form reads x in whole column blocks, outside a slab's rows.  The
+    record names the form that ran."""
+    import json
+    path = tmp_path / "loops.jsonl"
+    monkeypatch.setenv("JACC_LOG", str(path))
+    n = 1 << 20
+    rp, col, val = np.zeros(n + 1, np.int32), np.zeros(4 * n, np.int32), np.zeros(4 * n)
+    rp[:] = np.arange(n + 1) * 4
+    x, y = np.zeros(n), np.zeros(n)
+    c = jacc.Context(4, flags=jacc.INIT_DRYRUN)
+    c.enter(rp, halo=(1, 1))
+    for a in (col, val):
+        c.enter(a, whole=jacc.SHARED)
+    c.enter(x, **({"whole": True} if whole else {"halo": (2, 2)}))
+    c.enter(y, clause=jacc.CREATE)
+    args = [(rp, jacc.READ, 0, 1, 0), (col, jacc.READ, 0, 0, 1), (val, jacc.READ, 0, 0, 1),
+            (x, jacc.READ, 0, 0, 1) if whole else (x, jacc.READ, -2, 2, 0), (y, jacc.WRITE, 0, 0, 0)]
+    c.loop(jacc.SPMV_CSR, jacc.bounds((0, n)), args, cfg=cfg)
+    c.close()
+    assert json.loads(path.read_text().splitlines()[-1])["cfg"]["order"] == order
