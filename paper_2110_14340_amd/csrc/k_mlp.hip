@@ -22,6 +22,7 @@
 // predictions of 20,000 samples 205 and 80 us, of 30 samples 165 and 35 us.
 #include "k_common.h"
 #include "kernels.h"
+#include "mlp_walk.h"
 
 namespace jk {
 
@@ -50,8 +51,8 @@ __host__ __device__ inline Off offsets(int F) {
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));  // in memory: any float address
 
-constexpr int kTile = 16;       // samples of a workgroup's tile
-constexpr int kThreads = 256;   // 4 waves, wave w computing outputs 16w .. 16w+15 of a layer
+constexpr int kTile = kMlpTile;        // samples of a workgroup's tile
+constexpr int kThreads = kMlpThreads;  // 4 waves, wave w computing outputs 16w .. 16w+15 of a layer
 // LDS row strides: 4 floats past a multiple of 16, so the 16 rows that a
 // quarter of a wave reads 16 bytes of lie in different banks
 constexpr int SX = kMlpMaxFeatures + 4;
@@ -144,13 +145,13 @@ mlp_tile_kernel(const float *__restrict__ params, const float *__restrict__ mu, 
 
     const int fs = tid >> 4, ff = tid & 15;  // the sample and feature this thread stages
     const float fmu = ff < F ? mu[ff] : 0.f, fsd = ff < F ? sd[ff] : 1.f;
-    for (int base = blockIdx.x * kTile; base < n; base += gridDim.x * kTile) {
-        const int b = base + fs;
+    for (int64_t base = mlp_first(blockIdx.x); base < n; base = mlp_next(base, gridDim.x)) {
+        const int64_t b = base + fs;
         float xv = 0.f;
-        if (b < n && ff < F) xv = (X[(int64_t)(idx ? idx[b] : b) * F + ff] - fmu) / fsd;
+        if (b < n && ff < F) xv = (X[(idx ? idx[b] : b) * F + ff] - fmu) / fsd;
         xs[fs * SX + ff] = xv;
         __syncthreads();
-        const int valid = n - base - 4 * q;  // rows r < valid of this lane's four are samples
+        const int valid = (int)(n - base < kTile ? n - base : kTile) - 4 * q;  // rows r < valid of this lane's four are samples
         const f4 h1r = relu(mma16(*reinterpret_cast<const f4 *>(&xs[c * SX + 4 * q]), w1, f4{b1, b1, b1, b1}), valid);
         put(h1, q, o, h1r);
         __syncthreads();
@@ -304,7 +305,6 @@ Adam adam_args(const MlpBufs &B, int t, float lr) {
     return {B.params, B.m, B.v, lr, (float)(1.0 - pow((double)0.9f, t)), (float)(1.0 - pow((double)0.999f, t))};
 }
 
-unsigned tiles_of(int n) { return (unsigned)((n + kTile - 1) / kTile); }
 unsigned param_blocks(int P) { return (unsigned)((P + kThreads - 1) / kThreads); }
 
 }  // namespace
@@ -314,14 +314,14 @@ static_assert(kMlpGroups <= kWave, "one wave sums the groups' squared errors");
 int mlp_nparams(int F) { return offsets(F).P; }
 
 hipError_t mlp_forward(const MlpBufs &B, const float *X, int n, float *yhat, hipStream_t s) {
-    hipLaunchKernelGGL(mlp_tile_kernel<false>, dim3(tiles_of(n)), dim3(kThreads), 0, s, B.params, B.mu, B.sd, X,
+    hipLaunchKernelGGL(mlp_tile_kernel<false>, dim3(mlp_groups(n, kMlpMaxForward)), dim3(kThreads), 0, s, B.params, B.mu, B.sd, X,
                        (const int *)nullptr, (const float *)nullptr, n, B.F, yhat, (float *)nullptr, (double *)nullptr);
     return hipGetLastError();
 }
 
 hipError_t mlp_train(const MlpBufs &B, const float *X, const float *y, const int *idx, int n, int t, float lr,
                      float *loss, hipStream_t s) {
-    const unsigned tiles = tiles_of(n), groups = tiles < (unsigned)kMlpGroups ? tiles : (unsigned)kMlpGroups;
+    const unsigned groups = mlp_groups(n, kMlpGroups);
     hipLaunchKernelGGL(mlp_tile_kernel<true>, dim3(groups), dim3(kThreads), 0, s, B.params, B.mu, B.sd, X, idx, y, n, B.F,
                        (float *)nullptr, B.part, B.sqerr);
     const hipError_t e = hipGetLastError();

@@ -166,3 +166,22 @@ def test_training_steps_equal_gradients_and_adam_steps():
         m.close()
     for k in P:
         assert np.array_equal(fitted[k], stepped[k]), k
+
+
+@pytest.mark.parametrize("n", [(1 << 24) + 17, (1 << 30) + 33])
+def test_predict_past_a_launch_of_one_tile_a_workgroup(n):
+    """More samples than a forward launch has workgroups for (2^24), and more
+    than 2^30: each prediction has the bits it has among few samples."""
+    say(f"mlp predict n={n}")
+    X, _, P = _problem(1, 4096, seed=9)
+    with context(1) as c:
+        m = jacc.Model(c, 1)
+        m.set_params(P)
+        ref = m.predict(X)
+        big = np.resize(X, (n, 1))
+        say("  inputs made")
+        got = m.predict(big)
+        m.close()
+    full = n // 4096 * 4096
+    assert np.all(got[:full].reshape(-1, 4096) == ref)
+    assert np.array_equal(got[full:], ref[:n - full])
