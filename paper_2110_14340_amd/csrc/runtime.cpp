@@ -294,6 +294,7 @@ struct Batch {
     // arrays whose device slabs the graph's nodes address; when one of them
     // leaves the data region the graph is stale and is never replayed again
     std::vector<int> array_ids;
+    std::vector<int> written_ids;  // those its loops write
     bool stale = false;
     jk::PTask *dev_tasks = nullptr;   // kTaskCapacity device task records, then kMergeCapacity of merged loops
     jk::PTask *host_tasks = nullptr;  // pinned staging of the same size
@@ -1466,9 +1467,13 @@ int loop_impl(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const jacc
         if (rc) return rc;
     }
     if (c->cur && !c->plan_only) {
-        for (int i = 0; i < nargs; ++i)
-            if (std::find(c->cur->array_ids.begin(), c->cur->array_ids.end(), arr[i]->id) == c->cur->array_ids.end())
-                c->cur->array_ids.push_back(arr[i]->id);
+        auto once = [](std::vector<int> &ids, int id) {
+            if (std::find(ids.begin(), ids.end(), id) == ids.end()) ids.push_back(id);
+        };
+        for (int i = 0; i < nargs; ++i) {
+            once(c->cur->array_ids, arr[i]->id);
+            if (args[i].mode & JACC_WRITE) once(c->cur->written_ids, arr[i]->id);
+        }
         LoopCall lc;
         lc.kind = kind;
         lc.b = *b;
@@ -2154,7 +2159,16 @@ int replan(jacc_ctx *c, Batch *B, std::vector<jacc_trace_op> *log) {
     return rc;
 }
 
+// Before a replay of B: binned copies of a matrix that it writes are built
+// again at their next product (a replay plans no writes, so versions stay).
+void note_replay(jacc_ctx *c, const Batch *B) {
+    for (BinCache &bc : c->bins)
+        for (int id : {bc.rp_id, bc.col_id, bc.val_id})
+            if (std::find(B->written_ids.begin(), B->written_ids.end(), id) != B->written_ids.end()) bc.built = false;
+}
+
 int launch_graph(jacc_ctx *c, Batch *B, int repeats) {
+    note_replay(c, B);
     int rc = join_into0(c);
     if (rc) return rc;
     if (live(c))
@@ -2761,6 +2775,7 @@ int jacc_batch_time(jacc_ctx *c, int graph_id, int warmup, int reps, double *ms)
     int rc = jacc_batch_launch(c, graph_id, warmup);
     if (rc) return rc;
     Batch *B = c->batches[graph_id];
+    note_replay(c, B);
     rc = join_into0(c);
     if (rc) return rc;
     for (int r = 0; r < reps; ++r) {

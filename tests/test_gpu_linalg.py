@@ -386,3 +386,35 @@ def test_banded_matrix_with_a_halo_x(flags):
                 c.exit(x)
             assert np.all(np.abs(y - ref1) <= bound1), K
             assert np.all(np.abs(x - ref2) <= bound2), K
+
+
+@pytest.mark.parametrize("timed", [False, True])
+def test_binned_copy_follows_values_written_by_a_graph(timed):
+    """A graph that writes the matrix's values is replayed between products:
+    each product is that of the values the replay left (launched, and timed
+    without a warm-up launch)."""
+    say(f"binned copy and graph replays timed={timed}")
+    n = 3000
+    rp, col, val, x = inputs.csr_matrix(n, n, 8, seed=51)
+    src = inputs.uniform(val.size, seed=52, lo=-1.0, hi=1.0)
+    idx = np.arange(val.size, dtype=np.int32)
+    y = np.zeros(n)
+    cfg = jacc.config(order=4)
+    with context(1) as c:
+        for a in (rp, col, val, x, src, idx):
+            c.enter(a, whole=a is src or a is idx)
+        c.enter(y, clause=jacc.CREATE)
+        c.batch_begin()
+        c.scatter_sq(src, idx, val)
+        g = c.batch_end()
+        c.spmv(rp, col, val, x, y, cfg=cfg)
+        for step in range(3):
+            src[:] = inputs.uniform(val.size, seed=60 + step, lo=-1.0, hi=1.0)
+            c.update(src, jacc.UPDATE_DEVICE)
+            c.batch_time(g, warmup=0, reps=1) if timed else c.batch_launch(g)
+            c.spmv(rp, col, val, x, y, cfg=cfg)
+            c.update(y, jacc.UPDATE_HOST)
+            now = oracle.scatter_sq(src, idx, val.copy())
+            ref = oracle.spmv_csr(rp, col, now, x)
+            assert np.all(np.abs(y - ref) <= 1e-13 * _row_bound(rp, col, now, x)), step
+        c.exit(y)
