@@ -311,6 +311,7 @@ struct BinCache {
     int64_t lo = 0, hi = 0;
     uint64_t v_rp = 0, v_col = 0, v_val = 0;
     bool built = false;
+    bool refused = false;  // its memory was not to be had: not asked for again until the matrix changes
     SeqRef last;
     jk::BinBufs bb{};
 };
@@ -1331,18 +1332,24 @@ int bin_cache(jacc_ctx *c, Array **arr, int p, const jk::Launch *L, int n, BinCa
     Array *rp = arr[0], *col = arr[1], *val = arr[2];
     *out = nullptr;
     const int64_t lo = L[0].lo[0], hi = L[n - 1].hi[0];
-    for (BinCache &bc : c->bins)
+    for (size_t i = 0; i < c->bins.size(); ++i) {
+        BinCache &bc = c->bins[i];
         if (bc.rp_id == rp->id && bc.col_id == col->id && bc.val_id == val->id && bc.p == p && bc.K == n && bc.lo == lo &&
             bc.hi == hi && bc.bb.ncols == arr[3]->E) {
             if (bc.v_rp != rp->version || bc.v_col != col->version || bc.v_val != val->version) {
+                if (bc.refused) {
+                    c->bins.erase(c->bins.begin() + (long)i);
+                    break;
+                }
                 bc.built = false;
                 bc.v_rp = rp->version;
                 bc.v_col = col->version;
                 bc.v_val = val->version;
             }
-            *out = &bc;
+            if (!bc.refused) *out = &bc;
             return JACC_OK;
         }
+    }
     BinCache bc;
     if (!jk::bin_geometry(arr[3]->E, col->E, rp->E - 1, L, n, &bc.bb)) return JACC_OK;
     bc.rp_id = rp->id;
@@ -1355,13 +1362,16 @@ int bin_cache(jacc_ctx *c, Array **arr, int p, const jk::Launch *L, int n, BinCa
     bc.v_rp = rp->version;
     bc.v_col = col->version;
     bc.v_val = val->version;
-    for (int i = 0; i < jk::kBinBuffers; ++i)
+    const std::string err = c->err;
+    for (int i = 0; i < jk::kBinBuffers && !bc.refused; ++i)
         if (dev_alloc(c, bc.bb.bytes[i], &bc.bb.mem[i])) {
             for (int j = 0; j < i; ++j) dev_free(c, bc.bb.mem[j]);
-            return JACC_OK;
+            std::fill(bc.bb.mem, bc.bb.mem + jk::kBinBuffers, nullptr);
+            bc.refused = true;
+            c->err = err;  // the call goes on with the plain form
         }
     c->bins.push_back(bc);
-    *out = &c->bins.back();
+    if (!bc.refused) *out = &c->bins.back();
     return JACC_OK;
 }
 

@@ -418,3 +418,39 @@ def test_binned_copy_follows_values_written_by_a_graph(timed):
             ref = oracle.spmv_csr(rp, col, now, x)
             assert np.all(np.abs(y - ref) <= 1e-13 * _row_bound(rp, col, now, x)), step
         c.exit(y)
+
+
+class _NoCopyMemory(jacc.TorchAllocator):
+    """PyTorch memory, refused while `refuse` is set."""
+    refuse = False
+
+    def _alloc(self, nbytes, user):
+        return None if self.refuse else super()._alloc(nbytes, user)
+
+
+@pytest.mark.parametrize("K", [1, 4])
+@pytest.mark.parametrize("case", ["no_memory", "long_mean_row"])
+def test_binned_product_falls_back_to_the_plain_form(case, K):
+    """Without memory for the copy, and for a mean row longer than a row block
+    holds, order 4 runs the plain form: its bits, and no error left behind."""
+    say(f"binned fallback {case} K={K}")
+    n, d = (4000, 12) if case == "no_memory" else (9, 11000)
+    rp, col, val, x = _rows_matrix(np.full(n, d), 20000, seed=71)
+    ys = []
+    for cfg in (jacc.config(order=2), jacc.config(order=4)):
+        mem = _NoCopyMemory()
+        y = np.zeros(n)
+        with jacc.Context(K, streams="torch", allocator=mem) as c:
+            c.enter(rp, halo=(1, 1))
+            for a in (col, val, x):
+                c.enter(a, whole=True)
+            c.enter(y, clause=jacc.CREATE)
+            mem.refuse = case == "no_memory"
+            for _ in range(2):
+                c.spmv(rp, col, val, x, y, cfg=cfg)
+            assert c.last_error() == ""
+            mem.refuse = False
+            c.exit(y)
+        ys.append(y)
+    assert np.array_equal(ys[0], ys[1])
+    assert np.all(np.abs(ys[0] - oracle.spmv_csr(rp, col, val, x)) <= 1e-13 * _row_bound(rp, col, val, x))

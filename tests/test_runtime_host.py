@@ -1181,3 +1181,67 @@ def test_binned_spmv_needs_its_arguments_whole(whole, order, cfg, monkeypatch, t
     c.loop(jacc.SPMV_CSR, jacc.bounds((0, n)), args, cfg=cfg)
     c.close()
     assert json.loads(path.read_text().splitlines()[-1])["cfg"]["order"] == order
+
+
+class _Refusing:
+    """Allocator that hands out distinct addresses and, while `refuse` is set,
+    refuses every request, counting them."""
+
+    def __init__(self):
+        self.refuse, self.refused, self.next, self.held = False, 0, 1 << 44, {}
+        self._a, self._f = jacc.Allocator.ALLOC(self._alloc), jacc.Allocator.FREE(self._free)
+        self.struct = jacc.Allocator(self._a, self._f, None)
+
+    def _alloc(self, nbytes, user):
+        if self.refuse:
+            self.refused += 1
+            return None
+        self.next += (nbytes + 4095) // 4096 * 4096
+        self.held[self.next] = nbytes
+        return self.next
+
+    def _free(self, ptr, user):
+        del self.held[ptr]
+
+
+def _dry_product(c, rp, col, val, x, y, K=0):
+    c.enter(rp, halo=(1, 1), K=K)
+    for a in (col, val, x):
+        c.enter(a, whole=jacc.SHARED, K=K)
+    c.enter(y, clause=jacc.CREATE, K=K)
+
+
+@pytest.mark.parametrize("K", [1, 4])
+def test_binned_copy_without_memory_is_asked_for_once(K, monkeypatch, tmp_path):
+    """A product whose binned copy gets no memory succeeds as the plain form,
+    says so in its record, leaves the context's last error as it was, and
+    later products do not ask again until the matrix changes."""
+    import json
+    path = tmp_path / "loops.jsonl"
+    monkeypatch.setenv("JACC_LOG", str(path))
+    mem = _Refusing()
+    c = jacc.Context(K, allocator=mem, flags=jacc.INIT_DRYRUN)
+    n = 4000
+    rp = (np.arange(n + 1) * 8).astype(np.int32)
+    col, val, x, y = np.zeros(8 * n, np.int32), np.zeros(8 * n), np.zeros(n), np.zeros(n)
+    _dry_product(c, rp, col, val, x, y)
+    assert c.spmv(rp, col, val, y, y, raw=True) != jacc.OK
+    before, held = c.last_error(), dict(mem.held)
+    mem.refuse = True
+    cfg = jacc.config(order=4)
+    for _ in range(3):
+        c.spmv(rp, col, val, x, y, cfg=cfg)
+    assert mem.refused == 1 and c.last_error() == before and mem.held == held
+    c.update(val, jacc.UPDATE_DEVICE)
+    c.spmv(rp, col, val, x, y, cfg=cfg)
+    assert mem.refused == 2 and mem.held == held
+    mem.refuse = False
+    c.spmv(rp, col, val, x, y, cfg=cfg)
+    assert mem.held == held
+    c.update(val, jacc.UPDATE_DEVICE)
+    c.spmv(rp, col, val, x, y, cfg=cfg)
+    assert len(mem.held) > len(held)
+    c.close()
+    assert not mem.held
+    orders = [json.loads(line)["cfg"]["order"] for line in path.read_text().splitlines()]
+    assert orders == [2, 2, 2, 2, 2, 4]
