@@ -183,7 +183,10 @@ typedef struct {
  *              order 4 there returns JACC_ERR_UNSUPPORTED).  The plain form
  *              runs instead, also with order 4, where several partitions do
  *              not declare col, val and x whole, or where the device memory
- *              of the copy (20 bytes an entry) is not to be had.
+ *              of the copy is not to be had: 20 bytes for each entry of the
+ *              rows multiplied and 6 for each pair of a row block and a
+ *              column block.  The copies of one matrix (by partitions or
+ *              boxes of rows) hold its entries at most twice.
  *   vec        1 or 2 consecutive FP64 elements per lane (2 needs an even row
  *              length; the default takes two in rows of either parity)
  *   persistent 1 = run the loop inside the batched persistent kernel

@@ -480,7 +480,7 @@ int spmv_lanes(int64_t nnz, int64_t rows) {
     return mean > 8 ? 16 : mean > 4 ? 8 : 4;
 }
 
-bool bin_geometry(int64_t ncols, int64_t nnz, int64_t rows, const Launch *L, int n, BinBufs *bb) {
+bool bin_geometry(int64_t ncols, int64_t nnz, int64_t rows, int64_t entries, const Launch *L, int n, BinBufs *bb) {
     *bb = BinBufs{};
     // the histogram of column blocks takes 4 bytes of LDS each (128 KB); row
     // blocks are sized by the mean row length of the whole matrix, and so are
@@ -499,9 +499,9 @@ bool bin_geometry(int64_t ncols, int64_t nnz, int64_t rows, const Launch *L, int
         const int64_t r = L[k].hi[0] - L[k].lo[0];
         if (r > 0) nblk += (r + rb - 1) / rb;
     }
-    if (nblk > (1 << 24) || nnz + (int64_t)kPad * bb->nc > INT32_MAX) return false;
+    if (nblk > (1 << 24) || entries + (int64_t)kPad * bb->nc > INT32_MAX) return false;
     bb->nblk = (int)nblk;
-    const size_t cells = (size_t)nblk * bb->nc, cap = (size_t)nnz + (size_t)kPad * bb->nc;
+    const size_t cells = (size_t)nblk * bb->nc, cap = (size_t)entries + (size_t)kPad * bb->nc;
     const size_t bytes[kBinBuffers] = {cells * 4, cells * 2, (size_t)(bb->nc + 1) * 4, (size_t)kSegments * bb->nc * 4,
                                        cap * 8,   cap * 2,   cap * 2,                  cap * 8};
     for (int i = 0; i < kBinBuffers; ++i) bb->bytes[i] = bytes[i];

@@ -241,9 +241,10 @@ struct BinBufs {
 // Lanes per row by the mean row length of the whole matrix (not by
 // partition: the lanes decide the order of a row's sum).
 int spmv_lanes(int64_t nnz, int64_t rows);
-// Geometry and buffer sizes for a matrix of `rows` rows and `nnz` entries (false:
-// this form does not take it).  The launches are the partitions' rows.
-bool bin_geometry(int64_t ncols, int64_t nnz, int64_t rows, const Launch *L, int n, BinBufs *bb);
+// Geometry for a matrix of `rows` rows and `nnz` entries, and the buffer sizes of
+// a copy of the launches' rows, which hold `entries` of them (false: this form
+// does not take the matrix).
+bool bin_geometry(int64_t ncols, int64_t nnz, int64_t rows, int64_t entries, const Launch *L, int n, BinBufs *bb);
 // Both read col, val and x through the first launch's arguments (every
 // partition's replica holds the same values).
 hipError_t build_bins(const Launch *L, int n, const BinBufs &bb, hipStream_t s);

@@ -312,6 +312,8 @@ struct BinCache {
     uint64_t v_rp = 0, v_col = 0, v_val = 0;
     bool built = false;
     bool refused = false;  // its memory was not to be had: not asked for again until the matrix changes
+    int64_t entries = 0;   // it has room for
+    uint64_t used = 0;     // c->tick of its last product
     SeqRef last;
     jk::BinBufs bb{};
 };
@@ -1323,35 +1325,93 @@ int prepare_loop(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const j
     return JACC_OK;
 }
 
+// Gives a binned copy's memory back, after its last product.
+int drop_bin(jacc_ctx *c, size_t i) {
+    BinCache &bc = c->bins[i];
+    if (bc.last.seq > 0 && live(c)) HIPCHK(c, hipStreamSynchronize(c->st[bc.last.s].s), "hipStreamSynchronize");
+    for (void *m : bc.bb.mem) dev_free(c, m);
+    c->bins.erase(c->bins.begin() + (long)i);
+    return JACC_OK;
+}
+
+// Entries of the rows of launches L[0..n): those of the matrix for all its
+// rows, else by row_ptr on the device, read after stream s's copies to it.
+int bin_entries(jacc_ctx *c, Array **arr, const jk::Launch *L, int n, int s, int64_t *out) {
+    const int64_t lo = L[0].lo[0], hi = L[n - 1].hi[0];
+    *out = arr[1]->E;
+    if (lo == 0 && hi == arr[0]->E - 1) return JACC_OK;
+    int32_t ends[2];
+    if (live(c)) {
+        const int32_t *first = (const int32_t *)L[0].a[0].ptr + lo, *last = (const int32_t *)L[n - 1].a[0].ptr + hi;
+        HIPCHK(c, hipMemcpyAsync(&ends[0], first, 4, hipMemcpyDeviceToHost, c->st[s].s), "hipMemcpyAsync");
+        HIPCHK(c, hipMemcpyAsync(&ends[1], last, 4, hipMemcpyDeviceToHost, c->st[s].s), "hipMemcpyAsync");
+        HIPCHK(c, hipStreamSynchronize(c->st[s].s), "hipStreamSynchronize");
+    } else {  // without a device: the caller's row_ptr
+        const int32_t *rp = (const int32_t *)arr[0]->host;
+        ends[0] = rp[lo];
+        ends[1] = rp[hi];
+    }
+    const int64_t entries = (int64_t)ends[1] - ends[0];
+    *out = entries >= 0 && entries <= arr[1]->E ? entries : -1;
+    return JACC_OK;
+}
+
 // The binned copy of the rows of launches L[0..n) of the CSR matrix in
 // arr[0..2] (row_ptr, col, val) for x = arr[3]: found, marked for a rebuild
 // when the matrix changed since it was built, or allocated.  *out is null
 // when the form does not take the matrix or its memory is not to be had: the
-// caller then runs the plain form.
-int bin_cache(jacc_ctx *c, Array **arr, int p, const jk::Launch *L, int n, BinCache **out) {
+// caller then runs the plain form.  A copy is as large as its rows' entries, and
+// the copies of one matrix together (of its partitions, or of the boxes a
+// program multiplies) hold its entries at most twice: beyond that the one used
+// least recently goes.
+int bin_cache(jacc_ctx *c, Array **arr, int p, const jk::Launch *L, int n, int s, BinCache **out) {
     Array *rp = arr[0], *col = arr[1], *val = arr[2];
     *out = nullptr;
     const int64_t lo = L[0].lo[0], hi = L[n - 1].hi[0];
+    auto same_matrix = [&](const BinCache &bc) {
+        return bc.rp_id == rp->id && bc.col_id == col->id && bc.val_id == val->id;
+    };
+    int64_t entries = -1;
+    int rc = JACC_OK;
     for (size_t i = 0; i < c->bins.size(); ++i) {
         BinCache &bc = c->bins[i];
-        if (bc.rp_id == rp->id && bc.col_id == col->id && bc.val_id == val->id && bc.p == p && bc.K == n && bc.lo == lo &&
-            bc.hi == hi && bc.bb.ncols == arr[3]->E) {
-            if (bc.v_rp != rp->version || bc.v_col != col->version || bc.v_val != val->version) {
-                if (bc.refused) {
-                    c->bins.erase(c->bins.begin() + (long)i);
-                    break;
-                }
-                bc.built = false;
-                bc.v_rp = rp->version;
-                bc.v_col = col->version;
-                bc.v_val = val->version;
-            }
-            if (!bc.refused) *out = &bc;
-            return JACC_OK;
+        if (!same_matrix(bc) || bc.p != p || bc.K != n || bc.lo != lo || bc.hi != hi || bc.bb.ncols != arr[3]->E) continue;
+        const bool changed = bc.v_rp != rp->version || bc.v_col != col->version || bc.v_val != val->version;
+        if (bc.v_rp != rp->version) {
+            rc = bin_entries(c, arr, L, n, s, &entries);
+            if (rc) return rc;
         }
+        if (changed && (bc.refused || entries > bc.entries || (entries < 0 && bc.v_rp != rp->version))) {
+            rc = drop_bin(c, i);
+            if (rc) return rc;
+            break;
+        }
+        if (changed) {
+            bc.built = false;
+            bc.v_rp = rp->version;
+            bc.v_col = col->version;
+            bc.v_val = val->version;
+        }
+        bc.used = c->tick;
+        if (!bc.refused) *out = &bc;
+        return JACC_OK;
     }
     BinCache bc;
-    if (!jk::bin_geometry(arr[3]->E, col->E, rp->E - 1, L, n, &bc.bb)) return JACC_OK;
+    rc = bin_entries(c, arr, L, n, s, &entries);
+    if (rc) return rc;
+    if (entries < 0 || !jk::bin_geometry(arr[3]->E, col->E, rp->E - 1, entries, L, n, &bc.bb)) return JACC_OK;
+    for (;;) {
+        int64_t held = entries;
+        size_t oldest = c->bins.size();
+        for (size_t i = 0; i < c->bins.size(); ++i) {
+            if (!same_matrix(c->bins[i]) || c->bins[i].refused) continue;
+            held += c->bins[i].entries;
+            if (oldest == c->bins.size() || c->bins[i].used < c->bins[oldest].used) oldest = i;
+        }
+        if (held <= 2 * col->E || oldest == c->bins.size()) break;
+        rc = drop_bin(c, oldest);
+        if (rc) return rc;
+    }
     bc.rp_id = rp->id;
     bc.col_id = col->id;
     bc.val_id = val->id;
@@ -1362,6 +1422,8 @@ int bin_cache(jacc_ctx *c, Array **arr, int p, const jk::Launch *L, int n, BinCa
     bc.v_rp = rp->version;
     bc.v_col = col->version;
     bc.v_val = val->version;
+    bc.entries = entries;
+    bc.used = c->tick;
     const std::string err = c->err;
     for (int i = 0; i < jk::kBinBuffers && !bc.refused; ++i)
         if (dev_alloc(c, bc.bb.bytes[i], &bc.bb.mem[i])) {
@@ -1396,7 +1458,7 @@ int issue_spmv(jacc_ctx *c, Array **arr, const jacc_arg *args, int p, const jk::
                LoopNote *note) {
     BinCache *bc = nullptr;
     int rc = JACC_OK;
-    if (arr[0]->K == 1 || (args[1].whole && args[2].whole && args[3].whole)) rc = bin_cache(c, arr, p, L, n, &bc);
+    if (arr[0]->K == 1 || (args[1].whole && args[2].whole && args[3].whole)) rc = bin_cache(c, arr, p, L, n, s, &bc);
     if (rc) return rc;
     if (!bc) {
         for (int k = 0; k < n; ++k) {

@@ -454,3 +454,44 @@ def test_binned_product_falls_back_to_the_plain_form(case, K):
         ys.append(y)
     assert np.array_equal(ys[0], ys[1])
     assert np.all(np.abs(ys[0] - oracle.spmv_csr(rp, col, val, x)) <= 1e-13 * _row_bound(rp, col, val, x))
+
+
+@pytest.mark.parametrize("K", [1, 3])
+def test_binned_products_of_boxes_and_a_changed_row_ptr(K):
+    """Boxes of rows of one matrix (more of them than copies are kept) and a
+    row_ptr that gives a box more and fewer entries: each product is that of
+    the box's rows now, and rows outside it keep their values."""
+    say(f"binned boxes K={K}")
+    n = 6000
+    r = np.random.default_rng(5)
+    lens = [r.integers(0, 9, n), r.integers(0, 9, n), r.integers(0, 9, n)]
+    lens[1][n // 2:] = 0
+    lens[1][:n // 2] = 9
+    lens[1][n // 2] = 1
+    nnz = max(int(x.sum()) for x in lens)
+    rp = np.zeros(n + 1, np.int32)
+    col = r.integers(0, n, nnz).astype(np.int32)
+    val, x = r.standard_normal(nnz), r.random(n)
+    cfg = jacc.config(order=4)
+    boxes = [(k * 1000, k * 1000 + 3000) for k in range(4)] + [(0, n), (17, 18), (2500, 2500)]
+    with context(K) as c:
+        c.enter(rp, halo=(1, 1))
+        for a in (col, val, x):
+            c.enter(a, whole=True)
+        y = np.zeros(n)
+        c.enter(y)
+        for ls in lens:
+            np.cumsum(ls, out=rp[1:])
+            c.update(rp, jacc.UPDATE_DEVICE)
+            ref = oracle.spmv_csr(rp, col, val, x)
+            bound = 1e-13 * _row_bound(rp, col, val, x)
+            for lo, hi in boxes + boxes[::-1]:
+                y[:] = 7.0
+                c.update(y, jacc.UPDATE_DEVICE)
+                c.loop(jacc.SPMV_CSR, jacc.bounds((lo, hi)),
+                       [(rp, jacc.READ, 0, 1, 0), (col, jacc.READ, 0, 0, 1), (val, jacc.READ, 0, 0, 1),
+                        (x, jacc.READ, 0, 0, 1), (y, jacc.WRITE, 0, 0, 0)], cfg=cfg)
+                c.update(y, jacc.UPDATE_HOST)
+                assert np.all(np.abs(y[lo:hi] - ref[lo:hi]) <= bound[lo:hi]), (lo, hi)
+                assert np.all(y[:lo] == 7.0) and np.all(y[hi:] == 7.0)
+        c.exit(y)

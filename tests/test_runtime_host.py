@@ -1245,3 +1245,36 @@ def test_binned_copy_without_memory_is_asked_for_once(K, monkeypatch, tmp_path):
     assert not mem.held
     orders = [json.loads(line)["cfg"]["order"] for line in path.read_text().splitlines()]
     assert orders == [2, 2, 2, 2, 2, 4]
+
+
+def test_binned_copies_are_sized_by_their_rows_and_bounded():
+    """The copies of 20 partitions, and of many boxes of one matrix, each have
+    room for their own rows' entries; together they hold the matrix's entries
+    at most twice, and a box that comes back is still multiplied."""
+    n, K = 40000, 20
+    rp = (np.arange(n + 1) * 8).astype(np.int32)
+    col, val, x, y = np.zeros(8 * n, np.int32), np.zeros(8 * n), np.zeros(n), np.zeros(n)
+    cfg = jacc.config(order=4)
+    # an entry takes 20 bytes; 64 entries align each of the 3 column blocks, and
+    # their scans (64 x 3 counts, a table entry of 6 bytes a row block) are small
+    whole, extra = 20 * 8 * n, 20 * 64 * 3 + 64 * 3 * 4 + 3 * 6 * (n // 900) + 8 * 256
+    mem = _Refusing()
+    c = jacc.Context(K, allocator=mem, flags=jacc.INIT_DRYRUN)
+    _dry_product(c, rp, col, val, x, y)
+    held = sum(mem.held.values())
+    c.spmv(rp, col, val, x, y, cfg=cfg)
+    assert whole <= sum(mem.held.values()) - held <= whole + K * extra
+    c.close()
+    mem = _Refusing()
+    c = jacc.Context(1, allocator=mem, flags=jacc.INIT_DRYRUN)
+    _dry_product(c, rp, col, val, x, y)
+    held = sum(mem.held.values())
+    most = 0
+    for lo in list(range(0, n // 2, 1000)) * 2:
+        c.loop(jacc.SPMV_CSR, jacc.bounds((lo, lo + n // 2)),
+               [(rp, jacc.READ, 0, 1, 0), (col, jacc.READ, 0, 0, 1), (val, jacc.READ, 0, 0, 1),
+                (x, jacc.READ, 0, 0, 1), (y, jacc.WRITE, 0, 0, 0)], cfg=cfg)
+        most = max(most, sum(mem.held.values()) - held)
+    assert most <= 2 * whole + 5 * extra
+    c.close()
+    assert not mem.held
