@@ -1589,7 +1589,7 @@ int loop_impl(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const jacc
     bool packed = !c->cur && !c->no_pack && !c->serialize && !c->time_parts && !c->split && K > 1 &&
                   K <= jk::kMaxPack && !persistent && !dup &&
                   (kind == JACC_LOOP_JACOBI2D || kind == JACC_LOOP_HEAT3D || kind == JACC_LOOP_SUM ||
-                   (kind == JACC_LOOP_SPMV_CSR && L.cfg.order == 4 && L.cfg.rows <= 1)) &&
+                   (kind == JACC_LOOP_SPMV_CSR && L.cfg.order == 4)) &&
                   !(args[primary].mode & JACC_FILTERED) && (P->pdim == 0 || kind == JACC_LOOP_JACOBI2D) &&
                   !P->whole;
     if (packed && want_red) {

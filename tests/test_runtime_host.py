@@ -1278,3 +1278,17 @@ def test_binned_copies_are_sized_by_their_rows_and_bounded():
     assert most <= 2 * whole + 5 * extra
     c.close()
     assert not mem.held
+
+
+@pytest.mark.parametrize("rows", [0, 2, 4])
+def test_binned_spmv_packs_whatever_its_fields_without_effect(rows):
+    n = 64
+    rp, col, val = np.arange(n + 1, dtype=np.int32), np.zeros(n, np.int32), np.ones(n)
+    x, y = np.zeros(n), np.zeros(n)
+    c = dry(4)
+    _dry_product(c, rp, col, val, x, y)
+    c.trace_clear()
+    c.spmv(rp, col, val, x, y, cfg=jacc.config(order=4, tile=1, rows=rows))
+    kern = [t for t in c.trace() if t["op"] == "KERNEL"]
+    assert len(kern) == 4 and len({(t["stream"], t["seq"]) for t in kern}) == 1
+    c.close()
