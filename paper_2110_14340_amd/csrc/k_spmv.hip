@@ -15,6 +15,37 @@ namespace {
 constexpr int kSpmvThreads = 256;
 
 // v of another lane of its row of 16 lanes, by a DPP pattern.
+// Lane g's share of the row [kb, ke): its entries' products added in increasing
+// k.  Eight of them are in flight at once, so that a long row is not one load's
+// latency after the other.  NT: col and val are read once, so they are loaded
+// non-temporally and leave the caches to the gathered x.
+template <bool NT>
+__device__ __forceinline__ double lane_sum(const int32_t *__restrict__ col, const double *__restrict__ val,
+                                           const double *__restrict__ x, int32_t kb, int32_t ke, int g, int G) {
+    constexpr int kAhead = 8;
+    double s = 0.0;
+    int64_t k = (int64_t)kb + g;
+    for (; k + (kAhead - 1) * G < ke; k += kAhead * G) {
+        int32_t c[kAhead];
+        double v[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            c[u] = NT ? __builtin_nontemporal_load(&col[k + u * G]) : col[k + u * G];
+            v[u] = NT ? __builtin_nontemporal_load(&val[k + u * G]) : val[k + u * G];
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) v[u] *= x[c[u]];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) s += v[u];
+    }
+    for (; k < ke; k += G) {
+        const int32_t c = NT ? __builtin_nontemporal_load(&col[k]) : col[k];
+        const double v = NT ? __builtin_nontemporal_load(&val[k]) : val[k];
+        s += v * x[c];
+    }
+    return s;
+}
+
 template <int G, bool NT>
 __global__ void __launch_bounds__(kSpmvThreads)
 spmv_kernel(const int32_t *__restrict__ rp, const int32_t *__restrict__ col, const double *__restrict__ val,
@@ -58,7 +89,7 @@ spmv_kernel(const int32_t *__restrict__ rp, const int32_t *__restrict__ col, con
 // The order inside a bucket is whatever the build left; the sums do not
 // depend on it, nor on the row blocks, so y has the same bits for every
 // partition count.  A row block with more entries than LDS holds keeps no
-// buckets and is summed straight from the CSR arrays in the same order.
+// buckets: the multiply launch sums its rows straight from the CSR arrays.
 //
 // An entry costs 8 + 2 bytes read and 8 written, then 8 + 2 read: 1.9 GB for
 // 2^22 rows of 16.  Measured there: multiply 246 us (5.3 TB/s), sum 226 us
@@ -78,6 +109,7 @@ constexpr int kMulGroups = 512;
 constexpr int kSumRowThreads = 512;
 constexpr int kSegments = 64;             // of row blocks, in the scan of the bucket sizes
 constexpr int kPad = 64;                  // entries to which a column block's start is aligned
+constexpr int kLongRow = 8192;            // entries beyond which a row is a workgroup's work
 
 struct BinPart {
     const int32_t *rp;  // biased: rp[row]
@@ -113,6 +145,11 @@ __device__ __forceinline__ BinBlock bin_block(const BinParts &bp, int64_t blk, i
     B.e0 = B.rp[B.lo];
     B.m = B.rp[B.lo + B.rows] - B.e0;
     return B;
+}
+
+// group_sum for a lane count known at run time (the same in all lanes).
+__device__ __forceinline__ double group_sum_of(double s, int G) {
+    return G == 4 ? group_sum<4>(s) : G == 8 ? group_sum<8>(s) : group_sum<16>(s);
 }
 
 // Row block of a workgroup: the grid is a multiple of 8, and XCD x (workgroups
@@ -155,6 +192,32 @@ bin_segments_kernel(const uint16_t *__restrict__ cnt, int nblk, int nc, int per,
     if (j == 0 && c < nc) {
         for (int k = 1; k < 16; ++k) t += sh[k][threadIdx.x];
         segs[(int64_t)blockIdx.y * nc + c] = t;
+    }
+}
+
+// One workgroup: the list of row blocks beyond LDS and of their long rows:
+// over[0] and over[1] their counts, then the blocks, then (block, row within it).
+__global__ void __launch_bounds__(1024) bin_over_kernel(BinParts bp, int rb, int nblk, int32_t *__restrict__ over) {
+    __shared__ int blocks, longs;
+    if (threadIdx.x == 0) blocks = longs = 0;
+    __syncthreads();
+    for (int b = threadIdx.x; b < nblk; b += 1024)
+        if (bin_block(bp, b, rb).m > kBinCap) over[2 + atomicAdd(&blocks, 1)] = b;
+    __syncthreads();
+    for (int i = 0; i < blocks; ++i) {
+        const int b = over[2 + i];
+        const BinBlock B = bin_block(bp, b, rb);
+        for (int r = threadIdx.x; r < B.rows; r += 1024)
+            if (B.rp[B.lo + r + 1] - B.rp[B.lo + r] > kLongRow) {
+                const int at = 2 + blocks + 2 * atomicAdd(&longs, 1);
+                over[at] = b;
+                over[at + 1] = r;
+            }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        over[0] = blocks;
+        over[1] = longs;
     }
 }
 
@@ -299,18 +362,65 @@ bin_fill_kernel(BinParts bp, const int32_t *__restrict__ col, const double *__re
 typedef uint16_t us4 __attribute__((ext_vector_type(4)));
 typedef uint16_t us2u __attribute__((ext_vector_type(2), aligned(2)));
 
+// The rows of row blocks beyond LDS, straight from the CSR arrays and in the same
+// order, spread over all workgroups of the multiply launch: groups of G lanes a
+// row, and for the rows of more than kLongRow entries a workgroup a row, which
+// has the products of 16384 entries at a time in LDS and G lanes add them (2^20
+// rows of 3 and one of 200,000: 16.0 ms when the row's block was one workgroup's
+// work and its lanes took an entry at a time).
+__device__ void bin_over_rows(const BinParts &bp, int rb, int G, const int32_t *__restrict__ over,
+                              const int32_t *__restrict__ col, const double *__restrict__ val,
+                              const double *__restrict__ x, double *xs) {
+    const int tid = threadIdx.x, per = kMulThreads / G, g = tid & (G - 1);
+    const int slices = (rb + per - 1) / per;
+    const int32_t *longs = over + 2 + over[0];
+    for (int64_t u = blockIdx.x; u < (int64_t)over[0] * slices; u += gridDim.x) {
+        const BinBlock B = bin_block(bp, over[2 + u / slices], rb);
+        const int r = (int)(u % slices) * per + tid / G;
+        int32_t kb = 0, ke = 0;
+        if (r < B.rows) {
+            kb = B.rp[B.lo + r];
+            ke = B.rp[B.lo + r + 1];
+        }
+        const bool mine = r < B.rows && ke - kb <= kLongRow;
+        const double s = group_sum_of(mine ? lane_sum<true>(col, val, x, kb, ke, g, G) : 0.0, G);
+        if (mine && g == 0) B.y[B.lo + r] = s;
+    }
+    for (int32_t i = blockIdx.x; i < over[1]; i += gridDim.x) {
+        const BinBlock B = bin_block(bp, longs[2 * i], rb);
+        const int64_t row = B.lo + longs[2 * i + 1];
+        const int64_t kb = B.rp[row], ke = B.rp[row + 1];
+        double s = 0.0;
+        for (int64_t base = kb; base < ke; base += kBinCols) {
+            const int m = (int)(ke - base < kBinCols ? ke - base : kBinCols);
+            __syncthreads();  // xs is free
+#pragma unroll 8
+            for (int k = tid; k < m; k += kMulThreads) xs[k] = val[base + k] * x[col[base + k]];
+            __syncthreads();
+            if (tid < G)
+#pragma unroll 16
+                for (int k = tid; k < m; k += G) s += xs[k];
+        }
+        if (tid < kWave) {
+            s = group_sum_of(s, G);
+            if (tid == 0) B.y[row] = s;
+        }
+    }
+}
+
 // prod = bval * x[bcol] over this workgroup's share of the column-block-major
 // order.  The entries that align a column block's start hold anything: their
 // column is masked to the segment, their product is never read.
 __global__ void __launch_bounds__(kMulThreads)
 bin_multiply_kernel(const int32_t *__restrict__ cbase, int nc, int64_t ncols, const double *__restrict__ x,
-                    const double *__restrict__ bval, const uint16_t *__restrict__ bcol, double *__restrict__ prod) {
+                    const double *__restrict__ bval, const uint16_t *__restrict__ bcol, double *__restrict__ prod,
+                    BinParts bp, int rb, int G, const int32_t *__restrict__ over, const int32_t *__restrict__ col,
+                    const double *__restrict__ val) {
     __shared__ double xs[kBinCols];
     const int64_t total = cbase[nc];
     const int64_t per = ((total + gridDim.x - 1) / gridDim.x + kPad - 1) / kPad * kPad;
     int64_t i0 = blockIdx.x * per;
     const int64_t i1 = i0 + per < total ? i0 + per : total;
-    if (i0 >= i1) return;
     int c = 0;
     for (int lo = 0, hi = nc - 1; lo <= hi;) {  // the last column block starting at or before i0
         const int mid = (lo + hi) >> 1;
@@ -346,6 +456,7 @@ bin_multiply_kernel(const int32_t *__restrict__ cbase, int nc, int64_t ncols, co
         for (int64_t i = i0 + threadIdx.x * 4; i < end; i += kMulThreads * 4) four(i);
         i0 = end;
     }
+    if (over[0] != 0) bin_over_rows(bp, rb, G, over, col, val, x, xs);
 }
 
 // One row block per workgroup: LB lanes copy a bucket's products to LDS, two
@@ -359,8 +470,7 @@ bin_multiply_kernel(const int32_t *__restrict__ cbase, int nc, int64_t ncols, co
 template <int G, int LB>
 __global__ void __launch_bounds__(kSumRowThreads)
 bin_sum_kernel(BinParts bp, int rb, int nblk, int nc, const int32_t *__restrict__ start, const uint16_t *__restrict__ cnt,
-               const double *__restrict__ prod, const uint16_t *__restrict__ dst, const int32_t *__restrict__ col,
-               const double *__restrict__ val, const double *__restrict__ x) {
+               const double *__restrict__ prod, const uint16_t *__restrict__ dst) {
     __shared__ double v[kBinCap];
     __shared__ int32_t rps[kBinMaxRows + 1];
     constexpr int kQ = kSumRowThreads / LB;  // buckets side by side
@@ -373,14 +483,14 @@ bin_sum_kernel(BinParts bp, int rb, int nblk, int nc, const int32_t *__restrict_
     const int32_t *st = start + blk * nc;
     const uint16_t *ct = cnt + blk * nc;
     const BinBlock B = bin_block(bp, blk, rb);
-    const bool inlds = B.m <= kBinCap;
+    if (B.m > kBinCap) return;  // its rows are done (bin_over_rows)
     int32_t rp[kRp];
 #pragma unroll
     for (int u = 0; u < kRp; ++u) {
         const int i = tid + u * kSumRowThreads;
         rp[u] = B.rp[B.lo + (i <= B.rows ? i : B.rows)];
     }
-    for (int c0 = q; inlds && c0 < nc; c0 += kQ * kU) {
+    for (int c0 = q; c0 < nc; c0 += kQ * kU) {
         int32_t at[kU], n[kU];
         dpair p[kU], p2[kU];
         us2u d[kU], d2[kU];
@@ -423,31 +533,22 @@ bin_sum_kernel(BinParts bp, int rb, int nblk, int nc, const int32_t *__restrict_
     __syncthreads();
     const int g = tid & (G - 1);
     constexpr int kStep = kSumRowThreads / G, kR = 4;  // rows side by side, and in each group's hands
-    if (inlds) {
-        for (int r0 = tid / G; r0 < B.rows; r0 += kStep * kR) {
-            int32_t k[kR], ke[kR];
-            double t[kR];
+    for (int r0 = tid / G; r0 < B.rows; r0 += kStep * kR) {
+        int32_t k[kR], ke[kR];
+        double t[kR];
 #pragma unroll
-            for (int u = 0; u < kR; ++u) {
-                const int r = r0 + u * kStep < B.rows ? r0 + u * kStep : r0;
-                k[u] = rps[r] + g;
-                ke[u] = rps[r + 1];
-            }
-#pragma unroll
-            for (int u = 0; u < kR; ++u) t[u] = k[u] < ke[u] ? 0.0 + v[k[u]] : 0.0;
-#pragma unroll
-            for (int u = 0; u < kR; ++u) {
-                for (int32_t i = k[u] + G; i < ke[u]; i += G) t[u] += v[i];
-                t[u] = group_sum<G>(t[u]);
-                if (g == 0 && r0 + u * kStep < B.rows) B.y[B.lo + r0 + u * kStep] = t[u];
-            }
+        for (int u = 0; u < kR; ++u) {
+            const int r = r0 + u * kStep < B.rows ? r0 + u * kStep : r0;
+            k[u] = rps[r] + g;
+            ke[u] = rps[r + 1];
         }
-    } else {
-        for (int r = tid / G; r < B.rows; r += kStep) {
-            double t = 0.0;
-            for (int32_t k = rps[r] + g; k < rps[r + 1]; k += G) t += val[(int64_t)B.e0 + k] * x[col[(int64_t)B.e0 + k]];
-            t = group_sum<G>(t);
-            if (g == 0) B.y[B.lo + r] = t;
+#pragma unroll
+        for (int u = 0; u < kR; ++u) t[u] = k[u] < ke[u] ? 0.0 + v[k[u]] : 0.0;
+#pragma unroll
+        for (int u = 0; u < kR; ++u) {
+            for (int32_t i = k[u] + G; i < ke[u]; i += G) t[u] += v[i];
+            t[u] = group_sum<G>(t[u]);
+            if (g == 0 && r0 + u * kStep < B.rows) B.y[B.lo + r0 + u * kStep] = t[u];
         }
     }
 }
@@ -503,7 +604,8 @@ bool bin_geometry(int64_t ncols, int64_t nnz, int64_t rows, int64_t entries, con
     bb->nblk = (int)nblk;
     const size_t cells = (size_t)nblk * bb->nc, cap = (size_t)entries + (size_t)kPad * bb->nc;
     const size_t bytes[kBinBuffers] = {cells * 4, cells * 2, (size_t)(bb->nc + 1) * 4, (size_t)kSegments * bb->nc * 4,
-                                       cap * 8,   cap * 2,   cap * 2,                  cap * 8};
+                                       cap * 8,   cap * 2,   cap * 2,                  cap * 8,
+                                       (2 + (size_t)nblk + 2 * ((size_t)entries / kLongRow + 1)) * 4};
     for (int i = 0; i < kBinBuffers; ++i) bb->bytes[i] = bytes[i];
     return true;
 }
@@ -518,6 +620,7 @@ hipError_t build_bins(const Launch *L, int n, const BinBufs &bb, hipStream_t s) 
     const size_t lds = (size_t)bb.nc * 4;
     hipLaunchKernelGGL(bin_count_kernel, dim3(bin_grid(bb.nblk)), dim3(512), lds, s, bp, col, bb.rb, bb.nblk, bb.nc,
                        bb.cnt());
+    hipLaunchKernelGGL(bin_over_kernel, dim3(1), dim3(1024), 0, s, bp, bb.rb, bb.nblk, bb.over());
     hipLaunchKernelGGL(bin_segments_kernel, scan, dim3(1024), 0, s, bb.cnt(), bb.nblk, bb.nc, per, bb.segs());
     hipLaunchKernelGGL(bin_bases_kernel, dim3(1), dim3(1024), 0, s, bb.nc, bb.segs(), bb.cbase());
     hipLaunchKernelGGL(bin_starts_kernel, scan, dim3(1024), 0, s, bb.cnt(), bb.nblk, bb.nc, per, bb.segs(), bb.start());
@@ -535,13 +638,13 @@ hipError_t launch_spmv_bins(const Launch *L, int n, const BinBufs &bb, hipStream
     const BinParts bp = bin_parts(L, n, bb.rb);
     const double *x = (const double *)L[0].a[3].ptr;
     hipLaunchKernelGGL(bin_multiply_kernel, dim3(kMulGroups), dim3(kMulThreads), 0, s, bb.cbase(), bb.nc, bb.ncols, x,
-                       bb.bval(), bb.bcol(), bb.prod());
+                       bb.bval(), bb.bcol(), bb.prod(), bp, bb.rb, bb.lanes, bb.over(), (const int32_t *)L[0].a[1].ptr,
+                       (const double *)L[0].a[2].ptr);
     // lanes per bucket: 16 take up to 64 entries at once, 64 up to 256
     const bool wide = (int64_t)kBinTarget > (int64_t)48 * bb.nc;
 #define BIN_SUM(G, LB)                                                                                                 \
     hipLaunchKernelGGL((bin_sum_kernel<G, LB>), dim3(bin_grid(bb.nblk)), dim3(kSumRowThreads), 0, s, bp, bb.rb, bb.nblk, \
-                       bb.nc, bb.start(), bb.cnt(), bb.prod(), bb.dst(), (const int32_t *)L[0].a[1].ptr,               \
-                       (const double *)L[0].a[2].ptr, x)
+                       bb.nc, bb.start(), bb.cnt(), bb.prod(), bb.dst())
 #define BIN_SUM_LB(G)       \
     do {                    \
         if (wide)           \

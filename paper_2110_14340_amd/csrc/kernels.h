@@ -223,7 +223,7 @@ hipError_t launch_spmv(const Launch &L, hipStream_t s);
 
 // Binned SpMV: the device copy of the matrix rows of one or more partitions'
 // launches, its geometry and buffers (k_spmv.hip).
-constexpr int kBinBuffers = 8;
+constexpr int kBinBuffers = 9;
 struct BinBufs {
     int64_t ncols;
     int nc, rb, nblk, lanes;  // column blocks, rows per row block, row blocks, lanes per row
@@ -237,6 +237,7 @@ struct BinBufs {
     uint16_t *bcol() const { return (uint16_t *)mem[5]; }  // column within its block,
     uint16_t *dst() const { return (uint16_t *)mem[6]; }   // place in its row block
     double *prod() const { return (double *)mem[7]; }      // products of the last multiply
+    int32_t *over() const { return (int32_t *)mem[8]; }    // the row blocks beyond LDS and their long rows
 };
 // Lanes per row by the mean row length of the whole matrix (not by
 // partition: the lanes decide the order of a row's sum).

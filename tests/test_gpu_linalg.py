@@ -495,3 +495,22 @@ def test_binned_products_of_boxes_and_a_changed_row_ptr(K):
                 assert np.all(np.abs(y[lo:hi] - ref[lo:hi]) <= bound[lo:hi]), (lo, hi)
                 assert np.all(y[:lo] == 7.0) and np.all(y[hi:] == 7.0)
         c.exit(y)
+
+
+@pytest.mark.parametrize("mean,lanes", [(2, 4), (4, 8), (7, 16), (15, 16)])
+def test_binned_rows_beyond_lds(mean, lanes):
+    """Rows on both sides of the longest that a lane group adds (8192 entries)
+    and of the 16384 products a workgroup holds at a time, some in blocks of
+    other long rows, the rest short: the plain form's bits with the same lanes,
+    for K = 1, 4 and 20, and every row within the bound."""
+    say(f"binned rows beyond LDS, mean {mean}")
+    n = 60000
+    lens = np.random.default_rng(mean).integers(0, 2 * mean, n)
+    lens[:6] = (8191, 8192, 8193, 1, 9000, 0)
+    lens[30000:30005] = (16383, 16384, 16385, 40001, 2000)
+    lens[-1] = 9601
+    rp, col, val, x = _rows_matrix(lens, 50000, seed=mean)
+    plain = _spmv_dev(rp, col, val, x, 1, jacc.config(tile=lanes, order=2))
+    assert np.all(np.abs(plain - oracle.spmv_csr(rp, col, val, x)) <= 1e-13 * _row_bound(rp, col, val, x))
+    for K in (1, 4, 20):
+        assert np.array_equal(_spmv_dev(rp, col, val, x, K, jacc.config(order=4)), plain), K
