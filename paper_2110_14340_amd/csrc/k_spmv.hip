@@ -109,6 +109,7 @@ constexpr int kMulGroups = 512;
 constexpr int kSumRowThreads = 512;
 constexpr int kSegments = 64;             // of row blocks, in the scan of the bucket sizes
 constexpr int kPad = 64;                  // entries to which a column block's start is aligned
+constexpr int kBig = 1024;                // entries beyond which a bucket is the whole workgroup's work
 constexpr int kLongRow = 8192;            // entries beyond which a row is a workgroup's work
 
 struct BinPart {
@@ -460,7 +461,11 @@ bin_multiply_kernel(const int32_t *__restrict__ cbase, int nc, int64_t ncols, co
 }
 
 // One row block per workgroup: LB lanes copy a bucket's products to LDS, two
-// neighbours each, then G lanes add up a row.  The latency of its chain of
+// neighbours each, then G lanes add up a row.  What a bucket holds beyond its
+// lanes' first two rounds is copied by a wave, or by the whole workgroup: the rows
+// of a matrix with its columns near the diagonal have one or two buckets, over
+// which 16 lanes took 2471 us a product (2^22 rows of 16 neighbours; 494 so, the
+// plain form 274; 2^22 rows of 5: 762, 187 and 134).  The latency of its chain of
 // loads (bucket table, then products, then the sums) bounds it, so all
 // products of a block are in flight at once, and the row pointers with them.
 // (Tried at 2^22 rows of 16, against 226 us: four workgroups of half the size
@@ -473,6 +478,8 @@ bin_sum_kernel(BinParts bp, int rb, int nblk, int nc, const int32_t *__restrict_
                const double *__restrict__ prod, const uint16_t *__restrict__ dst) {
     __shared__ double v[kBinCap];
     __shared__ int32_t rps[kBinMaxRows + 1];
+    constexpr int kSumWaves = kSumRowThreads / kWave;
+    __shared__ __align__(16) int more[kSumWaves];  // a wave's buckets have entries left
     constexpr int kQ = kSumRowThreads / LB;  // buckets side by side
     constexpr int kU = 8;                    // and in each group's hands
     constexpr int kP = 2 * LB;               // entries a group takes at a time
@@ -480,6 +487,7 @@ bin_sum_kernel(BinParts bp, int rb, int nblk, int nc, const int32_t *__restrict_
     const int64_t blk = bin_order();
     if (blk >= nblk) return;
     const int tid = threadIdx.x, sub = 2 * (tid & (LB - 1)), q = tid / LB;
+    int most = 0;
     const int32_t *st = start + blk * nc;
     const uint16_t *ct = cnt + blk * nc;
     const BinBlock B = bin_block(bp, blk, rb);
@@ -521,16 +529,42 @@ bin_sum_kernel(BinParts bp, int rb, int nblk, int nc, const int32_t *__restrict_
             if (sub + 1 < n[u]) v[d[u].y] = p[u].y;
             if (sub + kP < n[u]) v[d2[u].x] = p2[u].x;
             if (sub + kP + 1 < n[u]) v[d2[u].y] = p2[u].y;
-            for (int i = sub + 2 * kP; i < n[u]; i += kP) {
-                v[dst[at[u] + i]] = prod[at[u] + i];
-                if (i + 1 < n[u]) v[dst[at[u] + i + 1]] = prod[at[u] + i + 1];
-            }
+            most = n[u] > most ? n[u] : most;
         }
     }
 #pragma unroll
     for (int u = 0; u < kRp; ++u)
         if (tid + u * kSumRowThreads <= B.rows) rps[tid + u * kSumRowThreads] = rp[u] - B.e0;
+    const bool left = __any(most > 2 * kP);
+    if ((tid & (kWave - 1)) == 0) more[tid / kWave] = left;
     __syncthreads();
+    const int4 m0 = *reinterpret_cast<const int4 *>(&more[0]), m1 = *reinterpret_cast<const int4 *>(&more[4]);
+    if (m0.x | m0.y | m0.z | m0.w | m1.x | m1.y | m1.z | m1.w) {  // entries past the first 2 kP of a bucket
+        __shared__ uint16_t big[kBinCap / (2 * kP) + 1];
+        __shared__ int nbig;
+        if (tid == 0) nbig = 0;
+        __syncthreads();
+        for (int c = tid; c < nc; c += kSumRowThreads)
+            if (ct[c] > 2 * kP) big[atomicAdd(&nbig, 1)] = (uint16_t)c;
+        __syncthreads();
+        auto copy = [&](int at, int m, int first, int step) {
+#pragma unroll 4
+            for (int i = 2 * kP + 2 * first; i < m; i += 2 * step) {
+                const dpair p = *reinterpret_cast<const dpair *>(prod + at + i);
+                const us2u d = *reinterpret_cast<const us2u *>(dst + at + i);
+                v[d.x] = p.x;
+                if (i + 1 < m) v[d.y] = p.y;
+            }
+        };
+        for (int b = 0; b < nbig; ++b) {  // a wave takes a bucket's, all of them those of a large one
+            const int c = big[b], m = ct[c];
+            if (m > kBig)
+                copy(st[c], m, tid, kSumRowThreads);
+            else if (b % kSumWaves == tid / kWave)
+                copy(st[c], m, tid & (kWave - 1), kWave);
+        }
+        __syncthreads();
+    }
     const int g = tid & (G - 1);
     constexpr int kStep = kSumRowThreads / G, kR = 4;  // rows side by side, and in each group's hands
     for (int r0 = tid / G; r0 < B.rows; r0 += kStep * kR) {
@@ -570,6 +604,9 @@ BinParts bin_parts(const Launch *L, int n, int rb) {
     return bp;
 }
 
+// Lanes per bucket: 16 take up to 64 entries at once, 64 up to 256.
+int64_t bin_lanes(int64_t nc) { return kBinTarget > 48 * nc ? 64 : 16; }
+
 unsigned bin_grid(int nblk) { return (unsigned)((nblk + 7) / 8 * 8); }
 
 }  // namespace
@@ -589,10 +626,15 @@ bool bin_geometry(int64_t ncols, int64_t nnz, int64_t rows, int64_t entries, con
     if (ncols < 1 || ncols > ((int64_t)kBinCols << 15) || n > kMaxPack) return false;
     const int64_t mean = (nnz + rows - 1) / (rows > 0 ? rows : 1);
     if (mean > kBinCap) return false;  // most row blocks would hold no buckets
-    int64_t rb = mean > 0 ? kBinTarget / mean : kBinMaxRows;
+    // just past the change to 16 lanes a bucket, smaller blocks, whose buckets
+    // seldom exceed the 64 entries that those take at once (2^22 rows of 16 over
+    // 157 column blocks: 459 us, 466 without)
+    const int64_t nc = (ncols + kBinCols - 1) >> kBinShift;
+    const int64_t target = bin_lanes(nc) == 16 && 44 * nc < kBinTarget ? 44 * nc : kBinTarget;
+    int64_t rb = mean > 0 ? target / mean : kBinMaxRows;
     rb = rb < 16 ? 16 : rb > kBinMaxRows ? kBinMaxRows : rb;
     bb->ncols = ncols;
-    bb->nc = (int)((ncols + kBinCols - 1) >> kBinShift);
+    bb->nc = (int)nc;
     bb->rb = (int)rb;
     bb->lanes = spmv_lanes(nnz, rows);
     int64_t nblk = 0;
@@ -640,8 +682,7 @@ hipError_t launch_spmv_bins(const Launch *L, int n, const BinBufs &bb, hipStream
     hipLaunchKernelGGL(bin_multiply_kernel, dim3(kMulGroups), dim3(kMulThreads), 0, s, bb.cbase(), bb.nc, bb.ncols, x,
                        bb.bval(), bb.bcol(), bb.prod(), bp, bb.rb, bb.lanes, bb.over(), (const int32_t *)L[0].a[1].ptr,
                        (const double *)L[0].a[2].ptr);
-    // lanes per bucket: 16 take up to 64 entries at once, 64 up to 256
-    const bool wide = (int64_t)kBinTarget > (int64_t)48 * bb.nc;
+    const bool wide = bin_lanes(bb.nc) == 64;
 #define BIN_SUM(G, LB)                                                                                                 \
     hipLaunchKernelGGL((bin_sum_kernel<G, LB>), dim3(bin_grid(bb.nblk)), dim3(kSumRowThreads), 0, s, bp, bb.rb, bb.nblk, \
                        bb.nc, bb.start(), bb.cnt(), bb.prod(), bb.dst())

@@ -514,3 +514,27 @@ def test_binned_rows_beyond_lds(mean, lanes):
     assert np.all(np.abs(plain - oracle.spmv_csr(rp, col, val, x)) <= 1e-13 * _row_bound(rp, col, val, x))
     for K in (1, 4, 20):
         assert np.array_equal(_spmv_dev(rp, col, val, x, K, jacc.config(order=4)), plain), K
+
+
+@pytest.mark.parametrize("ncols", [20000, 200 << 14])
+def test_binned_buckets_of_any_size(ncols):
+    """One row block whose entries lie in one column block but for a few: bucket
+    sizes around what the 16 or 64 lanes of a bucket take at once, and around
+    those that a wave and the whole workgroup take; then all rows of a banded
+    matrix.  The plain form's bits."""
+    say(f"binned bucket sizes, {ncols} columns")
+    r = np.random.default_rng(7)
+    for size in (31, 32, 33, 63, 64, 65, 66, 127, 129, 255, 256, 257, 1023, 1024, 1025, 1026, 2049, 7001):
+        lens = np.bincount(r.integers(0, 64, size + 3), minlength=64)
+        rp, col, val, x = _rows_matrix(lens, ncols, seed=size)
+        col[:] = r.integers(0, 16384, col.size)
+        col[r.permutation(col.size)[:3]] = ncols - 1
+        plain = _spmv_dev(rp, col, val, x, 1, jacc.config(order=2))
+        assert np.array_equal(_spmv_dev(rp, col, val, x, 1, jacc.config(order=4)), plain), size
+        assert np.all(np.abs(plain - oracle.spmv_csr(rp, col, val, x)) <= 1e-13 * _row_bound(rp, col, val, x)), size
+    n = 19999
+    rp, col, val, x = _rows_matrix(np.full(n, 5), ncols, seed=3)
+    col[:] = (np.arange(n)[:, None] * (ncols // n) + np.array([-300, -1, 0, 1, 300])).ravel() % ncols
+    plain = _spmv_dev(rp, col, val, x, 1, jacc.config(order=2))
+    for K in (1, 4):
+        assert np.array_equal(_spmv_dev(rp, col, val, x, K, jacc.config(order=4)), plain), K
