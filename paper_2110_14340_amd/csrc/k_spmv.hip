@@ -14,7 +14,6 @@ namespace {
 
 constexpr int kSpmvThreads = 256;
 
-// v of another lane of its row of 16 lanes, by a DPP pattern.
 // Lane g's share of the row [kb, ke): its entries' products added in increasing
 // k.  Eight of them are in flight at once, so that a long row is not one load's
 // latency after the other.  NT: col and val are read once, so they are loaded
@@ -55,16 +54,7 @@ spmv_kernel(const int32_t *__restrict__ rp, const int32_t *__restrict__ col, con
     const int g = threadIdx.x & (G - 1);
     double s = 0.0;
     const bool live = i < r_hi;
-    if (live) {
-        const int32_t kb = rp[i], ke = rp[i + 1];
-        for (int32_t k = kb + g; k < ke; k += G) {
-            // NT: col and val are read once, so they are loaded non-temporally
-            // and leave the caches to the gathered x
-            const int32_t c = NT ? __builtin_nontemporal_load(&col[k]) : col[k];
-            const double v = NT ? __builtin_nontemporal_load(&val[k]) : val[k];
-            s += v * x[c];
-        }
-    }
+    if (live) s = lane_sum<NT>(col, val, x, rp[i], rp[i + 1], g, G);
     s = group_sum<G>(s);
     if (live && g == 0) y[i] = s;
 }
