@@ -59,6 +59,36 @@ spmv_kernel(const int32_t *__restrict__ rp, const int32_t *__restrict__ col, con
     if (live && g == 0) y[i] = s;
 }
 
+// The partitions of one product in one launch: partition q's rows take the
+// workgroups from wg_begin on, each row summed as its own launch would.
+struct SpmvPart {
+    const int32_t *rp, *col;
+    const double *val, *x;
+    double *y;
+    int64_t lo, hi, wg_begin;
+};
+struct SpmvParts {
+    SpmvPart p[kMaxPack];
+    int32_t n;
+};
+typedef const __attribute__((address_space(4))) SpmvPart ConstSpmvPart;
+
+template <int G>
+__global__ void __launch_bounds__(kSpmvThreads) spmv_parts_kernel(SpmvParts sp) {
+    ConstSpmvPart *cp = (ConstSpmvPart *)&sp.p[0];
+    int q = 0;
+    for (int k = 1; k < sp.n; ++k)
+        if (cp[k].wg_begin <= (int64_t)blockIdx.x) q = k;
+    const int64_t i = cp[q].lo + ((blockIdx.x - cp[q].wg_begin) * kSpmvThreads + threadIdx.x) / G;
+    const int g = threadIdx.x & (G - 1);
+    const bool live = i < cp[q].hi;
+    const int32_t *rp = cp[q].rp;
+    double s = 0.0;
+    if (live) s = lane_sum<true>(cp[q].col, cp[q].val, cp[q].x, rp[i], rp[i + 1], g, G);
+    s = group_sum<G>(s);
+    if (live && g == 0) cp[q].y[i] = s;
+}
+
 // ---------------------------------------------------------------------------
 // Binned form.  What bounds the plain form is its gathers of x: each reads a
 // 128-byte line through L1 (and, for an x beyond an XCD's 4 MB L2, mostly
@@ -608,6 +638,29 @@ int spmv_lanes(int64_t nnz, int64_t rows) {
     return mean > 8 ? 16 : mean > 4 ? 8 : 4;
 }
 
+// Rows per row block, by the mean row length.
+static int64_t bin_rows(int64_t mean, int64_t nc) {
+    // just past the change to 16 lanes a bucket, smaller blocks, whose buckets
+    // seldom exceed the 64 entries that those take at once (2^22 rows of 16 over
+    // 157 column blocks: 459 us, 466 without)
+    const int64_t target = bin_lanes(nc) == 16 && 44 * nc < kBinTarget ? 44 * nc : kBinTarget;
+    const int64_t rb = mean > 0 ? target / mean : kBinMaxRows;
+    return rb < 16 ? 16 : rb > kBinMaxRows ? kBinMaxRows : rb;
+}
+
+// A binned product loads every column block's x and walks every bucket, whatever
+// they hold.  It is faster from about 2^22 entries on (us, plain and binned; 2^20
+// rows and columns, 2 / 4 / 8 entries a row: 30 and 42, 50 and 51, 93 and 75),
+// where a column has an entry on average (2^22 columns, 2^16 / 2^18 rows of 16:
+// 21 and 40, 74 and 57; 2^27 columns, 1000 rows of 16: 11 and 366) and a bucket
+// four (2^24 columns, 2^22 rows of 4: 332 and 247; 2^26 columns, rows of 16, 1.8 a
+// bucket: 1306 and 1301, and the copy takes 3 ms).
+bool bin_pays(int64_t ncols, int64_t nnz, int64_t rows) {
+    if (rows < 1) return false;
+    const int64_t nc = (ncols + kBinCols - 1) >> kBinShift, rb = bin_rows((nnz + rows - 1) / rows, nc);
+    return nnz >= ((int64_t)1 << 22) && nnz >= ncols && nnz >= 4 * nc * ((rows + rb - 1) / rb);
+}
+
 bool bin_geometry(int64_t ncols, int64_t nnz, int64_t rows, int64_t entries, const Launch *L, int n, BinBufs *bb) {
     *bb = BinBufs{};
     // the histogram of column blocks takes 4 bytes of LDS each (128 KB); row
@@ -616,13 +669,7 @@ bool bin_geometry(int64_t ncols, int64_t nnz, int64_t rows, int64_t entries, con
     if (ncols < 1 || ncols > ((int64_t)kBinCols << 15) || n > kMaxPack) return false;
     const int64_t mean = (nnz + rows - 1) / (rows > 0 ? rows : 1);
     if (mean > kBinCap) return false;  // most row blocks would hold no buckets
-    // just past the change to 16 lanes a bucket, smaller blocks, whose buckets
-    // seldom exceed the 64 entries that those take at once (2^22 rows of 16 over
-    // 157 column blocks: 459 us, 466 without)
-    const int64_t nc = (ncols + kBinCols - 1) >> kBinShift;
-    const int64_t target = bin_lanes(nc) == 16 && 44 * nc < kBinTarget ? 44 * nc : kBinTarget;
-    int64_t rb = mean > 0 ? target / mean : kBinMaxRows;
-    rb = rb < 16 ? 16 : rb > kBinMaxRows ? kBinMaxRows : rb;
+    const int64_t nc = (ncols + kBinCols - 1) >> kBinShift, rb = bin_rows(mean, nc);
     bb->ncols = ncols;
     bb->nc = (int)nc;
     bb->rb = (int)rb;
@@ -690,6 +737,29 @@ hipError_t launch_spmv_bins(const Launch *L, int n, const BinBufs &bb, hipStream
     }
 #undef BIN_SUM_LB
 #undef BIN_SUM
+    return hipGetLastError();
+}
+
+hipError_t launch_spmv_parts(const Launch *L, int n, hipStream_t s) {
+    if (n > kMaxPack) return hipErrorInvalidValue;
+    SpmvParts sp{};
+    const int G = n > 0 ? L[0].cfg.tile : 16;
+    int64_t wg = 0;
+    for (int k = 0; k < n; ++k) {
+        const int64_t rows = L[k].hi[0] - L[k].lo[0];
+        if (rows <= 0) continue;
+        sp.p[sp.n++] = {(const int32_t *)L[k].a[0].ptr, (const int32_t *)L[k].a[1].ptr, (const double *)L[k].a[2].ptr,
+                        (const double *)L[k].a[3].ptr,  (double *)L[k].a[4].ptr,        L[k].lo[0],
+                        L[k].hi[0],                     wg};
+        wg += (rows * G + kSpmvThreads - 1) / kSpmvThreads;
+    }
+    if (wg == 0) return hipSuccess;
+    if (wg > INT32_MAX) return hipErrorInvalidValue;
+    switch (G) {
+        case 4: hipLaunchKernelGGL(spmv_parts_kernel<4>, dim3((unsigned)wg), dim3(kSpmvThreads), 0, s, sp); break;
+        case 8: hipLaunchKernelGGL(spmv_parts_kernel<8>, dim3((unsigned)wg), dim3(kSpmvThreads), 0, s, sp); break;
+        default: hipLaunchKernelGGL(spmv_parts_kernel<16>, dim3((unsigned)wg), dim3(kSpmvThreads), 0, s, sp); break;
+    }
     return hipGetLastError();
 }
 

@@ -220,6 +220,9 @@ hipError_t launch_finalise(const double *partials, int64_t n, double *out, hipSt
 hipError_t launch_result(const Launch &L, int64_t n, hipStream_t s);
 hipError_t launch_gemm(const Launch &L, hipStream_t s);
 hipError_t launch_spmv(const Launch &L, hipStream_t s);
+// The plain products of at most kMaxPack partitions in one launch, each on its
+// own slabs (cfg.tile of the first: lanes per row).
+hipError_t launch_spmv_parts(const Launch *L, int n, hipStream_t s);
 
 // Binned SpMV: the device copy of the matrix rows of one or more partitions'
 // launches, its geometry and buffers (k_spmv.hip).
@@ -242,6 +245,9 @@ struct BinBufs {
 // Lanes per row by the mean row length of the whole matrix (not by
 // partition: the lanes decide the order of a row's sum).
 int spmv_lanes(int64_t nnz, int64_t rows);
+// Whether the binned form is the faster one for a matrix (by default, from 2^20
+// columns on).
+bool bin_pays(int64_t ncols, int64_t nnz, int64_t rows);
 // Geometry for a matrix of `rows` rows and `nnz` entries, and the buffer sizes of
 // a copy of the launches' rows, which hold `entries` of them (false: this form
 // does not take the matrix).

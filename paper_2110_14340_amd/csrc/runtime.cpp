@@ -1449,25 +1449,30 @@ struct LoopNote {
 };
 
 // Issues the products of launches L[0..n) as stream s's next op: binned, after
-// the last product that used the copy's buffers, or plain.  The binned form
-// reads x by whole column blocks and a packed one takes col, val and x from the
-// first partition, so over several partitions it needs these arguments whole:
-// a matrix whose x is entered with a halo runs the plain form, which touches
-// the referenced elements of each partition's own slabs only.
-int issue_spmv(jacc_ctx *c, Array **arr, const jacc_arg *args, int p, const jk::Launch *L, int n, int s,
+// the last product that used the copy's buffers, or plain.  Unless the caller
+// `asked` for it, the binned form is for matrices with entries enough.  It reads
+// x by whole column blocks and a packed one takes col, val and x from the first
+// partition, so over several partitions it needs these arguments whole: a matrix
+// whose x is entered with a halo runs the plain form, which touches the
+// referenced elements of each partition's own slabs only.
+int issue_spmv(jacc_ctx *c, Array **arr, const jacc_arg *args, bool asked, int p, const jk::Launch *L, int n, int s,
                LoopNote *note) {
     BinCache *bc = nullptr;
     int rc = JACC_OK;
-    if (arr[0]->K == 1 || (args[1].whole && args[2].whole && args[3].whole)) rc = bin_cache(c, arr, p, L, n, s, &bc);
+    if ((arr[0]->K == 1 || (args[1].whole && args[2].whole && args[3].whole)) &&
+        (asked || jk::bin_pays(arr[3]->E, arr[1]->E, arr[0]->E - 1)))
+        rc = bin_cache(c, arr, p, L, n, s, &bc);
     if (rc) return rc;
     if (!bc) {
-        for (int k = 0; k < n; ++k) {
-            jk::Launch P = L[k];
+        std::vector<jk::Launch> plain(L, L + n);
+        for (jk::Launch &P : plain) {
             P.cfg = jk::default_config(JACC_LOOP_SPMV_CSR, P, jk::Cfg{});
             P.cfg.tile = jk::spmv_lanes(arr[1]->E, arr[0]->E - 1);
-            if (note) note->cfg = P.cfg;
-            if (live(c)) HIPCHK(c, jk::launch_loop(P, c->st[s].s), "kernel launch");
         }
+        if (note) note->cfg = plain[0].cfg;
+        if (live(c))
+            HIPCHK(c, n > 1 ? jk::launch_spmv_parts(plain.data(), n, c->st[s].s) : jk::launch_loop(plain[0], c->st[s].s),
+                   "kernel launch");
         return JACC_OK;
     }
     rc = ensure_wait(c, s, bc->last.s, bc->last.seq);
@@ -1833,7 +1838,7 @@ int loop_impl(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const jacc
             return set_err(c, JACC_ERR_DEVICE, "injected fault in launch %lld", (long long)c->fault_count);
         }
         if (kind == JACC_LOOP_SPMV_CSR) {
-            rc = lps.empty() ? JACC_OK : issue_spmv(c, arr, args, -1, lps.data(), (int)lps.size(), s, note);
+            rc = lps.empty() ? JACC_OK : issue_spmv(c, arr, args, cfg && cfg->order == 4, -1, lps.data(), (int)lps.size(), s, note);
             if (rc) return rc;
         } else if (live(c)) {
             HIPCHK(c,
@@ -1968,7 +1973,7 @@ int loop_impl(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const jacc
         const bool timed = c->time_parts && live(c) && p < kMaxK;
         if (timed) HIPCHK(c, hipEventRecord(c->kev[2 * p], c->st[s].s), "hipEventRecord");
         if (kind == JACC_LOOP_SPMV_CSR && LP.cfg.order == 4) {
-            rc = issue_spmv(c, arr, args, p, &LP, 1, s, note);
+            rc = issue_spmv(c, arr, args, cfg && cfg->order == 4, p, &LP, 1, s, note);
             if (rc) return rc;
         } else if (live(c) && waits) {
             c->mloops.push_back(LP);

@@ -538,3 +538,18 @@ def test_binned_buckets_of_any_size(ncols):
     plain = _spmv_dev(rp, col, val, x, 1, jacc.config(order=2))
     for K in (1, 4):
         assert np.array_equal(_spmv_dev(rp, col, val, x, K, jacc.config(order=4)), plain), K
+
+
+@pytest.mark.parametrize("rows,ncols", [(1003, (1 << 21) + 7), (5, 1 << 20), (70001, (1 << 20) + 1)])
+def test_sparse_matrix_with_many_columns(rows, ncols):
+    """Matrices that the default leaves to the plain form for their few entries
+    a column: one launch over the partitions, a launch each, and both forms give
+    the same bits (K = 1, 4 and 16)."""
+    say(f"spmv {rows} rows, {ncols} columns")
+    lens = np.random.default_rng(rows).integers(0, 30, rows)
+    rp, col, val, x = _rows_matrix(lens, ncols, seed=rows)
+    ref = _spmv_dev(rp, col, val, x, 1, jacc.config(order=2))
+    assert np.all(np.abs(ref - oracle.spmv_csr(rp, col, val, x)) <= 1e-13 * _row_bound(rp, col, val, x))
+    for K in (k for k in (1, 4, 16) if k <= rows):
+        for cfg in (None, jacc.config(order=4)):
+            assert np.array_equal(_spmv_dev(rp, col, val, x, K, cfg), ref), (K, cfg)

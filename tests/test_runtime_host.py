@@ -1292,3 +1292,26 @@ def test_binned_spmv_packs_whatever_its_fields_without_effect(rows):
     kern = [t for t in c.trace() if t["op"] == "KERNEL"]
     assert len(kern) == 4 and len({(t["stream"], t["seq"]) for t in kern}) == 1
     c.close()
+
+
+@pytest.mark.parametrize("rows,ncols,per_row,order", [
+    (1 << 20, 1 << 20, 4, 4), (1 << 20, 1 << 20, 3, 2), (1000, 1 << 24, 16, 2), (1 << 16, 1 << 22, 16, 2),
+    (1 << 18, 1 << 22, 16, 4), (1 << 19, 1 << 26, 32, 2), (1 << 20, (1 << 20) - 1, 8, 2)])
+@pytest.mark.parametrize("K", [1, 4])
+def test_default_spmv_form_by_the_matrix(rows, ncols, per_row, order, K, monkeypatch, tmp_path):
+    """The default form (the record's order: 2 plain, 4 binned) follows the
+    matrix's columns, entries and entries a bucket, and order 4 is honoured for
+    each; either form's partitions are one launch from 2^20 columns on."""
+    import json
+    path = tmp_path / "loops.jsonl"
+    monkeypatch.setenv("JACC_LOG", str(path))
+    c = jacc.Context(K, flags=jacc.INIT_DRYRUN)
+    col, val = np.zeros(rows * per_row, np.int32), np.zeros(rows * per_row)
+    rp, x, y = np.zeros(rows + 1, np.int32), np.zeros(ncols), np.zeros(rows)
+    _dry_product(c, rp, col, val, x, y)
+    c.spmv(rp, col, val, x, y)
+    c.spmv(rp, col, val, x, y, cfg=jacc.config(order=4))
+    c.close()
+    recs = [json.loads(line) for line in path.read_text().splitlines()]
+    assert [r["cfg"]["order"] for r in recs] == [order, 4]
+    assert recs[0]["packed"] == (K > 1 and ncols >= 1 << 20)
