@@ -248,7 +248,7 @@ hipError_t launch_gemm(const Launch &L, hipStream_t s) {
     const int64_t m = L.hi[0] - L.lo[0], n = L.hi[1] - L.lo[1];
     if (m <= 0 || n <= 0) return hipSuccess;
     const int64_t K = L.a[0].row_elems, N = L.a[2].row_elems;
-    const int64_t parts = L.ext[0] > m ? (L.ext[0] + m / 2) / m : 1;  // partitions running beside this one
+    const int64_t parts = L.beside > 1 ? L.beside : 1;  // launches of the loop running side by side
     auto tiles = [](int64_t e, int blocks) { return (e + 32 * blocks - 1) / (32 * blocks); };
 #define GEMM_LAUNCH(MI, NJ, S, PAIR, OFF)                                                                              \
     do {                                                                                                               \

@@ -74,6 +74,7 @@ struct Launch {
     unsigned *ticket;  // for packed launches: zero, and zero again when the finaliser ends
     bool streamed;      // other loops' arrays pass through the caches between its runs
     int64_t part_rows;  // iterations along dim 0 of the largest partition (for defaults)
+    int beside;         // launches of the same loop on streams of their own, this one among them
 };
 
 // Launches the loop body (and, for reductions, the per-partition

@@ -1645,6 +1645,12 @@ int loop_impl(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const jacc
             HIPCHK(c, hipEventRecord(note->e0, c->st[s0].s), "hipEventRecord");
         }
     }
+    // launches that run side by side: the partitions with iterations, each on a
+    // stream of its own
+    L.beside = 0;
+    if (!one_stream && !persistent && !packed)
+        for (int p = 0; p < K; ++p) L.beside += !plan[p].iters.empty();
+    L.beside = std::min(L.beside, ns);
     // rows of its slab a partition may write: a filtered output entered
     // whole takes private writes anywhere in the partition's replica
     int first_run = 0;  // first partition with iterations (a duplicated loop's reference replica)
