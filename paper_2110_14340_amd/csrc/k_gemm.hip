@@ -259,8 +259,7 @@ hipError_t launch_gemm(const Launch &L, hipStream_t s) {
                            (double *)L.a[2].ptr, L.lo[0], L.hi[0], L.lo[1], L.hi[1], K, N, tm, tn);                    \
         return hipGetLastError();                                                                                      \
     } while (0)
-    // 32-bit lane offsets reach 64 rows of A and 8 rows of B
-    if (N < 2 || K >= ((int64_t)1 << 22) || N >= ((int64_t)1 << 25)) GEMM_LAUNCH(1, 2, 4, false, int64_t);
+    if (N < 2) GEMM_LAUNCH(1, 2, 4, false, int64_t);
     // wave tiles of 64x64, 32x64, 32x32 and 16x32, whichever keeps the
     // busiest compute unit shortest (1024^3: 134 / 77 / 51 / 59 us; 512^3:
     // 71 / 42 / 28 / 21 us; 2048^3: 291 / 304 / 354 / 409 us; 2467x3597x363:
@@ -269,8 +268,19 @@ hipError_t launch_gemm(const Launch &L, hipStream_t s) {
     const double c8 = stage_cost(parts, tiles(m, 2) * tiles(n, 4), 8, 1.035);
     const double c4 = stage_cost(parts, tiles(m, 2) * tiles(n, 2), 4, 1.19);
     const double c2 = stage_cost(parts, tiles(m, 1) * tiles(n, 2), 2, 1.40);
-    if (c16 <= c8 && c16 <= c4 && c16 <= c2) GEMM_LAUNCH(4, 4, 3, true, uint32_t);
-    if (c8 <= c4 && c8 <= c2) GEMM_LAUNCH(2, 4, 4, true, uint32_t);
+    const bool big = c16 <= c8 && c16 <= c4 && c16 <= c2, mid = c8 <= c4 && c8 <= c2;
+    // 32-bit lane offsets reach 64 rows of A and 8 rows of B.  Beyond, the large
+    // tiles take 64-bit ones and a stage less (256 x 2^25, 8 deep: 11.0 ms, 18.5
+    // as 16x32 tiles of single loads; 100 x 2^25, 20 deep: 9.0 and 12.3); few
+    // rows that are 2^22 long do best with the short stages of the last form
+    // (256 x 256, 2^22 deep: 118 ms, 153 in pairs).
+    if (K >= ((int64_t)1 << 22) || N >= ((int64_t)1 << 25)) {
+        if (big) GEMM_LAUNCH(4, 4, 2, true, int64_t);
+        if (mid) GEMM_LAUNCH(2, 4, 3, true, int64_t);
+        GEMM_LAUNCH(1, 2, 4, false, int64_t);
+    }
+    if (big) GEMM_LAUNCH(4, 4, 3, true, uint32_t);
+    if (mid) GEMM_LAUNCH(2, 4, 4, true, uint32_t);
     if (c4 <= c2) GEMM_LAUNCH(2, 2, 4, true, uint32_t);
     GEMM_LAUNCH(1, 2, 6, true, uint32_t);
 #undef GEMM_LAUNCH

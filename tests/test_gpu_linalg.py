@@ -553,3 +553,19 @@ def test_sparse_matrix_with_many_columns(rows, ncols):
     for K in (k for k in (1, 4, 16) if k <= rows):
         for cfg in (None, jacc.config(order=4)):
             assert np.array_equal(_spmv_dev(rp, col, val, x, K, cfg), ref), (K, cfg)
+
+
+@pytest.mark.parametrize("M,N,L", [(3, 3, 1 << 22), (17, 40, (1 << 22) + 5), (5, (1 << 25) + 3, 3), (33, 1 << 25, 2),
+                                   (65, (1 << 25) + 1, 2)])
+def test_gemm_beyond_32_bit_offsets(M, N, L):
+    """Rows of A from 2^22 elements and rows of B from 2^25 (a lane's offsets
+    take 64 bits), for each of the tiles that such shapes take: exact for
+    integer inputs."""
+    say(f"gemm {M}x{N}x{L}")
+    r = np.random.default_rng(M)
+    A = r.integers(-8, 9, (M, L)).astype(np.float64)
+    B = r.integers(-8, 9, (L, N), dtype=np.int8).astype(np.float64)
+    C = _gemm_dev(A, B, 1, whole=jacc.SHARED)
+    say("  product done")
+    for c0 in range(0, N, 1 << 22):
+        assert np.array_equal(C[:, c0:c0 + (1 << 22)], A @ B[:, c0:c0 + (1 << 22)])
