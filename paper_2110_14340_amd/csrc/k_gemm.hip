@@ -248,12 +248,23 @@ hipError_t launch_gemm(const Launch &L, hipStream_t s) {
     const int64_t m = L.hi[0] - L.lo[0], n = L.hi[1] - L.lo[1];
     if (m <= 0 || n <= 0) return hipSuccess;
     const int64_t K = L.a[0].row_elems, N = L.a[2].row_elems;
-    const int64_t parts = L.beside > 1 ? L.beside : 1;  // launches of the loop running side by side
     auto tiles = [](int64_t e, int blocks) { return (e + 32 * blocks - 1) / (32 * blocks); };
+    // more of the smallest tiles than a launch has room for (2^29 rows of one
+    // column): the rows in two launches
+    if (tiles(m, 1) * tiles(n, 2) > max_groups(kGemmThreads) - 7) {
+        if (m <= 32) return hipErrorInvalidValue;
+        Launch half = L;
+        half.hi[0] = L.lo[0] + (m / 2 + 31) / 32 * 32;  // less than m
+        const hipError_t e = launch_gemm(half, s);
+        if (e != hipSuccess) return e;
+        half.lo[0] = half.hi[0];
+        half.hi[0] = L.hi[0];
+        return launch_gemm(half, s);
+    }
+    const int64_t parts = L.beside > 1 ? L.beside : 1;  // launches of the loop running side by side
 #define GEMM_LAUNCH(MI, NJ, S, PAIR, OFF)                                                                              \
     do {                                                                                                               \
         const int64_t tm = tiles(m, MI), tn = tiles(n, NJ);                                                            \
-        if (tm * tn > INT32_MAX - 7) return hipErrorInvalidValue;                                                      \
         hipLaunchKernelGGL((gemm_kernel<MI, NJ, S, PAIR, OFF>), dim3((unsigned)((tm * tn + 7) / 8 * 8)),               \
                            dim3(kGemmThreads), spread_lds(parts, tm * tn), s, (const double *)L.a[0].ptr, (const double *)L.a[1].ptr,           \
                            (double *)L.a[2].ptr, L.lo[0], L.hi[0], L.lo[1], L.hi[1], K, N, tm, tn);                    \

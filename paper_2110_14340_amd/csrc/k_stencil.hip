@@ -1236,7 +1236,7 @@ bool make_merged(const Launch &L, PTask *t) {
 }
 
 hipError_t launch_merged(const PTask *tasks, int ntasks, int64_t workgroups, bool nt, hipStream_t s) {
-    if (ntasks < 1 || workgroups < 1 || workgroups > (int64_t)INT32_MAX) return hipErrorInvalidValue;
+    if (ntasks < 1 || workgroups < 1 || workgroups > max_groups(kPersistentThreads)) return hipErrorInvalidValue;
 #define MERGED_LAUNCH(N) \
     hipLaunchKernelGGL(merged_kernel<N>, dim3((unsigned)workgroups), dim3(kPersistentThreads), 0, s, tasks, ntasks)
     if (nt)

@@ -6,6 +6,10 @@
 
 namespace jk {
 
+// Workgroups of `threads` threads that one launch takes: its threads along a
+// dimension stay below 2^32.
+constexpr int64_t max_groups(int threads) { return (((int64_t)1 << 32) - 1) / threads; }
+
 // One argument as a kernel sees it: `ptr` is the device address of global
 // row 0 of the array *as if* the slab started there (slab pointer minus
 // slab_lo rows), so kernels index with global row numbers; only rows

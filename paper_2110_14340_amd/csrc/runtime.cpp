@@ -980,7 +980,7 @@ int flush_merged(jacc_ctx *c) {
             continue;
         }
         const bool fits = loops.size() > 1 && B->merged_used + n < kMergeCapacity && jk::make_merged(L, &t) &&
-                          workgroups + t.ntiles < INT32_MAX - 8;
+                          workgroups + t.ntiles < jk::max_groups(jk::kPersistentThreads) - 8;
         if (!fits) {
             HIPCHK(c, jk::launch_loop(L, c->st[0].s), "kernel launch");
         } else if (t.ntiles > 0) {

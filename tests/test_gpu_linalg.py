@@ -569,3 +569,13 @@ def test_gemm_beyond_32_bit_offsets(M, N, L):
     say("  product done")
     for c0 in range(0, N, 1 << 22):
         assert np.array_equal(C[:, c0:c0 + (1 << 22)], A @ B[:, c0:c0 + (1 << 22)])
+
+
+def test_gemm_of_more_rows_than_a_launch_has_tiles_for():
+    """2^29 and more rows of one column: their 32-row tiles are more workgroups
+    than one launch takes."""
+    m = (1 << 29) + 77
+    say(f"gemm {m}x1x1")
+    A = np.arange(m, dtype=np.float64).reshape(m, 1)
+    C = _gemm_dev(A, np.array([[3.0]]), 1)
+    assert np.array_equal(C, 3.0 * A)
