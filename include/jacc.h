@@ -327,10 +327,11 @@ enum {
  *   JACC_COHERENCE=lazy|eager add JACC_INIT_LAZY / _EAGER unless the caller chose one
  *   JACC_TUNE=model|off|exhaustive
  *                             what a stencil loop called with cfg = NULL outside a batch
- *                             runs: the attached model's pick (model, the default), the
- *                             library defaults (off), or jacc_tune's best non-persistent
- *                             candidate at the arrays' K, tuned once per loop signature
- *                             and kept for the context (exhaustive)
+ *                             runs: the attached model's pick (model, the default; rows
+ *                             of odd length keep the defaults), the library defaults
+ *                             (off), or jacc_tune's best non-persistent candidate at the
+ *                             arrays' K or the defaults, whichever is faster, timed once
+ *                             per loop signature and kept for the context (exhaustive)
  *   JACC_TUNE_DB=<path>       timing database of the exhaustive mode
  *   JACC_MODEL_PATH=<path>    a cost-model file loaded and attached at init; a file that
  *                             does not load leaves the context without a model (the

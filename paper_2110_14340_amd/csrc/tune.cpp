@@ -148,7 +148,8 @@ std::string build_key(jacc_ctx *c) {
 // ---- timing database --------------------------------------------------------
 // Text lines: "@ <build key>" opens a section; an entry is
 //   <kind> <e0> <e1> <e2> <K> <bx> <by> <tile> <vec> <persistent> <rows> <n> <s_1> ... <s_n>
-// (e2 = 0 for 2-D).  '#' starts a comment line.
+// (e2 = 0 for 2-D; bx = 0: the library's defaults, which are no candidate).
+// '#' starts a comment line.
 struct DbKey {
     int kind;
     int64_t e[3];
@@ -538,6 +539,42 @@ int load_model(jacc_ctx *ctx, const char *path) {
 
 }  // namespace
 
+namespace {
+
+// Median time of the loop under the library's defaults, from the database (its
+// row has bx = 0) or timed as the candidates are and recorded there.
+int default_ms(jacc_ctx *c, int kind, const jacc_bounds *b, const jacc_arg *args, const double *scalars, int nscalars,
+               const int64_t *e, int ndim, int K, const jacc_tune_opts &o, double *ms) {
+    Db db;
+    if (o.db_path) {
+        const std::string why = db_read(o.db_path, &db);
+        if (!why.empty()) return jr::error(c, JACC_ERR_INVALID, why.c_str());
+    }
+    jacc_candidate none{};
+    none.K = K;
+    auto &sec = db.sections[build_key(c)];
+    const DbKey key = db_key(kind, e, ndim, none);
+    auto hit = sec.find(key);
+    if (hit == sec.end()) {
+        Replica rep;
+        int rc = make_replica(c, args, K, rep);
+        if (rc) return rc;
+        jacc_arg targs[2] = {args[0], args[1]};
+        targs[0].host = rep.in.data();
+        targs[1].host = rep.out.data();
+        std::vector<double> t;
+        rc = time_candidate(c, kind, b, targs, scalars, nscalars, none.cfg, 1, 3, 1, t);
+        if (!rc) rc = time_candidate(c, kind, b, targs, scalars, nscalars, none.cfg, 1, 5, sweeps_for(median_of(t)), t);
+        if (rc) return rc;
+        hit = sec.emplace(key, t).first;
+        if (o.db_path && !db_write(o.db_path, db)) return jr::error(c, JACC_ERR_INVALID, "cannot write timing database");
+    }
+    *ms = median_of(hit->second);
+    return JACC_OK;
+}
+
+}  // namespace
+
 namespace jr {
 bool model_config(jacc_ctx *c, int kind, const int64_t *extent, int ndim, int K, jacc_config *cfg) {
     CostModel *cm = (CostModel *)attached_model(c);
@@ -549,6 +586,9 @@ bool model_config(jacc_ctx *c, int kind, const int64_t *extent, int ndim, int K,
         *cfg = it->second;
         return true;
     }
+    // rows of odd length keep the defaults, which take two doubles a lane there;
+    // the candidates take one (95x131x203 heat steps: 14.0 us and 21.5)
+    if (extent[ndim - 1] % 2) return false;
     if (in_batch(c) || failed(c)) return false;  // no device work while a capture is open
     jacc_candidate best;
     if (pick(c, cm, kind, extent, ndim, &K, 1, true, &best, nullptr, 0, nullptr) != JACC_OK) return false;
@@ -570,10 +610,11 @@ bool tuned_config(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const 
     }
     auto &picks = tuned_picks(c);
     auto it = picks.find(sig);
-    if (it != picks.end()) {
-        *cfg = it->second;
-        return true;
-    }
+    auto take = [&](const jacc_config &p) {  // zero fields: the defaults won
+        *cfg = p;
+        return p.bx > 0;
+    };
+    if (it != picks.end()) return take(it->second);
     if (in_batch(c) || failed(c) || dry(c)) return false;
     const std::vector<jacc_candidate> cands = enumerate(kind, e, ndim, &K, 1);
     if (cands.empty()) return false;
@@ -591,9 +632,12 @@ bool tuned_config(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const 
     for (int i = 0; i < n && i < (int)med.size(); ++i)
         if (!cands[(size_t)i].cfg.persistent && (bi < 0 || med[(size_t)i] < med[(size_t)bi])) bi = i;
     if (bi < 0) return false;
-    picks[sig] = cands[(size_t)bi].cfg;
-    *cfg = cands[(size_t)bi].cfg;
-    return true;
+    // the defaults may beat every candidate (on rows of odd length, where those
+    // take one double a lane; by their tile orders): they run unless one is faster
+    double ms = 0.0;
+    if (default_ms(c, kind, b, args, scalars, nscalars, e, ndim, K, o, &ms) != JACC_OK) return false;
+    picks[sig] = med[(size_t)bi] < ms ? cands[(size_t)bi].cfg : jacc_config{};
+    return take(picks[sig]);
 }
 }  // namespace jr
 
@@ -749,6 +793,7 @@ int jacc_model_train(jacc_ctx *ctx, const char *db_path, const char *out_path, c
         std::map<std::vector<int64_t>, int> sig_index;
         for (const auto &kv : it->second) {
             const DbKey &k = kv.first;
+            if (k.bx == 0) continue;  // the defaults' time
             const std::vector<int64_t> sig = {k.kind, k.e[0], k.e[1], k.e[2]};
             auto si = sig_index.emplace(sig, (int)sig_index.size()).first;
             const bool held = holdout > 0 && si->second % holdout == holdout - 1;

@@ -4,6 +4,8 @@ reused, tuning never writes the caller's arrays, a cost model trained on
 the GPU from the database is written, loaded and picks the argmin of its
 predictions, a loop without a configuration runs the model's pick with
 unchanged results, and a corrupt model file falls back to the tuner."""
+import json
+
 import numpy as np
 import pytest
 
@@ -86,3 +88,75 @@ def test_corrupt_model_falls_back_to_the_tuner(tmp_path):
         assert cand in jacc.candidates((66, 130), [1, 2])
         cand, src = c.choose(u, v, model_path=str(bad), tune=False)
         assert src == jacc.CHOICE_DEFAULT and cand["K"] == 2
+
+
+def _database(path, key, shape, K, ms, default_ms):
+    """A timing database in which every candidate of the shape takes `ms`(index)
+    and the library's defaults (the row with bx = 0) `default_ms`."""
+    kind = jacc.stencil_kind(shape)
+    e = list(shape) + [0] * (3 - len(shape))
+    lines = [f"@ {key}"]
+    for i, c in enumerate(jacc.candidates(shape, [K])):
+        lines.append(" ".join(map(str, [kind, *e, K, c["bx"], c["by"], c["tile"], c["vec"], c["persistent"], c["rows"], 1,
+                                        ms(i)])))
+    if default_ms:
+        lines.append(" ".join(map(str, [kind, *e, K, 0, 0, 0, 0, 0, 0, 1, default_ms])))
+    path.write_text("\n".join(lines) + "\n")
+
+
+def _record_of_one_sweep(shape, K, monkeypatch, tmp_path, model=None):
+    log = tmp_path / "loops.jsonl"
+    monkeypatch.setenv("JACC_LOG", str(log))
+    u0 = inputs.jacobi_grid(*shape, seed=1)
+    a, b = u0.copy(), u0.copy()
+    with context(K) as c:
+        if model:
+            c.model_load(model)
+        c.enter(a, halo=(1, 1))
+        c.enter(b, halo=(1, 1))
+        c.jacobi2d(a, b)
+        c.exit(b)
+    assert np.array_equal(b, oracle.jacobi2d(u0, 1))
+    return json.loads(log.read_text().splitlines()[-1])["cfg"]
+
+
+@pytest.mark.parametrize("shape", [(66, 131), (66, 130)])
+@pytest.mark.parametrize("faster", ["defaults", "candidate"])
+def test_exhaustive_tuning_runs_the_defaults_unless_a_candidate_is_faster(shape, faster, monkeypatch, tmp_path):
+    """By recorded times: the defaults (two doubles a lane in rows of odd length
+    too) where they are as fast as every candidate, else the fastest one."""
+    say(f"tuned or default {shape} {faster}")
+    db = tmp_path / "t.db"
+    with context(1) as c:
+        key = c.build_key()
+    best = 17
+    _database(db, key, shape, 1, lambda i: 1.0 if i == best else 2.0, 1.0 if faster == "defaults" else 1.5)
+    monkeypatch.setenv("JACC_TUNE", "exhaustive")
+    monkeypatch.setenv("JACC_TUNE_DB", str(db))
+    cfg = _record_of_one_sweep(shape, 1, monkeypatch, tmp_path)
+    want = jacc.candidates(shape, [1])[best]
+    picked = all(cfg[k] == want[k] for k in ("bx", "by", "tile", "vec"))
+    assert picked == (faster == "candidate")
+    if faster == "defaults":
+        assert cfg["vec"] == 2
+
+
+def test_defaults_are_timed_and_recorded_once_and_no_training_row(monkeypatch, tmp_path):
+    say("defaults in the timing database")
+    db, shape = tmp_path / "t.db", (66, 131)
+    with context(1) as c:
+        key = c.build_key()
+    _database(db, key, shape, 1, lambda i: 1.0, 0)
+    n = len(jacc.candidates(shape, [1]))
+    monkeypatch.setenv("JACC_TUNE", "exhaustive")
+    monkeypatch.setenv("JACC_TUNE_DB", str(db))
+    for _ in range(2):
+        _record_of_one_sweep(shape, 1, monkeypatch, tmp_path)
+        rows = [ln for ln in db.read_text().splitlines() if ln[0] not in "#@"]
+        assert len(rows) == n + 1 and sum(ln.split()[5] == "0" for ln in rows) == 1
+    monkeypatch.setenv("JACC_TUNE", "model")
+    path = str(tmp_path / "model.bin")
+    with context(1) as c:
+        assert c.model_train(str(db), path, members=1, epochs=2)["rows"] == n
+    # with the model attached, rows of odd length keep the defaults
+    assert _record_of_one_sweep(shape, 1, monkeypatch, tmp_path, model=path)["vec"] == 2
