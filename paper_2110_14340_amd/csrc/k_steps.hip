@@ -123,6 +123,13 @@ int64_t chain_tiles(const Chain &ch, int T, int64_t *gx) {
 
 }  // namespace
 
+// A region takes its 32 or 64 rows' time whatever the box fills of them, so wide
+// boxes of few rows take a launch a step (us a step alone and in chains of 40:
+// 1000000 columns, 1 row 7.8 and 29, 6 rows 19 and 30, 12 rows 32 and 31; 200000
+// columns, 1 row 3.6 and 6.7, 6 rows 6.8 and 7.2, 12 rows 9.8 and 7.5; 20000
+// columns, 1 row 3.1 and 1.5).
+bool steps_share(const Chain &ch) { return ch.hi[0] - ch.lo[0] >= 12 || ch.hi[1] - ch.lo[1] < 50000; }
+
 hipError_t launch_steps(const Chain &ch, int steps, hipStream_t s) {
     if (ch.n < 1 || ch.n > kMaxPack || steps < 1 || steps > kChainMax || steps % 2 == 0) return hipErrorInvalidValue;
     if (ch.hi[0] <= ch.lo[0] || ch.hi[1] <= ch.lo[1]) return hipSuccess;

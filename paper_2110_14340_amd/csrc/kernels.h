@@ -188,6 +188,8 @@ struct Chain {
     int64_t ny, nx, lo[2], hi[2];
 };
 hipError_t launch_steps(const Chain &ch, int steps, hipStream_t s);
+// Whether steps over that box gain by sharing launches.
+bool steps_share(const Chain &ch);
 
 // Workgroup partials a packed heat launch with a residual writes.
 int64_t parts_partials(const Launch *L, int n);

@@ -937,7 +937,7 @@ int launch_tasks(jacc_ctx *c, std::vector<jk::PTask> &tasks, const std::vector<P
 int issue_chain(jacc_ctx *c, int steps) {
     StepChain &C = c->chain;
     const int before = steps - 1;
-    int launches = (before + jk::kChainMax - 1) / jk::kChainMax;
+    int launches = jk::steps_share(C.ch[0]) ? (before + jk::kChainMax - 1) / jk::kChainMax : before;
     if ((before - launches) % 2) ++launches;
     for (int l = 0, done = 0; l <= launches; ++l) {
         const int pairs = l < launches ? (before - launches) / 2 : 0;

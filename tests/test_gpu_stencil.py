@@ -404,3 +404,24 @@ def test_packed_totals_have_the_unpacked_bits(K):
             vals += list(c.reductions(0, 12)) + list(c.reductions(20, 12))
         got.append(np.array(vals))
     assert np.array_equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("shape", [(13, 50001), (13, 50003), (14, 50003)])
+def test_captured_steps_of_wide_boxes(shape):
+    """Persistent steps on both sides of the box that takes a launch a step (11
+    rows of 50000 columns): both arrays end as the single steps leave them."""
+    say(f"captured steps {shape}")
+    u0 = inputs.jacobi_grid(*shape, seed=2)
+    cfg = jacc.config(persistent=1)
+    for K in (1, 4):
+        a, b = u0.copy(), u0.copy()
+        with context(K) as c:
+            c.enter(a, halo=(1, 1))
+            c.enter(b, halo=(1, 1))
+            c.batch_begin()
+            for k in range(12):
+                c.jacobi2d(*((a, b) if k % 2 == 0 else (b, a)), cfg=cfg)
+            c.batch_end()
+            c.exit(b)
+            c.exit(a)
+        assert np.array_equal(a, oracle.jacobi2d(u0, 12)) and np.array_equal(b, oracle.jacobi2d(u0, 11)), K
