@@ -83,17 +83,22 @@ Cfg default_config(int kind, const Launch &L, Cfg c) {
             // us, 2.9 as 64x4 of 1)
             const bool tiny = cells < 4096;
             const bool along = tiny || (!cached && ((L.ext[1] + 511) / 512) % 8 == 0);
-            if (!c.bx && !c.by && !along) {
-                c.bx = 64;
-                c.by = 4;
-            }
-            if (!c.bx) c.bx = 256;
-            if (!c.by) c.by = 1;
             // short tiles while there are few of them (512^2: 3.9 us with 2
             // rows, 4.3 with 4, 5.4 with 8; 2048^2: 12.3 with 4, 11.9 with 8)
             // (several partitions in a launch: 4, 1175x780 over 8 8.5 us, 8.9 with 2)
             const bool split = 3 * L.part_rows < 2 * L.ext[0];
-            if (!c.tile) c.tile = !cached || tiny ? 4 : cells < (1 << 20) && !split ? 2 : cells < (1 << 22) ? 4 : 8;
+            const int tile = c.tile ? c.tile : !cached || tiny ? 4 : cells < (1 << 20) && !split ? 2 : cells < (1 << 22) ? 4 : 8;
+            c.tile = tile;
+            if (!c.bx && !c.by && !along) {
+                // no more row groups than a partition's rows fill (us a sweep as
+                // 64x4 and so: 8x1000000 over 4 partitions 62 and 28, 10x500000 over
+                // 4 34 and 18, 20x300000 over 2 19.4 and 17.3)
+                const int64_t groups = (L.part_rows + tile - 1) / tile;
+                c.by = groups <= 1 ? 1 : groups == 2 ? 2 : 4;
+                c.bx = 256 / c.by;
+            }
+            if (!c.bx) c.bx = 256;
+            if (!c.by) c.by = 1;
             if (!c.order) c.order = cached ? 2 : 1;
             break;
         }

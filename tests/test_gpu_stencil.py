@@ -406,6 +406,28 @@ def test_packed_totals_have_the_unpacked_bits(K):
     assert np.array_equal(got[0], got[1])
 
 
+@pytest.mark.parametrize("shape,K", [((3, 5000), 1), ((6, 9001), 4), ((9, 3000), 2), ((11, 7004), 3), ((19, 6002), 2),
+                                     ((40, 6001), 4), ((34, 66000), 1), ((70, 8192), 8)])
+def test_default_shapes_of_few_rows_and_wide_rows(shape, K):
+    """Defaults whose row groups follow a partition's rows (1, 2 and 4 groups, a
+    partition of one row): eager and captured sweeps equal the oracle."""
+    say(f"default jacobi {shape} K={K}")
+    u0 = inputs.jacobi_grid(*shape, seed=shape[0])
+    want = oracle.jacobi2d(u0, 3)
+    assert np.array_equal(run_jacobi(u0, 3, K), want)
+    a, b = u0.copy(), u0.copy()
+    with context(K) as c:
+        c.enter(a, halo=(1, 1))
+        c.enter(b, halo=(1, 1))
+        c.batch_begin()
+        c.jacobi2d(a, b)
+        c.jacobi2d(b, a)
+        c.jacobi2d(a, b)
+        c.batch_end()
+        c.exit(b)
+    assert np.array_equal(b, want)
+
+
 @pytest.mark.parametrize("shape", [(13, 50001), (13, 50003), (14, 50003)])
 def test_captured_steps_of_wide_boxes(shape):
     """Persistent steps on both sides of the box that takes a launch a step (11
