@@ -71,18 +71,26 @@ Cfg default_config(int kind, const Launch &L, Cfg c) {
                 if (!c.order) c.order = 1;
                 break;
             }
-            // 256x1 threads when a row's tiles are a multiple of the 8 XCDs: the
-            // tile below then runs on the same XCD, and the rows both need meet
-            // in its L2 (8192^2: 171 us, 177 as 64x4).  Otherwise 64x4, whose
-            // waves share those rows within the workgroup (5000^2: 75 us as
-            // 256x1, 69 as 64x4; 6000^2 108 and 98).
+            // Beyond the cache: 64x4 threads, whose waves share the rows beside
+            // theirs within the workgroup, in rows of whole 64-byte pieces (us a
+            // sweep of 2^26 cells as 256x1 and 64x4: 3696 columns 185 and 170, 5744
+            // 188 and 170, 11888 183 and 170); in other rows a tile's ends are
+            // parts of lines that two workgroups touch, and 256x1 has fewer ends
+            // (4306 columns 177 and 187, 6556 175 and 185, 12700 175 and 194).  256x1
+            // also in rows of 4096 columns or a multiple, where the tile below runs
+            // on the same XCD (8192^2: 171 and 174), and from 2^16 columns on
+            // (33x3000000: 257 and 270).  Column slabs, whose pitch is their own:
+            // 64x4 unless the tile below runs on the same XCD (10001x6001 over 8: 178,
+            // 196 as 256x1).
             const bool cached = cache_resident(L);
             const int64_t cells = array_bytes(L) / 8;
             // under 4096 cells a step is its launch, and the shape stays
             // 256x1 of 4 rows, as loop records report it (60x60 in a graph: 3.6
             // us, 2.9 as 64x4 of 1)
             const bool tiny = cells < 4096;
-            const bool along = tiny || (!cached && ((L.ext[1] + 511) / 512) % 8 == 0);
+            const int64_t nx = L.ext[1];
+            const bool along = tiny || (!cached && (L.part_dim == 1 ? (nx + 511) / 512 % 8 == 0
+                                                                    : nx % 8 != 0 || nx % 4096 == 0 || nx >= (1 << 16)));
             // short tiles while there are few of them (512^2: 3.9 us with 2
             // rows, 4.3 with 4, 5.4 with 8; 2048^2: 12.3 with 4, 11.9 with 8)
             // (several partitions in a launch: 4, 1175x780 over 8 8.5 us, 8.9 with 2)

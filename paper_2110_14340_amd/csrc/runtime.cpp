@@ -1292,6 +1292,7 @@ int prepare_loop(jacc_ctx *c, int kind, const jacc_bounds *b, int nargs, const j
         }
     }
     jk::Cfg cf{};
+    L.part_dim = pd;
     L.part_rows = 0;
     for (const PartPlan &pp : plan)
         L.part_rows = std::max(L.part_rows, pd == 0 ? pp.iters.hi - pp.iters.lo

@@ -407,10 +407,12 @@ def test_packed_totals_have_the_unpacked_bits(K):
 
 
 @pytest.mark.parametrize("shape,K", [((3, 5000), 1), ((6, 9001), 4), ((9, 3000), 2), ((11, 7004), 3), ((19, 6002), 2),
-                                     ((40, 6001), 4), ((34, 66000), 1), ((70, 8192), 8)])
+                                     ((40, 6001), 4), ((34, 66000), 1), ((70, 8192), 8), ((2100, 8200), 1),
+                                     ((2050, 8206), 3)])
 def test_default_shapes_of_few_rows_and_wide_rows(shape, K):
     """Defaults whose row groups follow a partition's rows (1, 2 and 4 groups, a
-    partition of one row): eager and captured sweeps equal the oracle."""
+    partition of one row), and beyond the cache by the rows' alignment: eager
+    and captured sweeps equal the oracle."""
     say(f"default jacobi {shape} K={K}")
     u0 = inputs.jacobi_grid(*shape, seed=shape[0])
     want = oracle.jacobi2d(u0, 3)
