@@ -130,8 +130,13 @@ Cfg default_config(int kind, const Launch &L, Cfg c) {
             }
             const Cfg d = heat_shape(L, c);
             if (!c.bx && !c.by) {
-                c.bx = d.bx;
-                c.by = d.by;
+                // no more row groups than the field's rows fill: with a residual
+                // the waves without rows wait for the others' sums (3000x3x3000
+                // 111 us a step as 64x4, 4x4x1000000 41 as 128x2)
+                const int rows = c.rows ? c.rows : d.rows;
+                const int64_t groups = (L.ext[1] - 2 + rows - 1) / rows;
+                c.by = groups <= 1 ? 1 : groups == 2 && d.by > 2 ? 2 : d.by;
+                c.bx = d.bx * d.by / c.by;
             }
             if (!c.bx) c.bx = 128;
             if (!c.by) c.by = 2;

@@ -449,3 +449,16 @@ def test_captured_steps_of_wide_boxes(shape):
             c.exit(b)
             c.exit(a)
         assert np.array_equal(a, oracle.jacobi2d(u0, 12)) and np.array_equal(b, oracle.jacobi2d(u0, 11)), K
+
+
+@pytest.mark.parametrize("shape,K", [((5, 3, 300), 1), ((9, 4, 701), 2), ((30, 5, 130), 4), ((4, 6, 2000), 1),
+                                     ((40, 8, 33), 3), ((300, 3, 40000), 2)])
+def test_default_heat_shapes_of_few_rows(shape, K):
+    """Default shapes whose row groups follow the field's rows (1, 2 and more
+    groups): field and residuals."""
+    say(f"default heat {shape} K={K}")
+    u0 = inputs.heat_field(*shape, seed=sum(shape))
+    got, res = run_heat(u0, 3, 0.1, K)
+    want, want_res = oracle.heat3d(u0, 3, 0.1)
+    assert np.array_equal(got, want)
+    assert np.all(np.abs(res - want_res) <= 1e-13 * want_res)
