@@ -723,32 +723,24 @@ struct PartDesc {
     double *out;
     int64_t lo0, hi0;     // the partition's iterations along dim 0
     int64_t tiles;         // its tile count
+    int32_t first, span;   // its workgroups in the launch
     int64_t partial_off;   // its first workgroup partial (heat residual)
     Mirrors mir;
 };
 struct PartPack {
-    int32_t begin[kMaxPack];  // the first workgroups again, INT32_MAX past the last partition
+    int32_t begin[kMaxPack];  // the first workgroups, INT32_MAX past the last partition
     PartDesc p[kMaxPack];
     int32_t n;
 };
 typedef const __attribute__((address_space(4))) int32_t ConstInt;
 
-// Partition of workgroup b of a pack, its first workgroup and that of the next
-// one (`end` past the last).  The table is one wide scalar load and no branch: a
-// walk over the descriptors took two dependent loads a partition (over 8
+// Partition of workgroup b of a pack.  The table is one wide scalar load and no
+// branch: a walk over the descriptors took two dependent loads a partition (over 8
 // partitions, 20 sweeps: 2000x900 178 us and 153, 1175x780 166 and 141).
-__device__ __forceinline__ int pack_part(ConstInt *begin, int32_t b, int32_t end, int32_t &first, int32_t &next) {
+__device__ __forceinline__ int pack_part(ConstInt *begin, int32_t b) {
     int q = 0;
-    first = 0;
-    next = end;
 #pragma unroll
-    for (int k = 1; k < kMaxPack; ++k) {
-        const int32_t at = begin[k];
-        const bool mine = at <= b;
-        q += mine ? 1 : 0;
-        first = mine ? at : first;
-        next = !mine && at < next ? at : next;
-    }
+    for (int k = 1; k < kMaxPack; ++k) q += begin[k] <= b ? 1 : 0;
     return q;
 }
 typedef const __attribute__((address_space(4))) PartDesc ConstPart;
@@ -760,6 +752,8 @@ __device__ __forceinline__ PartDesc load_part(ConstPart *p) {
     d.lo0 = p->lo0;
     d.hi0 = p->hi0;
     d.tiles = p->tiles;
+    d.first = p->first;
+    d.span = p->span;
     d.partial_off = p->partial_off;
     d.mir.n = p->mir.n;
     for (int k = 0; k < 2; ++k) {
@@ -774,11 +768,9 @@ __device__ __forceinline__ PartDesc load_part(ConstPart *p) {
 // a padding workgroup).
 __device__ __forceinline__ int64_t part_tile(const PartPack &pk, int order, PartDesc &d) {
     ConstPart *cp = (ConstPart *)&pk.p[0];
-    int32_t first, next;
-    const int q = pack_part((ConstInt *)&pk.begin[0], blockIdx.x, gridDim.x, first, next);
-    d = load_part(cp + q);
-    const int32_t span = next - first, local = (int32_t)blockIdx.x - first;
-    const int64_t t = order >= 2 ? (local & 7) * (span >> 3) + (local >> 3) : local;
+    d = load_part(cp + pack_part((ConstInt *)&pk.begin[0], blockIdx.x));
+    const int32_t local = (int32_t)blockIdx.x - d.first;
+    const int64_t t = order >= 2 ? (local & 7) * (d.span >> 3) + (local >> 3) : local;
     return t < d.tiles ? t : -1;
 }
 
@@ -799,6 +791,7 @@ struct ColPartDesc {
     const double *in;
     double *out;
     int64_t tiles;                     // its tile count
+    int32_t first, span;               // its workgroups in the launch
     int64_t c_lo, c_hi, col0, pitch;  // its columns, first lane column, slab row pitch
     int64_t gx;                        // tiles per row of tiles
     ColMirrors mir;
@@ -815,6 +808,8 @@ __device__ __forceinline__ ColPartDesc load_colpart(ConstColPart *p) {
     d.in = p->in;
     d.out = p->out;
     d.tiles = p->tiles;
+    d.first = p->first;
+    d.span = p->span;
     d.c_lo = p->c_lo;
     d.c_hi = p->c_hi;
     d.col0 = p->col0;
@@ -834,11 +829,9 @@ template <int V, bool NT>
 __global__ void __launch_bounds__(1024)
 jacobi2d_colparts_kernel(ColPartPack pk, int64_t nx, int64_t r_lo, int64_t r_hi, int tile, int march, int order) {
     ConstColPart *cp = (ConstColPart *)&pk.p[0];
-    int32_t first, next;
-    const int q = pack_part((ConstInt *)&pk.begin[0], blockIdx.x, gridDim.x, first, next);
-    const ColPartDesc d = load_colpart(cp + q);
-    const int32_t span = next - first, local = (int32_t)blockIdx.x - first;
-    const int64_t t = order >= 2 ? (local & 7) * (span >> 3) + (local >> 3) : local;
+    const ColPartDesc d = load_colpart(cp + pack_part((ConstInt *)&pk.begin[0], blockIdx.x));
+    const int32_t local = (int32_t)blockIdx.x - d.first;
+    const int64_t t = order >= 2 ? (local & 7) * (d.span >> 3) + (local >> 3) : local;
     if (t >= d.tiles) return;
     jacobi_tile<V, 4, NT, ColMirrors>(d.in, d.out, nx, d.pitch, r_lo, r_hi, d.c_lo, d.c_hi, d.col0, tile, march, d.mir,
                                     mod32(t, d.gx), div32(t, d.gx), threadIdx.x, threadIdx.y, blockDim.x, blockDim.y);
@@ -1048,7 +1041,10 @@ static hipError_t launch_col_parts(const Launch *L, int n, hipStream_t s) {
         d.pitch = Lk.a[0].row_elems;
         d.gx = gx;
         d.mir = Lk.cmir;
-        begin += xcd ? (tiles + 7) / 8 * 8 : tiles;
+        const int64_t span = xcd ? (tiles + 7) / 8 * 8 : tiles;
+        d.first = (int32_t)begin;
+        d.span = (int32_t)span;
+        begin += span;
     }
     if (pk.n == 0) return hipSuccess;
     if (begin > (int64_t)INT32_MAX) return hipErrorInvalidValue;
@@ -1112,7 +1108,10 @@ hipError_t launch_parts(const Launch *L, int n, double *wg_partials, int64_t wg_
         pk.begin[pk.n - 1] = (int32_t)begin;
         d.partial_off = partial;
         d.mir = Lk.mir;
-        begin += xcd ? (tiles + 7) / 8 * 8 : tiles;
+        const int64_t span = xcd ? (tiles + 7) / 8 * 8 : tiles;
+        d.first = (int32_t)begin;
+        d.span = (int32_t)span;
+        begin += span;
         if (res) partial += tiles;
     }
     if (partial > wg_capacity || begin > (int64_t)INT32_MAX) return hipErrorInvalidValue;
