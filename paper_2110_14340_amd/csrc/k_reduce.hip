@@ -121,14 +121,6 @@ finalise_kernel(const double *__restrict__ p, int64_t n, double *__restrict__ ou
     if (threadIdx.x == 0) *out = s;
 }
 
-// Workgroup k finalises segment k (the same additions as finalise_kernel).
-__global__ void __launch_bounds__(kFinThreads) finalise_many_kernel(const double *__restrict__ base, Segments seg) {
-    __shared__ double sh[kFinThreads / kWave];
-    const int k = blockIdx.x;
-    const double s = finalise_block(base + seg.off[k], seg.n[k], sh);
-    if (threadIdx.x == 0) *seg.out[k] = s;
-}
-
 __global__ void combine_kernel(const double *__restrict__ partials, CombineList list, double *__restrict__ out,
                                double *__restrict__ host) {
     if (threadIdx.x == 0 && blockIdx.x == 0) {
@@ -220,8 +212,7 @@ hipError_t launch_sum_parts(const Launch *L, int n, double *wg_partials, int64_t
         hipLaunchKernelGGL(sum_parts_kernel<false>, dim3((unsigned)wg), dim3(kSumThreads), 0, s, sp);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return L[0].total ? launch_total(wg_partials, seg, L[0].ticket, L[0].total, L[0].total_host, s)
-                      : launch_finalise_many(wg_partials, seg, s);
+    return launch_total(wg_partials, seg, L[0].ticket, L[0].total, L[0].total_host, s);
 }
 
 hipError_t launch_result(const Launch &L, int64_t n, hipStream_t s) {
@@ -234,7 +225,7 @@ hipError_t launch_result(const Launch &L, int64_t n, hipStream_t s) {
 
 hipError_t launch_total(const double *base, const Segments &seg, unsigned *ticket, double *total, double *host,
                         hipStream_t s) {
-    if (seg.count <= 0 || seg.count > kMaxPack) return hipErrorInvalidValue;
+    if (seg.count <= 0 || seg.count > kMaxPack || !total) return hipErrorInvalidValue;
     if (seg.count > 1 && !ticket) return hipErrorInvalidValue;
     hipLaunchKernelGGL(total_kernel, dim3((unsigned)seg.count), dim3(kFinThreads), 0, s, base, seg, ticket, total, host);
     return hipGetLastError();
@@ -242,13 +233,6 @@ hipError_t launch_total(const double *base, const Segments &seg, unsigned *ticke
 
 hipError_t launch_finalise(const double *partials, int64_t n, double *out, hipStream_t s) {
     hipLaunchKernelGGL(finalise_kernel, dim3(1), dim3(kFinThreads), 0, s, partials, n, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_finalise_many(const double *base, const Segments &seg, hipStream_t s) {
-    if (seg.count <= 0) return hipSuccess;
-    if (seg.count > kMaxPack) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(finalise_many_kernel, dim3((unsigned)seg.count), dim3(kFinThreads), 0, s, base, seg);
     return hipGetLastError();
 }
 

@@ -1161,8 +1161,7 @@ hipError_t launch_parts(const Launch *L, int n, double *wg_partials, int64_t wg_
         if (e != hipSuccess) return e;
     }
     if (!res) return hipSuccess;
-    return L0.total ? launch_total(wg_partials, seg, L0.ticket, L0.total, L0.total_host, s)
-                    : launch_finalise_many(wg_partials, seg, s);
+    return launch_total(wg_partials, seg, L0.ticket, L0.total, L0.total_host, s);
 }
 
 bool make_task(const Launch &L, PTask *t) {

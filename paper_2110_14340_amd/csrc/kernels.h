@@ -165,8 +165,8 @@ hipError_t launch_merged(const PTask *tasks, int ntasks, int64_t workgroups, boo
 // kMaxPack.  Each partition's tiles take a run of workgroups starting at a
 // multiple of 8, so the XCD-aware tile orders hold within it.  With a
 // residual, partition p's workgroup partials go to wg_partials + (its first
-// tile among all partitions') and one finaliser launch writes every
-// partition's ordered sum to its part_out.  Returns hipErrorInvalidValue
+// tile among all partitions') and one more launch writes every partition's
+// ordered sum to its part_out and their total to the first one's total.  Returns hipErrorInvalidValue
 // for more than kMaxPack launches or more than wg_capacity partials.
 constexpr int kMaxPack = 16;
 hipError_t launch_parts(const Launch *L, int n, double *wg_partials, int64_t wg_capacity, hipStream_t s);
@@ -194,16 +194,14 @@ bool steps_share(const Chain &ch);
 // Workgroup partials a packed heat launch with a residual writes.
 int64_t parts_partials(const Launch *L, int n);
 
-// out[k] = ordered sum of base[off[k] .. off[k] + n[k]) for k < count, each
-// in the finaliser's order (one workgroup per segment).
+// Segments base[off[k] .. off[k] + n[k]) of workgroup partials, k < count.
 struct Segments {
     int64_t off[kMaxPack], n[kMaxPack];
     double *out[kMaxPack];
     int32_t count;
 };
-hipError_t launch_finalise_many(const double *base, const Segments &seg, hipStream_t s);
 // Finaliser and combine in one launch: *total (and *host, unless null) = the
-// segments' ordered sums added in segment order.  Each segment's sum also goes
+// segments' sums, each in the finaliser's order, added in segment order.  Each segment's sum also goes
 // to its `out`, and `ticket` is used, when there are several.
 hipError_t launch_total(const double *base, const Segments &seg, unsigned *ticket, double *total, double *host,
                         hipStream_t s);
