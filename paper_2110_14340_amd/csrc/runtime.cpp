@@ -1363,8 +1363,8 @@ int bin_entries(jacc_ctx *c, Array **arr, const jk::Launch *L, int n, int s, int
 // when the form does not take the matrix or its memory is not to be had: the
 // caller then runs the plain form.  A copy is as large as its rows' entries, and
 // the copies of one matrix together (of its partitions, or of the boxes a
-// program multiplies) hold its entries at most twice: beyond that the one used
-// least recently goes.
+// program multiplies) hold its entries at most twice and are kMaxK at most, the
+// refused ones among them: beyond that the one used least recently goes.
 int bin_cache(jacc_ctx *c, Array **arr, int p, const jk::Launch *L, int n, int s, BinCache **out) {
     Array *rp = arr[0], *col = arr[1], *val = arr[2];
     *out = nullptr;
@@ -1403,13 +1403,15 @@ int bin_cache(jacc_ctx *c, Array **arr, int p, const jk::Launch *L, int n, int s
     if (entries < 0 || !jk::bin_geometry(arr[3]->E, col->E, rp->E - 1, entries, L, n, &bc.bb)) return JACC_OK;
     for (;;) {
         int64_t held = entries;
+        int copies = 1;
         size_t oldest = c->bins.size();
         for (size_t i = 0; i < c->bins.size(); ++i) {
-            if (!same_matrix(c->bins[i]) || c->bins[i].refused) continue;
+            if (!same_matrix(c->bins[i])) continue;
             held += c->bins[i].entries;
+            ++copies;
             if (oldest == c->bins.size() || c->bins[i].used < c->bins[oldest].used) oldest = i;
         }
-        if (held <= 2 * col->E || oldest == c->bins.size()) break;
+        if ((held <= 2 * col->E && copies <= kMaxK) || oldest == c->bins.size()) break;
         rc = drop_bin(c, oldest);
         if (rc) return rc;
     }
@@ -1431,6 +1433,7 @@ int bin_cache(jacc_ctx *c, Array **arr, int p, const jk::Launch *L, int n, int s
             for (int j = 0; j < i; ++j) dev_free(c, bc.bb.mem[j]);
             std::fill(bc.bb.mem, bc.bb.mem + jk::kBinBuffers, nullptr);
             bc.refused = true;
+            bc.entries = 0;
             c->err = err;  // the call goes on with the plain form
         }
     c->bins.push_back(bc);

@@ -1315,3 +1315,25 @@ def test_default_spmv_form_by_the_matrix(rows, ncols, per_row, order, K, monkeyp
     recs = [json.loads(line) for line in path.read_text().splitlines()]
     assert [r["cfg"]["order"] for r in recs] == [order, 4]
     assert recs[0]["packed"] == (K > 1 and ncols >= 1 << 20)
+
+
+@pytest.mark.parametrize("refuse", [False, True])
+def test_binned_copies_of_many_small_boxes_are_few(refuse):
+    """200 boxes of a row each, with and without memory for their copies: at most
+    64 are remembered, so a box that comes back after all the others asks
+    for its memory again."""
+    n = 400
+    rp = (np.arange(n + 1) * 8).astype(np.int32)
+    col, val, x, y = np.zeros(8 * n, np.int32), np.zeros(8 * n), np.zeros(n), np.zeros(n)
+    mem = _Refusing()
+    c = jacc.Context(1, allocator=mem, flags=jacc.INIT_DRYRUN)
+    _dry_product(c, rp, col, val, x, y)
+    held = len(mem.held)
+    mem.refuse = refuse
+    for lo in list(range(200)) + [0]:
+        c.loop(jacc.SPMV_CSR, jacc.bounds((lo, lo + 1)),
+               [(rp, jacc.READ, 0, 1, 0), (col, jacc.READ, 0, 0, 1), (val, jacc.READ, 0, 0, 1),
+                (x, jacc.READ, 0, 0, 1), (y, jacc.WRITE, 0, 0, 0)], cfg=jacc.config(order=4))
+        assert len(mem.held) - held <= 64 * 9
+    assert mem.refused == (201 if refuse else 0)
+    c.close()
