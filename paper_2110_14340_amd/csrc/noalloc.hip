@@ -18,9 +18,9 @@
 #include "kernels.h"
 
 namespace {
-// 65,536 workgroup partials (512 KiB per device): with the default
-// heat launch (256 columns x 8 rows x 8 planes per workgroup) this covers
-// cubes up to 1026^3.
+// 65,536 workgroup partials (512 KiB per device): with the launch that fields of
+// many workgroups take by default (256 columns x 8 rows x 8 planes a
+// workgroup) this covers cubes up to 1026^3.
 constexpr int64_t kScratchDoubles = JACC_NOALLOC_MAX_PARTIALS;
 constexpr int kMaxDevices = 64;
 }  // namespace
