@@ -216,36 +216,11 @@ bin_segments_kernel(const uint16_t *__restrict__ cnt, int nblk, int nc, int per,
     }
 }
 
-// One workgroup: the list of row blocks beyond LDS and of their long rows:
-// over[0] and over[1] their counts, then the blocks, then (block, row within it).
-__global__ void __launch_bounds__(1024) bin_over_kernel(BinParts bp, int rb, int nblk, int32_t *__restrict__ over) {
-    __shared__ int blocks, longs;
-    if (threadIdx.x == 0) blocks = longs = 0;
-    __syncthreads();
-    for (int b = threadIdx.x; b < nblk; b += 1024)
-        if (bin_block(bp, b, rb).m > kBinCap) over[2 + atomicAdd(&blocks, 1)] = b;
-    __syncthreads();
-    for (int i = 0; i < blocks; ++i) {
-        const int b = over[2 + i];
-        const BinBlock B = bin_block(bp, b, rb);
-        for (int r = threadIdx.x; r < B.rows; r += 1024)
-            if (B.rp[B.lo + r + 1] - B.rp[B.lo + r] > kLongRow) {
-                const int at = 2 + blocks + 2 * atomicAdd(&longs, 1);
-                over[at] = b;
-                over[at + 1] = r;
-            }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        over[0] = blocks;
-        over[1] = longs;
-    }
-}
-
 // One workgroup: the start of every column block, aligned to kPad entries
 // (cbase[c]; cbase[nc] the end), and segs turned into the start of each
-// segment within it.
-__global__ void __launch_bounds__(1024) bin_bases_kernel(int nc, int32_t *__restrict__ segs, int32_t *__restrict__ cbase) {
+// segment within it; the counts of `over` are cleared.
+__global__ void __launch_bounds__(1024)
+bin_bases_kernel(int nc, int32_t *__restrict__ segs, int32_t *__restrict__ cbase, int32_t *__restrict__ over) {
     __shared__ int32_t sh[1024];
     int32_t before = 0;
     for (int c0 = 0; c0 < nc; c0 += 1024) {
@@ -280,7 +255,10 @@ __global__ void __launch_bounds__(1024) bin_bases_kernel(int nc, int32_t *__rest
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0) cbase[nc] = before;
+    if (threadIdx.x == 0) {
+        cbase[nc] = before;
+        over[0] = over[1] = 0;
+    }
 }
 
 // start[blk][c]: lane j of a column takes the j-th sixteenth of the segment.
@@ -309,13 +287,16 @@ bin_starts_kernel(const uint16_t *__restrict__ cnt, int nblk, int nc, int per, c
 // column block, place within the row block.  SORT: the entries are ordered by
 // bucket in LDS first, so that a bucket is written by neighbouring lanes
 // (2^22 rows of 16: 2.6 ms with each lane writing its own entry's bucket);
-// the column blocks' counters then have to fit beside them.
+// the column blocks' counters then have to fit beside them.  A row block beyond
+// LDS and its long rows go to the list `over` instead: over[0] and over[1] the
+// counts, from over[2] on the blocks, from over[2 + nblk] on (block, row within
+// it).
 constexpr int kSortCols = 2048;
 template <bool SORT>
 __global__ void __launch_bounds__(1024)
 bin_fill_kernel(BinParts bp, const int32_t *__restrict__ col, const double *__restrict__ val, int rb, int nblk, int nc,
                 const int32_t *__restrict__ start, const uint16_t *__restrict__ cnt, double *__restrict__ bval,
-                uint16_t *__restrict__ bcol, uint16_t *__restrict__ dst) {
+                uint16_t *__restrict__ bcol, uint16_t *__restrict__ dst, int32_t *__restrict__ over) {
     extern __shared__ int32_t at[];  // next free entry of each bucket
     __shared__ double sval[SORT ? kBinCap : 1];
     __shared__ int32_t scol[SORT ? kBinCap : 1];
@@ -325,8 +306,17 @@ bin_fill_kernel(BinParts bp, const int32_t *__restrict__ col, const double *__re
     const int64_t blk = bin_order();
     if (blk >= nblk) return;
     const BinBlock B = bin_block(bp, blk, rb);
-    if (B.m > kBinCap) return;
     const int tid = threadIdx.x;
+    if (B.m > kBinCap) {
+        if (tid == 0) over[2 + atomicAdd(&over[0], 1)] = (int32_t)blk;
+        for (int r = tid; r < B.rows; r += 1024)
+            if (B.rp[B.lo + r + 1] - B.rp[B.lo + r] > kLongRow) {
+                int32_t *at = over + 2 + nblk + 2 * atomicAdd(&over[1], 1);
+                at[0] = (int32_t)blk;
+                at[1] = r;
+            }
+        return;
+    }
     if constexpr (!SORT) {
         for (int c = tid; c < nc; c += 1024) at[c] = start[blk * nc + c];
         __syncthreads();
@@ -389,12 +379,12 @@ typedef uint16_t us2u __attribute__((ext_vector_type(2), aligned(2)));
 // has the products of 16384 entries at a time in LDS and G lanes add them (2^20
 // rows of 3 and one of 200,000: 16.0 ms when the row's block was one workgroup's
 // work and its lanes took an entry at a time).
-__device__ void bin_over_rows(const BinParts &bp, int rb, int G, const int32_t *__restrict__ over,
+__device__ void bin_over_rows(const BinParts &bp, int rb, int nblk, int G, const int32_t *__restrict__ over,
                               const int32_t *__restrict__ col, const double *__restrict__ val,
                               const double *__restrict__ x, double *xs) {
     const int tid = threadIdx.x, per = kMulThreads / G, g = tid & (G - 1);
     const int slices = (rb + per - 1) / per;
-    const int32_t *longs = over + 2 + over[0];
+    const int32_t *longs = over + 2 + nblk;
     for (int64_t u = blockIdx.x; u < (int64_t)over[0] * slices; u += gridDim.x) {
         const BinBlock B = bin_block(bp, over[2 + u / slices], rb);
         const int r = (int)(u % slices) * per + tid / G;
@@ -435,8 +425,8 @@ __device__ void bin_over_rows(const BinParts &bp, int rb, int G, const int32_t *
 __global__ void __launch_bounds__(kMulThreads)
 bin_multiply_kernel(const int32_t *__restrict__ cbase, int nc, int64_t ncols, const double *__restrict__ x,
                     const double *__restrict__ bval, const uint16_t *__restrict__ bcol, double *__restrict__ prod,
-                    BinParts bp, int rb, int G, const int32_t *__restrict__ over, const int32_t *__restrict__ col,
-                    const double *__restrict__ val) {
+                    BinParts bp, int rb, int nblk, int G, const int32_t *__restrict__ over,
+                    const int32_t *__restrict__ col, const double *__restrict__ val) {
     __shared__ double xs[kBinCols];
     const int64_t total = cbase[nc];
     const int64_t per = ((total + gridDim.x - 1) / gridDim.x + kPad - 1) / kPad * kPad;
@@ -477,7 +467,7 @@ bin_multiply_kernel(const int32_t *__restrict__ cbase, int nc, int64_t ncols, co
         for (int64_t i = i0 + threadIdx.x * 4; i < end; i += kMulThreads * 4) four(i);
         i0 = end;
     }
-    if (over[0] != 0) bin_over_rows(bp, rb, G, over, col, val, x, xs);
+    if (over[0] != 0) bin_over_rows(bp, rb, nblk, G, over, col, val, x, xs);
 }
 
 // One row block per workgroup: LB lanes copy a bucket's products to LDS, two
@@ -699,16 +689,15 @@ hipError_t build_bins(const Launch *L, int n, const BinBufs &bb, hipStream_t s) 
     const size_t lds = (size_t)bb.nc * 4;
     hipLaunchKernelGGL(bin_count_kernel, dim3(bin_grid(bb.nblk)), dim3(512), lds, s, bp, col, bb.rb, bb.nblk, bb.nc,
                        bb.cnt());
-    hipLaunchKernelGGL(bin_over_kernel, dim3(1), dim3(1024), 0, s, bp, bb.rb, bb.nblk, bb.over());
     hipLaunchKernelGGL(bin_segments_kernel, scan, dim3(1024), 0, s, bb.cnt(), bb.nblk, bb.nc, per, bb.segs());
-    hipLaunchKernelGGL(bin_bases_kernel, dim3(1), dim3(1024), 0, s, bb.nc, bb.segs(), bb.cbase());
+    hipLaunchKernelGGL(bin_bases_kernel, dim3(1), dim3(1024), 0, s, bb.nc, bb.segs(), bb.cbase(), bb.over());
     hipLaunchKernelGGL(bin_starts_kernel, scan, dim3(1024), 0, s, bb.cnt(), bb.nblk, bb.nc, per, bb.segs(), bb.start());
     if (bb.nc <= kSortCols)
         hipLaunchKernelGGL((bin_fill_kernel<true>), dim3(bin_grid(bb.nblk)), dim3(1024), lds, s, bp, col, val, bb.rb,
-                           bb.nblk, bb.nc, bb.start(), bb.cnt(), bb.bval(), bb.bcol(), bb.dst());
+                           bb.nblk, bb.nc, bb.start(), bb.cnt(), bb.bval(), bb.bcol(), bb.dst(), bb.over());
     else
         hipLaunchKernelGGL((bin_fill_kernel<false>), dim3(bin_grid(bb.nblk)), dim3(1024), lds, s, bp, col, val, bb.rb,
-                           bb.nblk, bb.nc, bb.start(), bb.cnt(), bb.bval(), bb.bcol(), bb.dst());
+                           bb.nblk, bb.nc, bb.start(), bb.cnt(), bb.bval(), bb.bcol(), bb.dst(), bb.over());
     return hipGetLastError();
 }
 
@@ -717,7 +706,7 @@ hipError_t launch_spmv_bins(const Launch *L, int n, const BinBufs &bb, hipStream
     const BinParts bp = bin_parts(L, n, bb.rb);
     const double *x = (const double *)L[0].a[3].ptr;
     hipLaunchKernelGGL(bin_multiply_kernel, dim3(kMulGroups), dim3(kMulThreads), 0, s, bb.cbase(), bb.nc, bb.ncols, x,
-                       bb.bval(), bb.bcol(), bb.prod(), bp, bb.rb, bb.lanes, bb.over(), (const int32_t *)L[0].a[1].ptr,
+                       bb.bval(), bb.bcol(), bb.prod(), bp, bb.rb, bb.nblk, bb.lanes, bb.over(), (const int32_t *)L[0].a[1].ptr,
                        (const double *)L[0].a[2].ptr);
     const bool wide = bin_lanes(bb.nc) == 64;
 #define BIN_SUM(G, LB)                                                                                                 \
