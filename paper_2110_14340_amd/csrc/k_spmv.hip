@@ -14,6 +14,12 @@ namespace {
 
 constexpr int kSpmvThreads = 256;
 
+// Orders a wave's LDS accesses before it and after it.
+__device__ __forceinline__ void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Lane g's share of the row [kb, ke): its entries' products added in increasing
 // k.  Eight of them are in flight at once, so that a long row is not one load's
 // latency after the other.  NT: col and val are read once, so they are loaded
@@ -45,17 +51,62 @@ __device__ __forceinline__ double lane_sum(const int32_t *__restrict__ col, cons
     return s;
 }
 
+constexpr int kWaveRow = 2048;   // entries beyond which a row may be its wave's work
+constexpr int kWaveChunk = 512;  // products of it that the wave has in LDS
+
+// Sum of the row [kb, ke) of this lane's group (none: kb == ke), whole in every
+// lane of the group.  Where a wave has one to five rows (20 / G) of more than
+// kWaveRow entries, its 64 lanes work out their products, 512 at a time in LDS, and
+// G of them add those as the group's own lanes would: 2^18 rows of 3 and one of
+// 200,000 took 3.4 ms with a group's own lanes, 2.0 so.
 template <int G, bool NT>
-__global__ void __launch_bounds__(kSpmvThreads)
+__device__ __forceinline__ double row_sum(const int32_t *__restrict__ col, const double *__restrict__ val,
+                                          const double *__restrict__ x, int32_t kb, int32_t ke, int g,
+                                          double (&sh)[kSpmvThreads / kWave][kWaveChunk]) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const bool is_long = ke - kb > kWaveRow;
+    uint64_t longs = __ballot(is_long && g == 0);
+    if (__popcll(longs) > 20 / G) longs = 0;
+    double s = 0.0;
+    if (!longs || !is_long) s = lane_sum<NT>(col, val, x, kb, ke, g, G);
+    double *buf = sh[threadIdx.x / kWave];
+    for (; longs; longs &= longs - 1) {
+        const int first = __builtin_ctzll(longs);  // the row's first lane
+        const int64_t b = __shfl(kb, first, kWave), e = __shfl(ke, first, kWave);
+        double t = 0.0;
+        for (int64_t k0 = b; k0 < e; k0 += kWaveChunk) {
+            double v[kWaveChunk / kWave];
+#pragma unroll
+            for (int u = 0; u < kWaveChunk / kWave; ++u) {
+                const int64_t k = k0 + u * kWave + lane;
+                v[u] = k < e ? val[k] * x[col[k]] : 0.0;
+            }
+            wave_order();  // the adds of the chunk before are done
+#pragma unroll
+            for (int u = 0; u < kWaveChunk / kWave; ++u) buf[u * kWave + lane] = v[u];
+            wave_order();
+            const int m = (int)(e - k0 < kWaveChunk ? e - k0 : kWaveChunk);
+            if (lane < G)
+#pragma unroll 16
+                for (int k = lane; k < m; k += G) t += buf[k];
+        }
+        t = __shfl(t, g, kWave);
+        if (lane - g == first) s = t;
+    }
+    return group_sum<G>(s);
+}
+
+// Eight waves a SIMD: the gathers' latency is what the plain form waits for.
+template <int G, bool NT>
+__global__ void __launch_bounds__(kSpmvThreads, 8)
 spmv_kernel(const int32_t *__restrict__ rp, const int32_t *__restrict__ col, const double *__restrict__ val,
             const double *__restrict__ x, double *__restrict__ y, int64_t r_lo, int64_t r_hi) {
     const int64_t t = (int64_t)blockIdx.x * kSpmvThreads + threadIdx.x;
     const int64_t i = r_lo + t / G;
     const int g = threadIdx.x & (G - 1);
-    double s = 0.0;
+    __shared__ double sh[kSpmvThreads / kWave][kWaveChunk];
     const bool live = i < r_hi;
-    if (live) s = lane_sum<NT>(col, val, x, rp[i], rp[i + 1], g, G);
-    s = group_sum<G>(s);
+    const double s = row_sum<G, NT>(col, val, x, live ? rp[i] : 0, live ? rp[i + 1] : 0, g, sh);
     if (live && g == 0) y[i] = s;
 }
 
@@ -74,7 +125,7 @@ struct SpmvParts {
 typedef const __attribute__((address_space(4))) SpmvPart ConstSpmvPart;
 
 template <int G>
-__global__ void __launch_bounds__(kSpmvThreads) spmv_parts_kernel(SpmvParts sp) {
+__global__ void __launch_bounds__(kSpmvThreads, 8) spmv_parts_kernel(SpmvParts sp) {
     ConstSpmvPart *cp = (ConstSpmvPart *)&sp.p[0];
     int q = 0;
     for (int k = 1; k < sp.n; ++k)
@@ -82,10 +133,9 @@ __global__ void __launch_bounds__(kSpmvThreads) spmv_parts_kernel(SpmvParts sp) 
     const int64_t i = cp[q].lo + ((blockIdx.x - cp[q].wg_begin) * kSpmvThreads + threadIdx.x) / G;
     const int g = threadIdx.x & (G - 1);
     const bool live = i < cp[q].hi;
+    __shared__ double sh[kSpmvThreads / kWave][kWaveChunk];
     const int32_t *rp = cp[q].rp;
-    double s = 0.0;
-    if (live) s = lane_sum<true>(cp[q].col, cp[q].val, cp[q].x, rp[i], rp[i + 1], g, G);
-    s = group_sum<G>(s);
+    const double s = row_sum<G, true>(cp[q].col, cp[q].val, cp[q].x, live ? rp[i] : 0, live ? rp[i + 1] : 0, g, sh);
     if (live && g == 0) cp[q].y[i] = s;
 }
 

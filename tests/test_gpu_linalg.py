@@ -579,3 +579,26 @@ def test_gemm_of_more_rows_than_a_launch_has_tiles_for():
     A = np.arange(m, dtype=np.float64).reshape(m, 1)
     C = _gemm_dev(A, np.array([[3.0]]), 1)
     assert np.array_equal(C, 3.0 * A)
+
+
+@pytest.mark.parametrize("lanes", [4, 8, 16])
+def test_plain_spmv_long_rows_have_the_same_bits_alone_and_among_others(lanes):
+    """A row on both sides of the length from which a wave works out a row's
+    products together (2048) and of its chunks of 512: alone in a wave, where
+    that is done, and in a wave of such rows, where each has its own lanes."""
+    say(f"plain spmv, long rows, {lanes} lanes")
+    for length in (2047, 2048, 2049, 2559, 2560, 2561, 4100, 30001):
+        rp, col, val, x = _rows_matrix(np.array([length]), 5000, seed=length)
+        bound = 1e-13 * _row_bound(rp, col, val, x)[0]
+        want = oracle.spmv_csr(rp, col, val, x)[0]
+        got = []
+        for many in (False, True):
+            lens = np.full(200, length if many else 3)
+            lens[100] = length
+            rp2 = np.zeros(201, np.int32)
+            np.cumsum(lens, out=rp2[1:])
+            col2, val2 = np.tile(col, 200)[:rp2[-1]].copy(), np.tile(val, 200)[:rp2[-1]].copy()
+            col2[rp2[100]:rp2[101]], val2[rp2[100]:rp2[101]] = col, val
+            for K in (1, 3):
+                got.append(_spmv_dev(rp2, col2, val2, x, K, jacc.config(tile=lanes, order=2))[100])
+        assert abs(got[0] - want) <= bound and all(g == got[0] for g in got), length
