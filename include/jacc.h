@@ -180,7 +180,8 @@ typedef struct {
  *              SpMV bound, and the same bits for every partition count.  It
  *              is the default when x has at least 2^20 elements and the matrix
  *              2^22 entries, one a column and four a bucket (the meeting of a
- *              row block and a column block) on average, except
+ *              row block and a column block) on average (fewer
+ *              entries of its own for a launch of some of the rows), except
  *              inside batches, which capture the plain form (an explicit
  *              order 4 there returns JACC_ERR_UNSUPPORTED).  The plain form
  *              runs instead, also with order 4, where several partitions do

@@ -695,10 +695,17 @@ static int64_t bin_rows(int64_t mean, int64_t nc) {
 // 21 and 40, 74 and 57; 2^27 columns, 1000 rows of 16: 11 and 366) and a bucket
 // four (2^24 columns, 2^22 rows of 4: 332 and 247; 2^26 columns, rows of 16, 1.8 a
 // bucket: 1306 and 1301, and the copy takes 3 ms).
-bool bin_pays(int64_t ncols, int64_t nnz, int64_t rows) {
+// A launch of some of the rows (a partition's, a box's) pays for all of x too, and
+// asks for 5/8 of those entries, and three for four columns (a launch a partition,
+// plain and binned: 2^21 rows of 6 over 4 187 and 146, over 8 198 and 224; 2^20 rows
+// of 16 over 4 187 and 147, over 8 198 and 214, over 20 233 and 415; 2^22 rows of 16
+// over 20 1186 and 810, over 64 1215 and 1740).
+bool bin_pays(int64_t ncols, int64_t nnz, int64_t rows, int64_t launch_rows) {
     if (rows < 1) return false;
     const int64_t nc = (ncols + kBinCols - 1) >> kBinShift, rb = bin_rows((nnz + rows - 1) / rows, nc);
-    return nnz >= ((int64_t)1 << 22) && nnz >= ncols && nnz >= 4 * nc * ((rows + rb - 1) / rb);
+    const int64_t most = (int64_t)1 << 22, here = (int64_t)((double)nnz * ((double)launch_rows / (double)rows));
+    return nnz >= most && nnz >= ncols && nnz >= 4 * nc * ((rows + rb - 1) / rb) &&
+           (launch_rows >= rows || (8 * here > 5 * most && 4 * here >= 3 * ncols));
 }
 
 bool bin_geometry(int64_t ncols, int64_t nnz, int64_t rows, int64_t entries, const Launch *L, int n, BinBufs *bb) {

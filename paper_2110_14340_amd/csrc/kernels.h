@@ -250,9 +250,9 @@ struct BinBufs {
 // Lanes per row by the mean row length of the whole matrix (not by
 // partition: the lanes decide the order of a row's sum).
 int spmv_lanes(int64_t nnz, int64_t rows);
-// Whether the binned form is the faster one for a matrix (by default, from 2^20
-// columns on).
-bool bin_pays(int64_t ncols, int64_t nnz, int64_t rows);
+// Whether the binned form is the faster one for a launch of `launch_rows` of a
+// matrix's rows (by default, from 2^20 columns on).
+bool bin_pays(int64_t ncols, int64_t nnz, int64_t rows, int64_t launch_rows);
 // Geometry for a matrix of `rows` rows and `nnz` entries, and the buffer sizes of
 // a copy of the launches' rows, which hold `entries` of them (false: this form
 // does not take the matrix).

@@ -1463,8 +1463,10 @@ int issue_spmv(jacc_ctx *c, Array **arr, const jacc_arg *args, bool asked, int p
                LoopNote *note) {
     BinCache *bc = nullptr;
     int rc = JACC_OK;
+    int64_t rows = 0;
+    for (int k = 0; k < n; ++k) rows += L[k].hi[0] - L[k].lo[0];
     if ((arr[0]->K == 1 || (args[1].whole && args[2].whole && args[3].whole)) &&
-        (asked || jk::bin_pays(arr[3]->E, arr[1]->E, arr[0]->E - 1)))
+        (asked || jk::bin_pays(arr[3]->E, arr[1]->E, arr[0]->E - 1, rows)))
         rc = bin_cache(c, arr, p, L, n, s, &bc);
     if (rc) return rc;
     if (!bc) {

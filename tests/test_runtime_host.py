@@ -1337,3 +1337,27 @@ def test_binned_copies_of_many_small_boxes_are_few(refuse):
         assert len(mem.held) - held <= 64 * 9
     assert mem.refused == (201 if refuse else 0)
     c.close()
+
+
+@pytest.mark.parametrize("per_row,K,order", [(16, 4, 4), (16, 8, 2), (4, 4, 2), (11, 4, 4), (10, 4, 2)])
+def test_default_spmv_form_of_a_launch_a_partition(per_row, K, order, monkeypatch, tmp_path):
+    """2^20 rows without packing: a partition's launch takes the binned form when
+    its own rows have more than 5/8 of 2^22 entries; one box of them likewise."""
+    import json
+    path = tmp_path / "loops.jsonl"
+    monkeypatch.setenv("JACC_LOG", str(path))
+    n = 1 << 20
+    rp = (np.arange(n + 1) * per_row).astype(np.int32)
+    col, val = np.zeros(n * per_row, np.int32), np.zeros(n * per_row)
+    x, y = np.zeros(n), np.zeros(n)
+    c = jacc.Context(K, flags=jacc.INIT_DRYRUN | jacc.INIT_NO_PACK)
+    _dry_product(c, rp, col, val, x, y)
+    c.spmv(rp, col, val, x, y)
+    c.close()
+    c = jacc.Context(1, flags=jacc.INIT_DRYRUN)
+    _dry_product(c, rp, col, val, x, y)
+    c.loop(jacc.SPMV_CSR, jacc.bounds((0, n // K)),
+           [(rp, jacc.READ, 0, 1, 0), (col, jacc.READ, 0, 0, 1), (val, jacc.READ, 0, 0, 1),
+            (x, jacc.READ, 0, 0, 1), (y, jacc.WRITE, 0, 0, 0)])
+    c.close()
+    assert [json.loads(line)["cfg"]["order"] for line in path.read_text().splitlines()] == [order, order]
